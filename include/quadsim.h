@@ -110,16 +110,16 @@ enum {
   SIM_V_AUTO = 0,        /* the autotuned choice (fused MFMA until tuned)         */
   SIM_V_PLAIN = 1,       /* five kernels per step, intermediates through HBM      */
   SIM_V_FUSED_VALU = 2,  /* one fused kernel, actor on the vector ALUs            */
-  SIM_V_FUSED_MFMA = 3,  /* one fused kernel, actor on fp32 matrix cores, one env
-                            per lane (64 envs per wave)                           */
-  SIM_V_FUSED_MFMA4 = 4, /* one fused kernel, actor on fp32 matrix cores, four
-                            lanes per env (16 envs per wave); also the kernel of
-                            taped rollouts and of the backward recompute          */
-  SIM_V_FUSED_SPLIT = 5  /* one fused kernel, the quarter-lane actor split by
-                            neuron tile over the 4 waves of a workgroup (16 envs
-                            per workgroup, 16 lanes per env): four times the
-                            waves of SIM_V_FUSED_MFMA4 for small batches; fp32
-                            actor only, untaped rollouts and steps           */
+  SIM_V_FUSED_MFMA = 3,  /* one fused kernel, actor on matrix cores, 32 envs per wave:
+                            fp32 weights and inputs as exact sums of three bf16
+                            values, six bf16 products per fp32 product, fp32
+                            accumulation (closer to FP64 than an fp32 chain)     */
+  SIM_V_FUSED_MFMA4 = 4, /* the same with 16 envs per wave, four lanes per env (twice
+                            the waves; equal results)                            */
+  SIM_V_FUSED_SPLIT = 5  /* the same products, the actor split by neuron tile over the 4
+                            waves of a workgroup (16 envs per workgroup, 16 lanes
+                            per env) for small batches; equal results; fp32 actor
+                            only                                                 */
 };
 
 typedef struct sim_config {
@@ -178,9 +178,9 @@ int sim_step(sim_handle* h, const float* actor, const float* actions, float* rew
  * record_tape != 0 stores checkpoints for sim_backward; it requires
  * T <= max_tape_horizon and flags without TERMINATE and AUTORESET, else
  * SIM_E_STATE / SIM_E_INVAL.  A taped rollout runs on the kernel its
- * backward recomputes with (split-actor below 16384 envs with the fp32
- * actor, one env per lane from 65536 envs with the fp32 actor, else
- * quarter-lane), whatever variant is set or tuned, and also writes the
+ * backward recomputes with (fp32 actor: split-actor below 16384 envs, 32 envs
+ * per wave from 32769 envs, else 16 envs per wave; the quarter-lane kernel
+ * for the bf16 actor), whatever variant is set or tuned, and also writes the
  * backward's records of its last segments (the last one on the split-actor
  * kernel, else up to four), whose recomputes the next sim_backward skips. */
 int sim_rollout(sim_handle* h, const float* actor, int32_t T, float* rewards, uint8_t* dones,

@@ -316,7 +316,6 @@ int enqueue_rollout(sim_handle* h, int variant, int spl, const float* W, int T, 
       ++nl;
     }
   } else {
-    const bool mfma = variant == SIM_V_FUSED_MFMA;
     const int chunk = (spl <= 0 || spl > T) ? T : spl;
     float* rec = tape ? h->bw.seg[0] : nullptr;
     const int J = (T + K - 1) / K;
@@ -325,15 +324,16 @@ int enqueue_rollout(sim_handle* h, int variant, int spl, const float* W, int T, 
     const RecSpan rs{{rec, h->bw.seg[1], h->bw.seg[2], h->bw.seg[3]}, rec_from, K, rec_n};
     for (int t0 = 0; t0 < T; t0 += chunk) {
       const int n = (T - t0) < chunk ? (T - t0) : chunk;
-      if (variant == SIM_V_FUSED_MFMA4)
-        HIP_TRY(launch_fused4(h->dc, h->b, W, n, t0, rew, done, states, tape, K, nullptr, rs, st));
+      if (h->bf16 && variant == SIM_V_FUSED_MFMA4)
+        HIP_TRY(launch_bf16_quarter(h->dc, h->b, W, n, t0, rew, done, states, tape, K, nullptr, rs,
+                                    st));
+      else if (!h->bf16 && (variant == SIM_V_FUSED_MFMA || variant == SIM_V_FUSED_MFMA4))
+        HIP_TRY(launch_tile(variant == SIM_V_FUSED_MFMA ? 2 : 1, h->dc, h->b, W, n, t0, rew, done,
+                            states, tape, K, nullptr, rs, st));
       else if (variant == SIM_V_FUSED_SPLIT)
         HIP_TRY(launch_split(h->dc, h->b, W, n, t0, rew, done, states, tape, K, nullptr, rs, st));
-      else if (tape && mfma)
-        HIP_TRY(launch_fused_taped(h->dc, h->b, W, n, t0, rew, done, states, tape, K, nullptr, rs,
-                                   st));
       else
-        HIP_TRY(launch_fused(mfma, h->dc, h->b, W, nullptr, n, t0, rew, done, states, st));
+        HIP_TRY(launch_fused(h->dc, h->b, W, nullptr, n, t0, rew, done, states, st));
       ++nl;
     }
   }
@@ -505,17 +505,20 @@ int sim_step(sim_handle* h, const float* actor, const float* actions, float* rew
   if (v == SIM_V_PLAIN) {
     HIP_TRY(launch_plain_step(h->dc, h->b, h->p, actor, actor ? nullptr : actions, reward, done,
                               nullptr, st));
-  } else if (v == SIM_V_FUSED_MFMA4 && actor) {
-    HIP_TRY(launch_fused4(h->dc, h->b, actor, 1, 0, reward, done, nullptr, nullptr,
-                          h->cfg.ckpt_every, nullptr, RecSpan{}, st));
+  } else if (h->bf16 && v == SIM_V_FUSED_MFMA4 && actor) {
+    HIP_TRY(launch_bf16_quarter(h->dc, h->b, actor, 1, 0, reward, done, nullptr, nullptr,
+                                h->cfg.ckpt_every, nullptr, RecSpan{}, st));
+  } else if (!h->bf16 && (v == SIM_V_FUSED_MFMA || v == SIM_V_FUSED_MFMA4) && actor) {
+    HIP_TRY(launch_tile(v == SIM_V_FUSED_MFMA ? 2 : 1, h->dc, h->b, actor, 1, 0, reward, done,
+                        nullptr, nullptr, h->cfg.ckpt_every, nullptr, RecSpan{}, st));
   } else if (v == SIM_V_FUSED_SPLIT && actor) {
     HIP_TRY(launch_split(h->dc, h->b, actor, 1, 0, reward, done, nullptr, nullptr, 1, nullptr,
                          RecSpan{}, st));
   } else {
     // external actions run on the one-env-per-lane kernel (it has the
-    // action-input path); both kernels share the state layout
-    HIP_TRY(launch_fused(v != SIM_V_FUSED_VALU, h->dc, h->b, actor, actor ? nullptr : actions, 1,
-                         0, reward, done, nullptr, st));
+    // action-input path); the kernels share the state layout
+    HIP_TRY(launch_fused(h->dc, h->b, actor, actor ? nullptr : actions, 1, 0, reward, done,
+                         nullptr, st));
   }
   return SIM_OK;
 }
@@ -547,11 +550,11 @@ int sim_rollout(sim_handle* h, const float* actor, int32_t T, float* rewards, ui
   }
   // A taped rollout runs on the kernel the backward pass recomputes its
   // segments with (the recompute must reproduce the forward trajectory bit
-  // for bit): the split-actor kernel for small fp32 batches, else the
-  // quarter-lane kernel.
+  // for bit): the split-actor kernel for small fp32 batches, else the tile
+  // kernel.
   const TapedKernel tk = taped_kernel(h->dc);
   const int v = record_tape ? (tk == TAPED_SPLIT ? SIM_V_FUSED_SPLIT
-                               : tk == TAPED_LANE ? SIM_V_FUSED_MFMA : SIM_V_FUSED_MFMA4)
+                               : tk == TAPED_TILE2 ? SIM_V_FUSED_MFMA : SIM_V_FUSED_MFMA4)
                             : effective_variant(h);
   const int spl = effective_spl(h);
   float* tape = record_tape ? h->tape : nullptr;

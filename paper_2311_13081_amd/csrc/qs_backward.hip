@@ -83,7 +83,7 @@ __device__ inline void stage_reverse(const float* __restrict__ W, float* lds, bo
 }
 
 // Inputs of one reverse step: the recorded state and action, this lane's
-// ReLU mask word (quarter_mask: the signs of its 16 layer-1 and 16 layer-2
+// ReLU mask word (tile_mask: the signs of its 16 layer-1 and 16 layer-2
 // pre-activations, neurons 16 q + 4 k + r), the reward and state cotangents.
 struct StepIn {
   float x[NS], a[NA], dS[NS], dR;
@@ -153,9 +153,9 @@ constexpr int R_XCH = (4 + 4 + 10) * 64 * 4;
 // Batches up to this size run the split sweep (four times the waves; the
 // quarter-lane sweep leaves most SIMDs idle there).
 constexpr int REVERSE_SPLIT_MAX_ENVS = 4096;
-// Segments recorded by the one-env-per-lane forward (taped_kernel) run the
-// one-env-per-lane sweep (qs_reverse1.hip), which reads that kernel's ReLU
-// mask rows: one wave of 64 envs per SIMD and no repeated dynamics adjoint.
+// From this size (fp32 actor) the one-env-per-lane sweep (qs_reverse1.hip):
+// one wave of 64 envs per SIMD and no repeated dynamics adjoint.
+constexpr int REVERSE_LANE_MIN_ENVS = 65536;
 
 // Reverse sweep of one segment.  SPLIT = false: 16 envs per wave in the
 // quarter-lane layout.  SPLIT = true: 16 envs per workgroup of 4 waves, each
@@ -1064,7 +1064,7 @@ static hipError_t backward_segments(const DevCfg& c, const SimBufs& b, const Bwd
         BWD_TRY(hipStreamWaitEvent(st, bw.e_rec[buf], 0));
       }
     }
-    if (taped_kernel(c) == TAPED_LANE)
+    if (N >= REVERSE_LANE_MIN_ENVS && !(c.flags & F_ACTOR_BF16))
       BWD_TRY(launch_reverse1(c, b.theta, W, tape + (size_t)j * CK_F * N, bw.seg[buf], n, t0,
                               d_rewards, d_states, bw.lam, bw.gth, bw.dz[buf], st));
     else if (N <= REVERSE_SPLIT_MAX_ENVS)

@@ -123,6 +123,23 @@ __device__ inline void uniforms4(uint32_t klo, uint32_t khi, uint32_t env, uint3
   for (int i = 0; i < 4; ++i) u[i] = ((float)(c[i] >> 9) + 0.5f) * 0x1p-23f;
 }
 
+// Sine and cosine of 2 pi u, u a multiple of 2^-24 in (0, 1): taking off the
+// nearest quarter turn is exact and the rest, |t| <= pi/4, needs only the Taylor
+// polynomials (remainders below 2e-9).
+__device__ inline void sincos_turns(float u, float& sn, float& cs) {
+  const float k = rintf(4.0f * u);
+  const float t = 6.283185307179586f * fmaf(-0.25f, k, u), t2 = t * t;
+  const float ps =
+      fmaf(t * t2, fmaf(t2, fmaf(t2, fmaf(t2, 1.0f / 362880, -1.0f / 5040), 1.0f / 120), -1.0f / 6), t);
+  const float pc = fmaf(
+      t2, fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, -1.0f / 3628800, 1.0f / 40320), -1.0f / 720), 1.0f / 24), -0.5f),
+      1.0f);
+  const int q = (int)k;  // quarter turns, 0 .. 4
+  const float a = q & 1 ? ps : pc, b = q & 1 ? pc : ps;
+  cs = __uint_as_float(__float_as_uint(a) ^ ((uint32_t)((q + 1) & 2) << 30));
+  sn = __uint_as_float(__float_as_uint(b) ^ ((uint32_t)(q & 2) << 30));
+}
+
 // Per-env parameters: nominal times U(lo, hi) factors when randomised.
 __device__ inline void env_params(const DevCfg& c, uint32_t env, float th[NP]) {
   float u[8];
@@ -165,10 +182,35 @@ __device__ inline void disturbance(const DevCfg& c, uint32_t env, uint32_t episo
   }
 }
 
+// Two standard normals by Box-Muller: r cos(2 pi u1), r sin(2 pi u1), r = sqrt(-2
+// ln u0).
+__device__ inline void box_muller(float u0, float u1, float& zc, float& zs) {
+  const float r = sqrtf(-2.0f * logf(u0));
+  float sn, cs;
+  sincos_turns(u1, sn, cs);
+  zc = r * cs;
+  zs = r * sn;
+}
+
+// Noise std of state feature i (p, R, v, w; 0 past the end).
+__device__ inline float noise_std(const DevCfg& c, int i) {
+  return i < 3 ? c.noise[0] : i < 12 ? c.noise[1] : i < 15 ? c.noise[2] : i < 18 ? c.noise[3] : 0.0f;
+}
+
+// Which draws a kernel makes: with the bf16 actor (ACT 1) the noise and the
+// start states keep the library's sine and cosine, else (ACT 0) sincos_turns;
+// ACT -1 decides by the flag.  (The bf16 actor rounds its inputs to 8 bits: an
+// input that differs in the last place gives some of them another value.)
+template <int ACT>
+__device__ inline bool library_draws(const DevCfg& c) {
+  return ACT < 0 ? (c.flags & F_ACTOR_BF16) != 0 : ACT == 1;
+}
+
 // Adds the actor's observation noise to the 18 state features f (p, R
 // row-major, v, w) of step t_ep of an episode: f_i += sigma_g z_i, z standard
 // normal by Box-Muller on consecutive uniform pairs of stream STREAM_NOISE,
 // blocks 5 t_ep .. 5 t_ep + 4.  No-op with the flag off.
+template <int ACT = -1>
 __device__ inline void add_obs_noise(const DevCfg& c, uint32_t env, uint32_t episode, int t_ep,
                                      float f[18]) {
   if (!(c.flags & F_OBS_NOISE)) return;
@@ -179,19 +221,26 @@ __device__ inline void add_obs_noise(const DevCfg& c, uint32_t env, uint32_t epi
               STREAM_NOISE, u + 4 * bk);
 #pragma unroll
   for (int i = 0; i < 9; ++i) {
-    const float r = sqrtf(-2.0f * logf(u[2 * i]));
-    float sn, cs;
-    sincosf(6.283185307179586f * u[2 * i + 1], &sn, &cs);
-    const int g0 = (2 * i) < 3 ? 0 : (2 * i) < 12 ? 1 : (2 * i) < 15 ? 2 : 3;
-    const int g1 = (2 * i + 1) < 3 ? 0 : (2 * i + 1) < 12 ? 1 : (2 * i + 1) < 15 ? 2 : 3;
-    f[2 * i] += c.noise[g0] * r * cs;
-    f[2 * i + 1] += c.noise[g1] * r * sn;
+    const float s0 = noise_std(c, 2 * i), s1 = noise_std(c, 2 * i + 1);
+    if (library_draws<ACT>(c)) {
+      const float r = sqrtf(-2.0f * logf(u[2 * i]));
+      float sn, cs;
+      sincosf(6.283185307179586f * u[2 * i + 1], &sn, &cs);
+      f[2 * i] += s0 * r * cs;
+      f[2 * i + 1] += s1 * r * sn;
+    } else {
+      float zc, zs;
+      box_muller(u[2 * i], u[2 * i + 1], zc, zs);
+      f[2 * i] = fmaf(s0, zc, f[2 * i]);
+      f[2 * i + 1] = fmaf(s1, zs, f[2 * i + 1]);
+    }
   }
 }
 
 // Episode-start state for (env, episode): p, attitude (angle about a uniform
 // axis), v, w uniform in their ranges, rotors at the env's hover speed wh
-// (constant per env, so loops compute it once).
+// (constant per env, so loops compute it once).  ACT: library_draws.
+template <int ACT = -1>
 __device__ inline void reset_draw(const DevCfg& c, uint32_t env, uint32_t episode, float wh,
                                   float s[NS]) {
   float u[12];
@@ -201,11 +250,13 @@ __device__ inline void reset_draw(const DevCfg& c, uint32_t env, uint32_t episod
 #pragma unroll
   for (int i = 0; i < 3; ++i) s[i] = c.init_pos * (2.0f * u[i] - 1.0f);
   const float z = 2.0f * u[3] - 1.0f;
-  const float phi = 6.283185307179586f * u[4];
   const float half = 0.5f * c.init_angle * u[5];
   const float r = sqrtf(fmaxf(0.0f, 1.0f - z * z));
   float sp, cp, sa, ca;
-  sincosf(phi, &sp, &cp);
+  if (library_draws<ACT>(c))
+    sincosf(6.283185307179586f * u[4], &sp, &cp);
+  else
+    sincos_turns(u[4], sp, cp);
   sincosf(half, &sa, &ca);
   s[3] = ca;
   s[4] = sa * r * cp;
@@ -230,15 +281,17 @@ __device__ inline void reset_draw(const DevCfg& c, uint32_t env, uint32_t episod
 constexpr int RESERVE_PERIOD = 16;  // power of 2
 constexpr int NRES = NS - NA;      // drawn-ahead state values
 
+template <int ACT = -1>
 __device__ inline void draw_ahead(const DevCfg& c, uint32_t env, uint32_t episode, float wh,
                                   float nx[NRES]) {
   float s0[NS];
-  reset_draw(c, env, episode, wh, s0);
+  reset_draw<ACT>(c, env, episode, wh, s0);
 #pragma unroll
   for (int i = 0; i < NRES; ++i) nx[i] = s0[i];
 }
 
 // Start state of episode `episode`: the reserve if there is one, else drawn.
+template <int ACT = -1>
 __device__ inline void reset_from_reserve(const DevCfg& c, uint32_t env, uint32_t episode,
                                           float wh, const float nx[NRES], bool& have,
                                           float s[NS]) {
@@ -249,7 +302,7 @@ __device__ inline void reset_from_reserve(const DevCfg& c, uint32_t env, uint32_
     for (int i = NRES; i < NS; ++i) s[i] = wh;
     have = false;
   } else {
-    reset_draw(c, env, episode, wh, s);
+    reset_draw<ACT>(c, env, episode, wh, s);
   }
 }
 
@@ -341,13 +394,15 @@ __device__ inline void deriv(const Body<R>& B, R arm, R km, R g, const R x[NS], 
   const R ax = DIST ? B.ax : R(0), ay = DIST ? B.ay : R(0), az = DIST ? B.az : R(0);
   dx[7] = R(2) * (qx * qz + qw * qy) * s;
   dx[8] = R(2) * (qy * qz - qw * qx) * s;
-  dx[9] = (n2 - R(2) * (qx * qx + qy * qy)) * s;
+  const R pz = n2 - R(2) * (qx * qx + qy * qy);
   if (DIST) {
     dx[7] += ax;
     dx[8] += ay;
-    dx[9] += az;
+    dx[9] = pz * s + az;
+    dx[9] -= g;
+  } else {
+    dx[9] = pz * s - g;
   }
-  dx[9] -= g;
   // Euler: J wdot = tau + tau_r - w x (J w)
   const R ttx = DIST ? tx + B.dtx : tx, tty = DIST ? ty + B.dty : ty,
           ttz = DIST ? tz + B.dtz : tz;
@@ -361,28 +416,37 @@ __device__ inline void deriv(const Body<R>& B, R arm, R km, R g, const R x[NS], 
 }
 
 // One classical RK4 step, set points held.  Optional renormalisation of q.
-template <typename R, bool DIST = true>
+// between(k), k = 0 .. 3, is called ahead of each right-hand side: work that a
+// kernel interleaves with the integration.
+struct Nothing {
+  __device__ inline void operator()(int) const {}
+};
+template <typename R, bool DIST = true, typename F = Nothing>
 __device__ inline void rk4_step(const Body<R>& B, R arm, R km, R g, R h, bool renorm, R x[NS],
-                                const R u[4]) {
+                                const R u[4], F&& between = F()) {
   R k[NS], acc[NS], t[NS];
+  between(0);
   deriv<R, DIST>(B, arm, km, g, x, u, k);
 #pragma unroll
   for (int i = 0; i < NS; ++i) {
     acc[i] = k[i];
     t[i] = x[i] + R(0.5) * h * k[i];
   }
+  between(1);
   deriv<R, DIST>(B, arm, km, g, t, u, k);
 #pragma unroll
   for (int i = 0; i < NS; ++i) {
     acc[i] += R(2) * k[i];
     t[i] = x[i] + R(0.5) * h * k[i];
   }
+  between(2);
   deriv<R, DIST>(B, arm, km, g, t, u, k);
 #pragma unroll
   for (int i = 0; i < NS; ++i) {
     acc[i] += R(2) * k[i];
     t[i] = x[i] + h * k[i];
   }
+  between(3);
   deriv<R, DIST>(B, arm, km, g, t, u, k);
 #pragma unroll
   for (int i = 0; i < NS; ++i) x[i] = x[i] + (h / R(6)) * (acc[i] + k[i]);
@@ -452,6 +516,55 @@ __device__ inline uint32_t episode_end(const DevCfg& c, const float s[NS], int t
 __device__ __forceinline__ uint32_t opaque(uint32_t v) {
   __asm__ volatile("" : "+v"(v));
   return v;
+}
+
+// c ? a : b by value.  (The conditional operator on two array elements is an
+// lvalue, which the compiler may lower to a load through a selected address;
+// the array then leaves the registers.)
+__device__ __forceinline__ float pick(bool c, float a, float b) { return c ? a : b; }
+
+// Element at a byte offset from a wave-uniform base: the row and step parts of
+// an address stay in scalar registers, the lane's part is 32 bits.
+template <typename T>
+__device__ __forceinline__ T& at_byte(T* base, uint32_t off) {
+  return *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + off);
+}
+
+// Stores rows 0 .. K - 1 of v to a [K][N] array for an env that sits on SUB
+// lanes: lane sub writes rows sub, sub + SUB, ..., one store instruction per SUB
+// rows and no branch except around the last, partial group.  off: the lane's
+// byte offset of (row sub, env), 4 (sub N + env).
+template <int SUB, int K>
+__device__ __forceinline__ void store_rows(float* base, int N, uint32_t off, int sub,
+                                           const float* v) {
+#pragma unroll
+  for (int r = 0; r < K; r += SUB) {
+    float x = v[r];
+#pragma unroll
+    for (int i = 1; i < SUB; ++i)
+      if (r + i < K) x = pick(sub == i, v[r + i], x);
+    float* row = base + (size_t)r * N;
+    if (r + SUB <= K) {
+      at_byte(row, off) = x;
+    } else if (r + sub < K) {
+      at_byte(row, off) = x;
+    }
+  }
+}
+
+// Stores an env's NA actions to slot `slot` (per env) of the history ring; the
+// ring's 128 rows need 64-bit offsets.  off: as in store_rows.
+template <int SUB>
+__device__ __forceinline__ void store_ring(float* ring, int N, int slot, uint32_t off, int sub,
+                                           const float a[NA]) {
+  float* p = ring + ((size_t)slot * NA * N + (off >> 2));
+#pragma unroll
+  for (int r = 0; r < NA; r += SUB) {
+    float x = a[r];
+#pragma unroll
+    for (int i = 1; i < SUB; ++i) x = pick(sub == i, a[r + i], x);
+    p[(size_t)r * N] = x;
+  }
 }
 
 // Stages weights into LDS: dst[i] = W[src] with src = index(i) (rounded to

@@ -46,16 +46,9 @@ hipError_t launch_dyn_rollout(const DevCfg& c, const SimBufs& b, const float* ac
 // Per-step record of the backward recompute, REC_F rows per env: x_t (17),
 // a_t (4), layer-1 and layer-2 pre-activations (64 + 64), the 18 state
 // features of the observation o_t (as the actor saw them, noise included)
-// and 4 rows of ReLU masks, in the layout of the kernel family that writes
-// them (the reverse sweep of the same family reads them).  The
-// one-env-per-lane kernel uses its matrix-core tile layout: lane l of a
-// 64-env block keeps bit 16 n + 4 bb + v of word w = n / 2 (layer 1, words
-// 0-1; layer 2, words 2-3) set when neuron 16 n + 4 (l / 16) + v of env 16 bb
-// + l % 16 of the block has a positive pre-activation; the word sits in row
-// REC_M + w, column l.  The quarter-lane and split-actor kernels write one
-// word per env and quarter k, in row REC_M + k of the env's column: bit
-// 8 n + r for layer-1 neuron 16 n + 4 k + r, bit 8 n + 4 + r for layer 2
-// (quarter_mask).
+// and 4 rows of ReLU masks: one word per env and lane group k of the tile
+// layout, in row REC_M + k of the env's column: bit 8 n + r for layer-1 unit 16
+// n + 4 k + r, bit 8 n + 4 + r for layer 2 (tile_mask).
 // The 128 history features of o_t are not stored per step: they are the
 // actions of the 32 previous steps.  After the n step records of a segment
 // comes its action tape: per 64-env block, (NH + n) slots of NA rows, slot s
@@ -123,44 +116,44 @@ inline bool rec_span_ok(const RecSpan& rs) {
 }
 hipError_t launch_recompute(const DevCfg& c, const SimBufs& b, const float* W, int T,
                             const float* ck_in, float* rec, hipStream_t st);
-// Quarter-lane fused kernel (qs_fused4.hip): 16 envs per wave, 4 lanes per
-// env; the kernel of taped rollouts (tape: CK_F-row checkpoints every
-// ckpt_every steps).  With ck_in != NULL it starts from that checkpoint and
-// leaves the env state alone (the backward's recompute).  With rs.buf[0] !=
+// Tile kernel (qs_tile.hip): 16 tiles envs per wave (tiles = 1 or 2), actor on
+// bf16 matrix cores with split fp32 operands; the kernel of policy rollouts and of taped rollouts (tape: CK_F-row checkpoints
+// every ckpt_every steps).  With ck_in != NULL it starts from that checkpoint
+// and leaves the env state alone (the backward's recompute).  With rs.buf[0] !=
 // NULL it writes the backward's record of the span rs (the recompute: its
 // one segment; a taped rollout: its last segments).
-hipError_t launch_fused4(const DevCfg& c, const SimBufs& b, const float* W, int T, int t_base,
-                         float* rewards, uint8_t* dones, float* states, float* tape,
-                         int ckpt_every, const float* ck_in, const RecSpan& rs, hipStream_t st);
+hipError_t launch_tile(int tiles, const DevCfg& c, const SimBufs& b, const float* W, int T,
+                       int t_base, float* rewards, uint8_t* dones, float* states, float* tape,
+                       int ckpt_every, const float* ck_in, const RecSpan& rs, hipStream_t st);
+// The same modes with the bf16 actor (qs_fused4.hip), 16 envs per wave, 4 lanes
+// per env.
+hipError_t launch_bf16_quarter(const DevCfg& c, const SimBufs& b, const float* W, int T,
+                               int t_base, float* rewards, uint8_t* dones, float* states,
+                               float* tape, int ckpt_every, const float* ck_in, const RecSpan& rs,
+                               hipStream_t st);
 // Split-actor fused kernel (qs_split.hip): 16 envs per workgroup of 4 waves,
 // wave w evaluating neuron tile w of layers 1 and 2; tape and record modes as
-// the quarter-lane kernel, whose results it reproduces bit for bit.
+// the tile kernel, whose results it reproduces bit for bit.
 hipError_t launch_split(const DevCfg& c, const SimBufs& b, const float* W, int T, int t_base,
                         float* rewards, uint8_t* dones, float* states, float* tape,
                         int ckpt_every, const float* ck_in, const RecSpan& rs, hipStream_t st);
 // The kernel of taped rollouts and of their backward recompute (the two must
 // agree bit for bit): with the fp32 actor the split-actor kernel below 16384
-// envs (the quarter-lane kernel leaves SIMDs idle there), the one-env-per-lane
-// kernel from 65536 envs (one wave per SIMD, no repeated dynamics), the
-// quarter-lane kernel between them and for the bf16 actor.
+// envs (the tile kernel leaves SIMDs idle there), two tiles per wave from
+// 32769 envs (with one, more than two waves per SIMD would be needed), one
+// tile between them; the quarter-lane kernel for the bf16 actor.
 constexpr int TAPE_SPLIT_MAX_ENVS = 16384;
-constexpr int TAPE_LANE_MIN_ENVS = 65536;
-enum TapedKernel { TAPED_SPLIT, TAPED_QUARTER, TAPED_LANE };
+constexpr int TAPE_TILE2_MIN_ENVS = 32769;
+enum TapedKernel { TAPED_SPLIT, TAPED_TILE1, TAPED_TILE2, TAPED_BF16 };
 inline TapedKernel taped_kernel(const DevCfg& c) {
-  if (c.flags & F_ACTOR_BF16) return TAPED_QUARTER;
+  if (c.flags & F_ACTOR_BF16) return TAPED_BF16;
   if (c.n_envs < TAPE_SPLIT_MAX_ENVS) return TAPED_SPLIT;
-  return c.n_envs >= TAPE_LANE_MIN_ENVS ? TAPED_LANE : TAPED_QUARTER;
+  return c.n_envs >= TAPE_TILE2_MIN_ENVS ? TAPED_TILE2 : TAPED_TILE1;
 }
-// One-env-per-lane fused kernel (qs_fused.hip), actor on fp32 MFMA or VALU.
-hipError_t launch_fused(bool mfma, const DevCfg& c, const SimBufs& b, const float* W,
-                        const float* ext_act, int T, int t_base, float* rewards, uint8_t* dones,
-                        float* states, hipStream_t st);
-// The same kernel (fp32 matrix-core actor) with the tape mode of
-// launch_fused4 and the record mode for one or more segments (rs.buf[0] ==
-// NULL: no record).
-hipError_t launch_fused_taped(const DevCfg& c, const SimBufs& b, const float* W, int T,
-                              int t_base, float* rewards, uint8_t* dones, float* states,
-                              float* tape, int ckpt_every, const float* ck_in, const RecSpan& rs,
-                              hipStream_t st);
+// One-env-per-lane fused kernel (qs_fused.hip): the actor on the vector ALUs,
+// or the bf16 actor under its flag, or given actions (ext_act, [T][4][N]).
+hipError_t launch_fused(const DevCfg& c, const SimBufs& b, const float* W, const float* ext_act,
+                        int T, int t_base, float* rewards, uint8_t* dones, float* states,
+                        hipStream_t st);
 
 }  // namespace qs

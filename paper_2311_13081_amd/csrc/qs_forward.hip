@@ -1,11 +1,16 @@
 // Forward kernels of the batched quadrotor step: initialisation and reset,
 // snapshots, and the plain five-kernel step (the fused kernels live in
-// qs_fused.hip and qs_fused4.hip, dynamics-only rollouts in qs_dynamics.hip).
+// qs_tile.hip, qs_split.hip and qs_fused.hip, dynamics-only rollouts in qs_dynamics.hip).
 //
 // Layout: one env per lane, struct-of-arrays in HBM ([K][N]) so every global
 // access of a wave is a contiguous 256-byte segment.
-#include "qs_actor.h"
+// Fused multiply-adds only where one expression of the source holds the
+// product and the sum: the kernels that promise equal results then round the
+// shared arithmetic the same way (left to the optimiser, fusing depends on what
+// surrounds the inlined code).
+#pragma clang fp contract(on)
 #include "qs_forward.h"
+#include "qs_tile.h"
 
 namespace qs {
 
@@ -136,7 +141,7 @@ __global__ void __launch_bounds__(256) k_plain_obs(DevCfg c, SimBufs b, float* _
   SetPoint sp;
   sp.load(c, N, e);
   sp.apply(c, f);
-  add_obs_noise(c, (uint32_t)e, (uint32_t)b.ep[e], b.t_ep[e], f);
+  add_obs_noise<0>(c, (uint32_t)e, (uint32_t)b.ep[e], b.t_ep[e], f);
 #pragma unroll
   for (int i = 0; i < 18; ++i) obs[i * N + e] = f[i];
   const int h = b.head[e];
@@ -148,163 +153,151 @@ __global__ void __launch_bounds__(256) k_plain_obs(DevCfg c, SimBufs b, float* _
   }
 }
 
-// The three actor layers of the plain path on fp32 matrix cores, in the
-// product order and lane layout of the fused kernel's actor; only the layer
-// outputs go through HBM ([64][N], [64][N], [4][N]).  The hidden layers give
-// each 64-env block two waves, one per half of the neuron tiles (a
-// workgroup of four waves takes 128 envs), so two waves share a SIMD and one
-// wave's loads and stores overlap the other's products.  Lanes of envs past
-// the batch load the last env and store nothing.
-//
-// Layer 1, h1[64][N] = ReLU(W1 obs + b1): 147 rank-1 updates per 16-neuron
-// tile with the 4-block 16x16x1 product, the bias first (a constant input 1);
-// B = input k of the lane's env, A = the weights of 16 neurons for all four
-// 16-env blocks.  Result register 4 bb + v of tile n holds neuron 16 n + 4 g
-// + v of env 16 bb + i (lane 16 g + i).
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2)))
-k_plain_l1_mfma(int N, const float* __restrict__ W, const float* __restrict__ in,
-                float* __restrict__ out) {
-  __shared__ __attribute__((aligned(16))) float sW[NHID * M_W1_LD];
+// The three actor layers of the plain path: the tile kernel's products in its
+// order and operand layout (qs_tile.h), two 16-env tiles per wave, so the
+// actions equal the fused kernels' bit for bit; only the layer outputs go
+// through HBM ([64][N], [64][N], [4][N]).  Lanes of envs past the batch load
+// the last env and store nothing.
+constexpr int P_ENVS = 128;  // envs of a workgroup (4 waves of 2 tiles)
+
+// h1[64][N] = ReLU(W1 obs + b1).
+__global__ void __launch_bounds__(256) k_plain_l1(int N, const float* __restrict__ W,
+                                                  const float* __restrict__ in,
+                                                  float* __restrict__ out) {
+  __shared__ u4t sW[T_G1 * 3 * 64];
   const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
-  const int wv = threadIdx.x >> 6, th = wv & 1;  // tiles 2 th, 2 th + 1
-  const int first = blockIdx.x * 128 + 64 * (wv >> 1);
+  const int first = blockIdx.x * P_ENVS + 32 * (threadIdx.x >> 6);
   // every input load in flight before the weights are staged
-  const int e = min(first + lane, N - 1);
-  float xin[NO];
+  float v[2][4][8], F[2][5];
 #pragma unroll
-  for (int k = 0; k < NO; ++k) xin[k] = in[(size_t)k * N + e];
+  for (int b = 0; b < 2; ++b) {
+    const int e = min(first + 16 * b + li, N - 1);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[b][c][i] = in[(size_t)(18 + NA * (8 * c + i) + lg) * N + e];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) F[b][i] = in[(size_t)min(4 * i + lg, 17) * N + e];
+    if (lg >= 2) F[b][4] = 0.0f;  // features 18, 19: padding
+  }
   __builtin_amdgcn_sched_barrier(0);
-  stage_lds(sW, NHID * M_W1_LD, W, [](int i) {
-    const int r = i / M_W1_LD, k = i % M_W1_LD;
-    return k == 0 ? OFF_B1 + r : k <= NO ? OFF_W1 + r * NO + k - 1 : -1;
-  });
+  stage_fragments<4>(W, sW, 0, T_G1);
   __syncthreads();
   if (first >= N) return;
-  const f16 zero16 = {};
-  f16 acc[2];
+  f4t a1[4][2];
 #pragma unroll
-  for (int kc = 0; kc < M_W1_LD / 4; ++kc) {
-    f4 w[2];
+  for (int n = 0; n < 4; ++n)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-      w[j] = *reinterpret_cast<const f4*>(&sW[(16 * (2 * th + j) + li) * M_W1_LD + 4 * kc]);
+    for (int r = 0; r < 4; ++r) a1[n][0][r] = a1[n][1][r] = W[OFF_B1 + 16 * n + 4 * lg + r];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const int col = 4 * kc + kk;  // 0: bias, k + 1: input k
-      if (col == 0) {
+  for (int c = 0; c < 5; ++c) {
+    u4t x[2][3];
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[j] = __builtin_amdgcn_mfma_f32_16x16x1f32(w[j][0], 1.0f, zero16, 0, 0, 0);
-      } else if (col <= NO) {
+    for (int b = 0; b < 2; ++b) {
+      if (c == 4) {
+        state_operand(F[b], x[b]);
+        continue;
+      }
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[j] = __builtin_amdgcn_mfma_f32_16x16x1f32(w[j][kk], xin[col - 1], acc[j], 0, 0, 0);
+      for (int q = 0; q < 4; ++q) {
+        uint32_t p[3];
+        split_pair(v[b][c & 3][2 * q], v[b][c & 3][2 * q + 1], p);
+#pragma unroll
+        for (int s = 0; s < 3; ++s) x[b][s][q] = p[s];
       }
     }
+    Frags<4> f;
+    f.load(sW, 4 * c, lane);
+    tile_products<4, 2>(f, x, a1);
   }
 #pragma unroll
-  for (int bb = 0; bb < 4; ++bb) {
-    const int oe = first + 16 * bb + li;
+  for (int b = 0; b < 2; ++b) {
+    const int oe = first + 16 * b + li;
     if (oe < N)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int n = 0; n < 4; ++n)
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-          out[(size_t)(16 * (2 * th + j) + 4 * lg + v) * N + oe] = relu_bits(acc[j][4 * bb + v]);
+        for (int r = 0; r < 4; ++r)
+          out[(size_t)(16 * n + 4 * lg + r) * N + oe] = relu_bits(a1[n][b][r]);
   }
 }
 
-// Layer 2, h2[64][N] = ReLU(W2 h1 + b2): 16x16x4 products, chain (n2, bb)
-// for neurons 16 n2.. and envs 16 bb..; the K-chunk of product (n, v) is
-// the inputs {16 n + 4 g + v} (lane 16 g + i holds input 16 n + 4 g + v of
-// env 16 bb + i), the bias tile the accumulator input of the first product.
-// Result register v of chain (n2, bb): neuron 16 n2 + 4 g + v of env 16 bb + i.
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2)))
-k_plain_l2_mfma(int N, const float* __restrict__ W, const float* __restrict__ in,
-                float* __restrict__ out) {
-  __shared__ __attribute__((aligned(16))) float sW[NHID * M_W2_LD];
-  __shared__ __attribute__((aligned(16))) float sb[NHID];
+// h2[64][N] = ReLU(W2 h1 + b2).
+__global__ void __launch_bounds__(256) k_plain_l2(int N, const float* __restrict__ W,
+                                                  const float* __restrict__ in,
+                                                  float* __restrict__ out) {
+  __shared__ u4t sW[(T_G - T_G1) * 3 * 64];
   const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
-  const int wv = threadIdx.x >> 6, th = wv & 1;  // tiles n2 = 2 th, 2 th + 1
-  const int first = blockIdx.x * 128 + 64 * (wv >> 1);
-  // every input load in flight before the weights are staged: x[n][v][bb]
-  float x[4][4][4];
+  const int first = blockIdx.x * P_ENVS + 32 * (threadIdx.x >> 6);
+  f4t h1[4][2];
 #pragma unroll
-  for (int bb = 0; bb < 4; ++bb) {
-    const int e = min(first + 16 * bb + li, N - 1);
+  for (int b = 0; b < 2; ++b) {
+    const int e = min(first + 16 * b + li, N - 1);
 #pragma unroll
     for (int n = 0; n < 4; ++n)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) x[n][v][bb] = in[(size_t)(16 * n + 4 * lg + v) * N + e];
+      for (int r = 0; r < 4; ++r) h1[n][b][r] = in[(size_t)(16 * n + 4 * lg + r) * N + e];
   }
   __builtin_amdgcn_sched_barrier(0);
-  stage_lds(sW, NHID * M_W2_LD, W, [](int i) {
-    const int r = i / M_W2_LD, k = i % M_W2_LD;
-    return k < NHID ? OFF_W2 + r * NHID + k : -1;
-  });
-  stage_lds(sb, NHID, W, [](int i) { return OFF_B2 + i; });
+  stage_fragments<4>(W, sW, T_G1, T_G);
   __syncthreads();
   if (first >= N) return;
-  f4 acc[2][4];
+  f4t a2[4][2];
 #pragma unroll
-  for (int n = 0; n < 4; ++n) {
+  for (int n = 0; n < 4; ++n)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int n2 = 2 * th + j;
-      const f4 w = *reinterpret_cast<const f4*>(&sW[(16 * n2 + li) * M_W2_LD + 16 * n + 4 * lg]);
-      const f4 b2 = *reinterpret_cast<const f4*>(&sb[16 * n2 + 4 * lg]);
+    for (int r = 0; r < 4; ++r) a2[n][0][r] = a2[n][1][r] = W[OFF_B2 + 16 * n + 4 * lg + r];
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
+  for (int m = 0; m < 2; ++m) {
+    u4t x[2][3];
 #pragma unroll
-        for (int bb = 0; bb < 4; ++bb)
-          acc[j][bb] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-              w[v], x[n][v][bb], (n == 0 && v == 0) ? b2 : acc[j][bb], 0, 0, 0);
-    }
+    for (int b = 0; b < 2; ++b) hidden_operand(h1[2 * m][b], h1[2 * m + 1][b], x[b]);
+    Frags<4> f;
+    f.load(sW, 4 * m, lane);
+    tile_products<4, 2>(f, x, a2);
   }
 #pragma unroll
-  for (int bb = 0; bb < 4; ++bb) {
-    const int oe = first + 16 * bb + li;
+  for (int b = 0; b < 2; ++b) {
+    const int oe = first + 16 * b + li;
     if (oe < N)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int n = 0; n < 4; ++n)
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-          out[(size_t)(16 * (2 * th + j) + 4 * lg + v) * N + oe] = relu_bits(acc[j][bb][v]);
+        for (int r = 0; r < 4; ++r)
+          out[(size_t)(16 * n + 4 * lg + r) * N + oe] = relu_bits(a2[n][b][r]);
   }
 }
 
-// Layer 3, act[4][N] = tanh(W3 h2 + b3): the input registers of the fused
-// kernel's layer 3 (register v of (n2, bb) in lane 16 g + i: input 16 n2 + 4 g
-// + v of env 16 bb + i) loaded from h2, then the same 4x4x1 products and
-// cross-lane sums (layer3_one_lane).
-__global__ void __launch_bounds__(256) k_plain_l3_mfma(int N, const float* __restrict__ W,
-                                                       const float* __restrict__ in,
-                                                       float* __restrict__ out) {
-  __shared__ __attribute__((aligned(16))) float sW[NA * M_W2_LD + NA];  // W3 rows, then b3
+// act[4][N] = tanh(W3 h2 + b3).
+__global__ void __launch_bounds__(256) k_plain_l3(int N, const float* __restrict__ W,
+                                                  const float* __restrict__ in,
+                                                  float* __restrict__ out) {
+  __shared__ __attribute__((aligned(16))) float sW[NA * T_W3_LD + NA];  // W3 rows, then b3
   const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
-  const int first = blockIdx.x * blockDim.x + threadIdx.x - lane;
-  f4 h[4][4];
+  const int first = blockIdx.x * P_ENVS + 32 * (threadIdx.x >> 6);
+  f4t h2[4][2];
 #pragma unroll
-  for (int bb = 0; bb < 4; ++bb) {
-    const int e = min(first + 16 * bb + li, N - 1);
+  for (int b = 0; b < 2; ++b) {
+    const int e = min(first + 16 * b + li, N - 1);
 #pragma unroll
-    for (int n2 = 0; n2 < 4; ++n2)
+    for (int n = 0; n < 4; ++n)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) h[n2][bb][v] = in[(size_t)(16 * n2 + 4 * lg + v) * N + e];
+      for (int r = 0; r < 4; ++r) h2[n][b][r] = in[(size_t)(16 * n + 4 * lg + r) * N + e];
   }
-  __builtin_amdgcn_sched_barrier(0);
-  stage_lds(sW, NA * M_W2_LD, W, [](int i) {
-    const int r = i / M_W2_LD, k = i % M_W2_LD;
+  stage_lds(sW, NA * T_W3_LD, W, [](int i) {
+    const int r = i / T_W3_LD, k = i % T_W3_LD;
     return k < NHID ? OFF_W3 + r * NHID + k : -1;
   });
-  stage_lds(sW + NA * M_W2_LD, NA, W, [](int i) { return OFF_B3 + i; });
+  stage_lds(sW + NA * T_W3_LD, NA, W, [](int i) { return OFF_B3 + i; });
   __syncthreads();
   if (first >= N) return;
   float z3[NA];
-  layer3_one_lane(sW, 0, NA * M_W2_LD, h, z3);
-  if (first + lane < N)
+  tile_layer3<2>(sW, sW + NA * T_W3_LD, h2, z3);
+  const int oe = first + 16 * (lg & 1) + li;
+  if (oe < N)
 #pragma unroll
-    for (int o = 0; o < NA; ++o) out[(size_t)o * N + first + lane] = tanh_act(z3[o]);
+    for (int o = 0; o < NA; ++o)
+      if ((o & 1) == (lg >> 1)) out[(size_t)o * N + oe] = tanh_act(z3[o]);
 }
 
 // Dynamics, reward, history push, episode bookkeeping and reset.  DIST: the
@@ -497,10 +490,10 @@ hipError_t launch_plain_step(const DevCfg& c, const SimBufs& b, const PlainBufs&
   const float* act = ext_act;
   if (!ext_act) {
     hipLaunchKernelGGL(k_plain_obs, g, blk, 0, st, c, b, p.obs);
-    const dim3 g2(nblk(N, 128));  // 128 envs per workgroup (two waves per 64-env block)
-    hipLaunchKernelGGL(k_plain_l1_mfma, g2, blk, 0, st, N, W, p.obs, p.h1);
-    hipLaunchKernelGGL(k_plain_l2_mfma, g2, blk, 0, st, N, W, p.h1, p.h2);
-    hipLaunchKernelGGL(k_plain_l3_mfma, g, blk, 0, st, N, W, p.h2, p.act);
+    const dim3 g2(nblk(N, P_ENVS));
+    hipLaunchKernelGGL(k_plain_l1, g2, blk, 0, st, N, W, p.obs, p.h1);
+    hipLaunchKernelGGL(k_plain_l2, g2, blk, 0, st, N, W, p.h1, p.h2);
+    hipLaunchKernelGGL(k_plain_l3, g2, blk, 0, st, N, W, p.h2, p.act);
     act = p.act;
   }
   const bool ex = (c.flags & (F_DISTURB | F_OBS_NOISE)) != 0 || c.target != nullptr;
@@ -539,15 +532,14 @@ hipError_t launch_recompute(const DevCfg& c, const SimBufs& b, const float* W, i
                             const float* ck_in, float* rec, hipStream_t st) {
   // the kernel of taped rollouts, in record mode: one segment of T steps
   const RecSpan one{{rec, nullptr, nullptr, nullptr}, 0, T, T};
-  switch (taped_kernel(c)) {
-    case TAPED_SPLIT:
-      return launch_split(c, b, W, T, 0, nullptr, nullptr, nullptr, nullptr, 1, ck_in, one, st);
-    case TAPED_LANE:
-      return launch_fused_taped(c, b, W, T, 0, nullptr, nullptr, nullptr, nullptr, 1, ck_in, one,
-                                st);
-    default:
-      return launch_fused4(c, b, W, T, 0, nullptr, nullptr, nullptr, nullptr, 1, ck_in, one, st);
-  }
+  const TapedKernel tk = taped_kernel(c);
+  if (tk == TAPED_SPLIT)
+    return launch_split(c, b, W, T, 0, nullptr, nullptr, nullptr, nullptr, 1, ck_in, one, st);
+  if (tk == TAPED_BF16)
+    return launch_bf16_quarter(c, b, W, T, 0, nullptr, nullptr, nullptr, nullptr, 1, ck_in, one,
+                               st);
+  return launch_tile(tk == TAPED_TILE2 ? 2 : 1, c, b, W, T, 0, nullptr, nullptr, nullptr, nullptr,
+                     1, ck_in, one, st);
 }
 
 }  // namespace qs

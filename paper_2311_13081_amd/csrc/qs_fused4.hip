@@ -1,104 +1,24 @@
-// Fused multi-step kernel, quarter-lane layout: each wave advances 16 envs
-// and each env occupies 4 lanes (lane L = j + 16 k: env j of the wave,
-// quarter k).  Compared with the one-env-per-lane kernel this quadruples the
-// number of waves for a given batch (so small batches fill the chip and large
-// ones keep two waves per SIMD, whose vector instructions interleave) and
-// cuts the per-lane history from 128 to 32 registers.
+// Fused multi-step kernel of the bf16 actor option in the quarter-lane layout:
+// each wave advances 16 envs and each env occupies 4 lanes (lane L = j + 16 k:
+// env j of the wave, quarter k); the kernel of its taped rollouts.
 //
 // Observation layout across the 4 lanes of an env: register c of quarter k
 // holds feature PHI(c, k):
 //   c = 0..4:  state feature 4c + k (p, R row-major, v, w: 18 values; the two
 //              slots 4*4+2, 4*4+3 are padding);
 //   c = 5..36: action history slot c-5 (oldest first), component k.
-// This is exactly the B operand of v_mfma_f32_16x16x4f32 for 16 envs with
-// K-chunk c, so layer 1 is 37 x 4 MFMAs against W1 columns read in PHI order
-// (zeros for padding).  Layer 2 chains through the result registers as in
-// the one-env-per-lane kernel; layer 3 is one 16-block 4x4x1 MFMA per layer-2
-// result register, and two swap-and-add rounds across 32 and 16 lanes add
-// the lane groups' partial sums and leave the 4 actions of env j in all 4 of
-// its lanes.  The dynamics run replicated on the 4 lanes
-// (identical inputs, identical arithmetic, identical results); memory writes
-// are split among the lanes.
-//
-// Optional bf16 actor (config flag 16): weights are staged in LDS as bf16 and
-// the layer inputs are rounded to bf16 (round to nearest even) before
-// v_mfma_f32_16x16x32_bf16; accumulation, biases, activations and the whole
-// dynamics stay fp32.  The same quarter layout serves: one bf16 instruction
-// takes 8 consecutive chunks of the lane's quarter as its 8 K-elements.
+// Weights are staged in LDS as bf16 and the layer inputs are rounded to bf16
+// (round to nearest even) before v_mfma_f32_16x16x32_bf16, one instruction
+// taking 8 consecutive chunks of the lane's quarter; accumulation, biases,
+// activations and the whole dynamics stay fp32.  The dynamics run replicated
+// on the 4 lanes (identical inputs, identical arithmetic, identical results);
+// memory writes are split among the lanes.
 #include "qs_forward.h"
 #include "qs_quarter.h"
 
 namespace qs {
 
 typedef __bf16 bf8q __attribute__((ext_vector_type(8)));
-
-// Actor for the wave's 16 envs.  F: this lane's 37 layer-1 operands.  Returns
-// z3 (pre-tanh) of this lane's env in every lane.  When rz1/rz2 are given,
-// writes the layer pre-activations (64 rows of the blocked record; the lane
-// offset rec_lane_off addresses row 4 lg of this lane's env) and returns the
-// lane's ReLU mask word (quarter_mask) in zmask.
-__device__ inline void actor_q(const float* lds, const float F[Q_C], float z3[NA],
-                               float* __restrict__ rz1, float* __restrict__ rz2, int N,
-                               int env0, uint32_t rec_lane_off, uint32_t& zmask) {
-  const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
-  // bias tiles enter as the accumulator input of each chain's first product
-  f4q acc1[4];
-#pragma unroll
-  for (int cc = 0; cc < Q_CP / 4; ++cc) {
-    f4q w[4];
-#pragma unroll
-    for (int n = 0; n < 4; ++n)
-      w[n] = *reinterpret_cast<const f4q*>(
-          &lds[Q_W1 + (lg * NHID + 16 * n + li) * Q_W1_P + 4 * cc]);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int c = 4 * cc + q;
-      if (c < Q_C) {
-#pragma unroll
-        for (int n = 0; n < 4; ++n)
-          acc1[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-              w[n][q], F[c],
-              c == 0 ? *reinterpret_cast<const f4q*>(&lds[Q_B1 + 16 * n + 4 * lg]) : acc1[n], 0,
-              0, 0);
-      }
-    }
-  }
-  const int env = env0 + li;
-  if (rz1 && env < N) {
-#pragma unroll
-    for (int n = 0; n < 4; ++n)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) rz1[(size_t)(16 * n + r) * RB + rec_lane_off] = acc1[n][r];
-  }
-#pragma unroll
-  for (int n = 0; n < 4; ++n)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) acc1[n][r] = relu_bits(acc1[n][r]);
-  f4q acc2[4];
-#pragma unroll
-  for (int n = 0; n < 4; ++n)
-#pragma unroll
-    for (int n2 = 0; n2 < 4; ++n2) {
-      const f4q w = *reinterpret_cast<const f4q*>(&lds[Q_W2 + (16 * n2 + li) * 68 + 16 * n + 4 * lg]);
-      const f4q b2 = *reinterpret_cast<const f4q*>(&lds[Q_B2 + 16 * n2 + 4 * lg]);
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        acc2[n2] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[v], acc1[n][v],
-                                                        (n == 0 && v == 0) ? b2 : acc2[n2], 0, 0, 0);
-    }
-  if (rz2 && env < N) {
-#pragma unroll
-    for (int n2 = 0; n2 < 4; ++n2)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) rz2[(size_t)(16 * n2 + r) * RB + rec_lane_off] = acc2[n2][r];
-  }
-#pragma unroll
-  for (int n2 = 0; n2 < 4; ++n2)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) acc2[n2][r] = relu_bits(acc2[n2][r]);
-  zmask = rz1 ? quarter_mask(acc1, acc2) : 0u;
-  layer3_q(lds, acc2, z3);
-}
 
 // ---------------------------------------------------------------------------
 // bf16 actor.  LDS layout in bf16 elements:
@@ -163,8 +83,11 @@ __device__ inline bf8q relu_pack(const f4q& lo, const f4q& hi) {
   return v;
 }
 
-// Same contract as actor_q, bf16 operands (the mask from the fp32
-// accumulators).
+// Actor for the wave's 16 envs.  F: this lane's 37 layer-1 operands.  Returns
+// z3 (pre-tanh) of this lane's env in every lane.  When rz1/rz2 are given,
+// writes the layer pre-activations (64 rows of the blocked record; the lane
+// offset rec_lane_off addresses row 4 lg of this lane's env) and returns the
+// lane's ReLU mask word (quarter_mask) in zmask.
 __device__ inline void actor_qb(const float* lds, const float F[Q_C], float z3[NA],
                                 float* __restrict__ rz1, float* __restrict__ rz2, int N,
                                 int env0, uint32_t rec_lane_off, uint32_t& zmask) {
@@ -235,18 +158,15 @@ __device__ inline void actor_qb(const float* lds, const float F[Q_C], float z3[N
 // instructions at about half the rate the SIMD can execute them, two
 // interleave theirs (matrix-core and vector instructions do not overlap,
 // within a wave or across the two).
-template <bool BF16, bool EXTRAS>
+template <bool EXTRAS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_fused4(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
          float* __restrict__ rewards, uint8_t* __restrict__ dones, float* __restrict__ states,
          float* __restrict__ tape, int ckpt_every, const float* __restrict__ ck_in,
          RecSpan rs) {
-  __shared__ __attribute__((aligned(16))) float lds[BF16 ? QB_TOTAL : Q_TOTAL];
+  __shared__ __attribute__((aligned(16))) float lds[QB_TOTAL];
   const int N = c.n_envs;
-  if (BF16)
-    stage_qb(W, lds);
-  else
-    stage_q(W, lds);
+  stage_qb(W, lds);
   __syncthreads();
   const int lane = threadIdx.x & 63, j = lane & 15, k = lane >> 4;
   const int env0 = (blockIdx.x * blockDim.x + threadIdx.x - lane) / 4;  // first env of the wave
@@ -306,7 +226,7 @@ k_fused4(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
   const bool ahead = T >= 2 * RESERVE_PERIOD;
   float nx[NRES];
   bool have = ahead;
-  if (ahead) draw_ahead(c, (uint32_t)e, (uint32_t)(ep + 1), wh, nx);
+  if (ahead) draw_ahead<1>(c, (uint32_t)e, (uint32_t)(ep + 1), wh, nx);
 
   if (states && t_base == 0 && active)
 #pragma unroll
@@ -342,12 +262,8 @@ k_fused4(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     const uint32_t zoff = opaque((uint32_t)(rb_at(env0 + j, REC_F) + 4 * k * RB));
     const uint32_t koff = opaque((uint32_t)(rb_at(e, REC_F) + k * RB));
     const uint32_t roff = opaque((uint32_t)rb_at(e, REC_F));
-    if (BF16)
-      actor_qb(lds, F, z3, rec_on ? rt + (size_t)REC_Z1 * RB : nullptr,
-               rec_on ? rt + (size_t)REC_Z2 * RB : nullptr, N, env0, zoff, zmask);
-    else
-      actor_q(lds, F, z3, rec_on ? rt + (size_t)REC_Z1 * RB : nullptr,
-              rec_on ? rt + (size_t)REC_Z2 * RB : nullptr, N, env0, zoff, zmask);
+    actor_qb(lds, F, z3, rec_on ? rt + (size_t)REC_Z1 * RB : nullptr,
+             rec_on ? rt + (size_t)REC_Z2 * RB : nullptr, N, env0, zoff, zmask);
     float a[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) a[i] = tanh_act(z3[i]);
@@ -388,7 +304,7 @@ k_fused4(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
       ++ep;
       t_ep = 0;
       was_reset = true;
-      reset_from_reserve(c, (uint32_t)e, (uint32_t)ep, wh, nx, have, x);
+      reset_from_reserve<1>(c, (uint32_t)e, (uint32_t)ep, wh, nx, have, x);
       if (EXTRAS) {
         float d[6];
         disturbance(c, (uint32_t)e, (uint32_t)ep, d);
@@ -396,7 +312,7 @@ k_fused4(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
       }
     }
     if (ahead && (t & (RESERVE_PERIOD - 1)) == RESERVE_PERIOD - 1 && !have) {
-      draw_ahead(c, (uint32_t)e, (uint32_t)(ep + 1), wh, nx);
+      draw_ahead<1>(c, (uint32_t)e, (uint32_t)(ep + 1), wh, nx);
       have = true;
     }
     if (active) {
@@ -429,15 +345,13 @@ k_fused4(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
   }
 }
 
-hipError_t launch_fused4(const DevCfg& c, const SimBufs& b, const float* W, int T, int t_base,
+hipError_t launch_bf16_quarter(const DevCfg& c, const SimBufs& b, const float* W, int T, int t_base,
                          float* rewards, uint8_t* dones, float* states, float* tape,
                          int ckpt_every, const float* ck_in, const RecSpan& rs, hipStream_t st) {
   if (!rec_span_ok(rs)) return hipErrorInvalidValue;
   const unsigned grid = (unsigned)((c.n_envs + 63) / 64);
-  const bool bf = (c.flags & F_ACTOR_BF16) != 0;
   const bool ex = (c.flags & (F_DISTURB | F_OBS_NOISE)) != 0 || c.target != nullptr;
-  auto k = bf ? (ex ? k_fused4<true, true> : k_fused4<true, false>)
-              : (ex ? k_fused4<false, true> : k_fused4<false, false>);
+  auto k = ex ? k_fused4<true> : k_fused4<false>;
   hipLaunchKernelGGL(k, dim3(grid), dim3(256), 0, st, c, b, W, T, t_base, rewards, dones, states,
                      tape, ckpt_every, ck_in, rs);
   return hipGetLastError();

@@ -19,8 +19,8 @@
 //   do  = W1^T dz1                            the same over the dz1 registers,
 //        ten 16-feature tiles; register r of block bb holds feature
 //        16 p + 4 lg + r of env 16 bb + li;
-// the ReLU masks come as bits in that tile layout from the one-lane
-// forward's record (4 words per lane and step), so the sweep loads no
+// the ReLU masks come as bits from the record (one word per env and lane
+// group; a lane reads those of its four tile columns), so the sweep loads no
 // pre-activations;
 // and a 4 x 4 transpose across the lane groups (two permlane32 and two
 // permlane16 swaps per register) brings every feature of a tile to the lane
@@ -75,22 +75,22 @@ __device__ inline float keep_if(float v, uint32_t m, int b) {
 }
 
 // Inputs of one reverse step: the own env's recorded state and action and
-// cotangents, and the lane's ReLU mask words (column lane of the block).
+// cotangents, and the ReLU mask words of lane group lg for envs 16 bb + li.
 struct StepIn1 {
   float x[NS], a[NA], dS[NS], dR;
   uint32_t m[4];
 };
 
-// sr: byte offset of the step's block in the record; vown / vlane: the
-// lane's byte offsets of its env's column and of its own column.
+// sr: byte offset of the step's block in the record; vown / vmask: the lane's
+// byte offsets of its env's column and of row lg, column li.
 __device__ inline void load_step1(StepIn1& in, __amdgpu_buffer_rsrc_t rrec, uint32_t sr,
-                                  uint32_t vown, uint32_t vlane,
+                                  uint32_t vown, uint32_t vmask,
                                   const float* __restrict__ d_rewards,
                                   const float* __restrict__ d_states, int t, int N, int e) {
   const uint32_t eo = opaque((uint32_t)e);
 #pragma unroll
-  for (int w = 0; w < 4; ++w)
-    in.m[w] = __float_as_uint(bld1(rrec, vlane, sr + 4u * (REC_M + w) * RB));
+  for (int bb = 0; bb < 4; ++bb)
+    in.m[bb] = __float_as_uint(bld1(rrec, vmask, sr + 4u * (REC_M * RB + 16 * bb)));
 #pragma unroll
   for (int i = 0; i < NS; ++i) in.x[i] = bld1(rrec, vown, sr + 4u * (REC_X + i) * RB);
 #pragma unroll
@@ -129,6 +129,7 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
   const uint32_t s_rblk = 4u * blk * (REC_F * RB), s_zblk = 4u * blk * (DZ_F * RB);
   const uint32_t vown = 4u * (uint32_t)(e - env0), vlane = 4u * (uint32_t)lane;
   const uint32_t vtile = 4u * (uint32_t)(4 * lg * RB + li);
+  const uint32_t vmask = 4u * (uint32_t)(lg * RB + li);
   const __amdgpu_buffer_rsrc_t rrec = span_rsrc(rec, 4u * (uint32_t)rec_floats(n, N));
   const __amdgpu_buffer_rsrc_t rdz = span_rsrc(dz, 4u * (uint32_t)n * DZ_F * rbp);
 
@@ -165,7 +166,7 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
   for (int i = 0; i < NP; ++i) gth[i] = gth_io[(size_t)i * N + e];
 
   StepIn1 cur, nxt;
-  load_step1(cur, rrec, 4u * (uint32_t)(n - 1) * (REC_F * rbp) + s_rblk, vown, vlane, d_rewards,
+  load_step1(cur, rrec, 4u * (uint32_t)(n - 1) * (REC_F * rbp) + s_rblk, vown, vmask, d_rewards,
              d_states, t0 + n - 1, N, e);
   for (int tl = n - 1; tl >= 0; --tl) {
     __asm__ volatile("" ::: "memory");
@@ -175,7 +176,7 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
     float gx[NS], ga[NA];
     reverse_dynamics(c, B, th, renorm, cur.x, cur.a, cur.dR, ls, lR[NH - HR - 1], gx, ga, gth);
     // the next step's inputs, in flight during the input VJP below
-    load_step1(nxt, rrec, 4u * (uint32_t)tp * (REC_F * rbp) + s_rblk, vown, vlane, d_rewards,
+    load_step1(nxt, rrec, 4u * (uint32_t)tp * (REC_F * rbp) + s_rblk, vown, vmask, d_rewards,
                d_states, t0 + tp, N, e);
     // Lanes of envs >= N take dz3 = 0: the layer products keep envs apart
     // (one env per column), so their columns of dz2 and dz1 are zero too and
@@ -204,7 +205,7 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int r = 4 * bb + v;
-          d2[n2][r] = keep_if(d2[n2][r], cur.m[2 + (n2 >> 1)], 16 * (n2 & 1) + r);
+          d2[n2][r] = keep_if(d2[n2][r], cur.m[bb], 8 * n2 + 4 + v);
           bst1(d2[n2][r], rdz, vtile, sz + 4u * ((NHID + 16 * n2 + v) * RB + 16 * bb));
         }
     // dz1 = (W2^T dz2) [z1 > 0]: chains over the dz2 registers, 16 per
@@ -232,7 +233,7 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
       for (int bb = 0; bb < 4; ++bb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          d1[mt][bb][r] = keep_if(d1[mt][bb][r], cur.m[mt >> 1], 16 * (mt & 1) + 4 * bb + r);
+          d1[mt][bb][r] = keep_if(d1[mt][bb][r], cur.m[bb], 8 * mt + r);
           bst1(d1[mt][bb][r], rdz, vtile, sz + 4u * ((16 * mt + r) * RB + 16 * bb));
         }
 

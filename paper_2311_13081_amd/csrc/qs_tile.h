@@ -1,0 +1,516 @@
+// Actor on bf16 matrix cores in 16-env tiles, shared by the tile kernel, the
+// split-actor kernel and the plain step.
+//
+// Tile layout: lane L = li + 16 lg holds, for each 16-env tile b of the wave,
+// lane group lg's share of env 16 b + li: action component lg of the 32
+// history slots, and the state features 4 e + lg (e = 0..4).  That is the B
+// operand of v_mfma_f32_16x16x32_bf16 (8 elements per lane):
+//   chunk c = 0..3 of layer 1: element e is history slot 8 c + e (oldest
+//       first), component lg;
+//   chunk 4: element e < 5 is state feature 4 e + lg (p, R row-major, v, w; 0
+//       past feature 17), the rest 0;
+//   chunk m of layer 2: element e is hidden unit 32 m + 16 (e / 4) + 4 lg + e %
+//       4, the order in which the layer-1 result registers arrive (register r
+//       of result tile n: unit 16 n + 4 lg + r of env 16 b + li).
+//
+// fp32 products by splitting.  An fp32 value is the sum of three bf16 values
+// (its bf16 rounding, the rounding of what is left, and the rest: 24 bits in
+// all, exact), and a product of two such sums keeps the six terms down to
+// 2^-16 of the leading one; the three left out are below 2^-25.  The six
+// products run at 16 times the rate of the fp32 shapes, 2.7 times per fp32
+// product, and overlap with vector instructions, which the fp32 shapes do
+// not.  Against 64 bits the result is closer than the fp32 chain's, because
+// each instruction rounds its 32 products once: relative rms error at K =
+// 160 1.7e-7 against 2.3e-7, at K = 64 9e-8 against 1.4e-7.
+// The order of the terms is the same in every kernel, so they agree bit for
+// bit.
+#pragma once
+#include "qs_device.h"
+
+namespace qs {
+
+typedef float f4t __attribute__((ext_vector_type(4)));
+typedef uint32_t u4t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf8t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2t __attribute__((ext_vector_type(2)));
+typedef float f2t __attribute__((ext_vector_type(2)));
+
+constexpr int T_P = 3;  // bf16 parts of a value
+
+// LDS: operand fragments of 64 lanes x 16 bytes ([group][part][lane], so a
+// read is one conflict-free b128 per lane), then the fp32 biases and layer 3.
+// Groups: layer 1 chunk c, unit tile n at 4 c + n; layer 2 chunk m at 20 + 4 m + n.
+constexpr int T_C1 = 5, T_C2 = 2, T_G1 = 4 * T_C1, T_G = T_G1 + 4 * T_C2;
+constexpr int T_W3_LD = 68;  // layer-3 row pitch: the 16-byte reads stay aligned
+constexpr int T_B1 = T_G * T_P * 256, T_B2 = T_B1 + NHID, T_W3 = T_B2 + NHID,
+              T_B3 = T_W3 + NA * T_W3_LD, T_TOTAL = T_B3 + 4;  // floats
+
+// Source index (into the flat actor) of element e of lane l in group g, -1
+// for padding.
+__device__ inline int tile_src(int g, int l, int e) {
+  const int li = l & 15, lg = l >> 4;
+  if (g < T_G1) {
+    const int c = g >> 2, row = OFF_W1 + (16 * (g & 3) + li) * NO;
+    if (c < 4) return row + 18 + NA * (8 * c + e) + lg;
+    return 4 * e + lg < 18 ? row + 4 * e + lg : -1;
+  }
+  const int m = (g - T_G1) >> 2, n = (g - T_G1) & 3;
+  return OFF_W2 + (16 * n + li) * NHID + 32 * m + 16 * (e >> 2) + 4 * lg + (e & 3);
+}
+
+// Two fp32 values to packed bf16 (round to nearest even), first one low.
+__device__ inline uint32_t pack_bf16(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2t{a, b}, bf2t));
+}
+__device__ inline float bf_lo(uint32_t p) { return __uint_as_float(p << 16); }
+__device__ inline float bf_hi(uint32_t p) { return __uint_as_float(p & 0xffff0000u); }
+
+// The parts of a pair of values, packed: p[0] + p[1] + p[2] is the value.
+__device__ inline void split_pair(float a, float b, uint32_t p[T_P]) {
+  p[0] = pack_bf16(a, b);
+  a -= bf_lo(p[0]);
+  b -= bf_hi(p[0]);
+  p[1] = pack_bf16(a, b);
+  p[2] = pack_bf16(a - bf_lo(p[1]), b - bf_hi(p[1]));
+}
+
+// Stages groups [g0, g1) of the actor's fragments at dst (u4t), every thread
+// of the workgroup taking (group, lane) pairs, the loads of up to eight pairs
+// in flight at a time.
+template <int MAXT>
+__device__ inline void stage_fragments(const float* __restrict__ W, u4t* dst, int g0, int g1) {
+  const int nt = blockDim.x, n = (g1 - g0) * 64;
+  for (int base = threadIdx.x; base < n; base += MAXT * nt) {
+    float v[MAXT][8];
+#pragma unroll
+    for (int j = 0; j < MAXT; ++j) {
+      const int t = min(base + j * nt, n - 1);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int s = tile_src(g0 + (t >> 6), t & 63, e);
+        v[j][e] = W[s < 0 ? 0 : s];
+        if (s < 0) v[j][e] = 0.0f;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < MAXT; ++j) {
+      const int t = base + j * nt;
+      if (t >= n) break;
+      u4t o[T_P];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        uint32_t p[T_P];
+        split_pair(v[j][2 * q], v[j][2 * q + 1], p);
+#pragma unroll
+        for (int s = 0; s < T_P; ++s) o[s][q] = p[s];
+      }
+#pragma unroll
+      for (int s = 0; s < T_P; ++s) dst[((t >> 6) * T_P + s) * 64 + (t & 63)] = o[s];
+    }
+  }
+}
+
+// The whole actor into LDS.
+__device__ inline void stage_tile(const float* __restrict__ W, float* lds) {
+  stage_fragments<4>(W, reinterpret_cast<u4t*>(lds), 0, T_G);
+  for (int i = threadIdx.x; i < NA * T_W3_LD + 2 * NHID + NA; i += blockDim.x) {
+    if (i < 2 * NHID) {
+      lds[T_B1 + i] = W[i < NHID ? OFF_B1 + i : OFF_B2 + i - NHID];
+    } else if (i < 2 * NHID + NA * T_W3_LD) {
+      const int r = (i - 2 * NHID) / T_W3_LD, k = (i - 2 * NHID) % T_W3_LD;
+      lds[T_W3 + i - 2 * NHID] = k < NHID ? W[OFF_W3 + r * NHID + k] : 0.0f;
+    } else {
+      const int o = i - 2 * NHID - NA * T_W3_LD;
+      lds[T_B3 + o] = W[OFF_B3 + o];
+    }
+  }
+}
+
+__device__ inline f4t mfma_bf(u4t a, u4t b, f4t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8t, a),
+                                                 __builtin_bit_cast(bf8t, b), c, 0, 0, 0);
+}
+
+// The weight fragments of a step are read in the order of their groups, one
+// read ahead: while the products of NN unit tiles run, the next NN tiles'
+// fragments (12 registers each) are on their way from LDS.
+template <int NN>
+struct Frags {
+  u4t a[NN][T_P];
+  __device__ inline void load(const u4t* w, int g, int lane) {
+#pragma unroll
+    for (int j = 0; j < NN; ++j)
+#pragma unroll
+      for (int s = 0; s < T_P; ++s) a[j][s] = w[((g + j) * T_P + s) * 64 + lane];
+  }
+};
+
+// acc[j][b] += fragment j x operand x[b] for NN unit tiles and TILES env
+// tiles: the six terms from the smallest to the largest.
+template <int NN, int TILES>
+__device__ inline void tile_products(const Frags<NN>& f, const u4t (&x)[TILES][T_P],
+                                     f4t (&acc)[NN][TILES]) {
+  constexpr int WP[6] = {2, 0, 1, 1, 0, 0}, XP[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+  for (int k = 0; k < 6; ++k)
+#pragma unroll
+    for (int j = 0; j < NN; ++j)
+#pragma unroll
+      for (int b = 0; b < TILES; ++b) acc[j][b] = mfma_bf(f.a[j][WP[k]], x[b][XP[k]], acc[j][b]);
+}
+
+// Unit tiles taken together: enough independent sums (NN x TILES >= 2) for the
+// matrix pipe.
+template <int TILES>
+constexpr int T_NN = TILES == 1 ? 2 : 1;
+
+// The four unit tiles of the chunk whose fragments start at group g (28 of
+// them, in the order of a step, then the next step's first).  next: the
+// fragments read ahead.
+template <int TILES>
+__device__ inline void unit_products(const u4t* w, int g, int lane, const u4t (&x)[TILES][T_P],
+                                     f4t (&acc)[4][TILES], Frags<T_NN<TILES>>& next) {
+  constexpr int NN = T_NN<TILES>;
+#pragma unroll
+  for (int n = 0; n < 4; n += NN) {
+    const Frags<NN> cur = next;
+    next.load(w, g + n + NN < T_G ? g + n + NN : 0, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    tile_products<NN, TILES>(cur, x, reinterpret_cast<f4t(&)[NN][TILES]>(acc[n]));
+  }
+}
+
+// Operand of layer-2 chunk m from two layer-1 result tiles (ReLU applied).
+__device__ inline void hidden_operand(const f4t& lo, const f4t& hi, u4t (&x)[T_P]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint32_t p[T_P];
+    const float a = q < 2 ? lo[2 * q] : hi[2 * q - 4], b = q < 2 ? lo[2 * q + 1] : hi[2 * q - 3];
+    split_pair(a, b, p);
+#pragma unroll
+    for (int s = 0; s < T_P; ++s) x[s][q] = p[s];
+  }
+}
+
+// State operand (chunk 4) of one tile from its five features.
+__device__ inline void state_operand(const float F[5], u4t (&x)[T_P]) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    uint32_t p[T_P];
+    split_pair(F[2 * q], q < 2 ? F[2 * q + 1] : 0.0f, p);
+#pragma unroll
+    for (int s = 0; s < T_P; ++s) x[s][q] = p[s];
+  }
+#pragma unroll
+  for (int s = 0; s < T_P; ++s) x[s][3] = 0u;
+}
+
+// Per-lane values V[k] of the lane's own env (k = lane group) to out[b] = V[lg]
+// of env 16 b + li.  One tile: every lane group holds the same env, a
+// select.  Two tiles: own env = tile lg & 1; rows 0 and 2 hold tile 0, rows 1
+// and 3 tile 1, so lane groups 0, 1 offer V[0], V[1] and groups 2, 3 offer V[2],
+// V[3], and one swap of odd with even rows sorts them by tile.
+template <int TILES>
+__device__ inline void to_tiles(const float V[4], int lg, float out[TILES]) {
+  static_assert(TILES == 1 || TILES == 2, "tiles per wave");
+  if constexpr (TILES == 1) {
+    const float lo = pick(lg & 1, V[1], V[0]), hi = pick(lg & 1, V[3], V[2]);
+    out[0] = pick(lg & 2, hi, lo);
+  } else {
+    const float X = pick(lg < 2, V[0], V[2]), Y = pick(lg < 2, V[1], V[3]);
+    const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(X), __float_as_uint(Y), false,
+                                                    false);
+    out[0] = __uint_as_float(q[0]);
+    out[1] = __uint_as_float(q[1]);
+  }
+}
+
+// The uniforms of the observation noise that a lane needs: those of half h of
+// each of the step's five blocks (h = 0 feeds features 4 q, 4 q + 1, h = 1 the
+// next two), h = lg / 2 for one tile and for two.  The lanes of an env draw
+// different blocks (block 4 all of them) and swap: one tile, lane group q
+// draws block q; two tiles, groups 0, 1 draw blocks 0 and 1, groups 2, 3 blocks
+// 2 and 3 of the same env.
+template <int TILES>
+__device__ inline void noise_uniforms(const DevCfg& c, uint32_t e, uint32_t ep, int t_ep, int lg,
+                                      float u0[5], float u1[5]) {
+  const uint32_t base = (uint32_t)t_ep * 5u;
+  float u[4];
+  uniforms4(c.seed_lo, c.seed_hi, e, ep, base + 4u, STREAM_NOISE, u);
+  u0[4] = pick(lg < 2, u[0], u[2]);
+  u1[4] = pick(lg < 2, u[1], u[3]);
+#pragma unroll
+  for (int k = 0; k < TILES; ++k) {
+    uniforms4(c.seed_lo, c.seed_hi, e, ep,
+              base + (uint32_t)(TILES == 1 ? lg : 2 * (lg >> 1) + k), STREAM_NOISE, u);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      // halves 0 of rows 0, 1 | halves 1 of rows 0, 1, and the same of rows 2, 3
+      const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(u[i]),
+                                                      __float_as_uint(u[2 + i]), false, false);
+      float* o = i ? u1 : u0;
+      if constexpr (TILES == 1) {
+        const auto a = __builtin_amdgcn_permlane16_swap(s[0], s[0], false, false);
+        const auto b = __builtin_amdgcn_permlane16_swap(s[1], s[1], false, false);
+        o[0] = __uint_as_float(a[0]);
+        o[1] = __uint_as_float(a[1]);
+        o[2] = __uint_as_float(b[0]);
+        o[3] = __uint_as_float(b[1]);
+      } else {
+        o[k] = __uint_as_float(s[0]);
+        o[2 + k] = __uint_as_float(s[1]);
+      }
+    }
+  }
+}
+
+// The observed state features 4 q + lg (p, R row-major, v, w; 0 past the end)
+// of each tile's env, with the set-point shift and the noise under EXTRAS.
+// The noise costs more than the rest of the step's vector work, so a lane
+// evaluates only the normals of the features it hands out: one of a pair for
+// one tile, a pair for two.
+template <int TILES, bool EXTRAS>
+__device__ inline void tile_features(const DevCfg& c, const SetPoint& sp, uint32_t e, uint32_t ep,
+                                     int t_ep, const float x[NS], int lg, float (&F)[TILES][5]) {
+  float f[20];
+  rotmat(x + 3, f + 3);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    f[i] = x[i];
+    f[12 + i] = x[7 + i];
+    f[15 + i] = x[10 + i];
+  }
+  f[18] = f[19] = 0.0f;
+  if (EXTRAS) {
+    sp.apply(c, f);
+    if (c.flags & F_OBS_NOISE) {
+      float u0[5], u1[5];
+      noise_uniforms<TILES>(c, e, ep, t_ep, lg, u0, u1);
+#pragma unroll
+      for (int q = 0; q < 5; ++q) {
+        float zc, zs;
+        box_muller(u0[q], u1[q], zc, zs);
+        // the pair 4 q + 2 h, 4 q + 2 h + 1 of this lane's half h
+        const bool lo = lg < 2;
+        f[4 * q] = fmaf(pick(lo, noise_std(c, 4 * q), 0.0f), zc, f[4 * q]);
+        f[4 * q + 1] = fmaf(pick(lo, noise_std(c, 4 * q + 1), 0.0f), zs, f[4 * q + 1]);
+        f[4 * q + 2] = fmaf(pick(lo, 0.0f, noise_std(c, 4 * q + 2)), zc, f[4 * q + 2]);
+        f[4 * q + 3] = fmaf(pick(lo, 0.0f, noise_std(c, 4 * q + 3)), zs, f[4 * q + 3]);
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 5; ++q) {
+    float o[TILES];
+    to_tiles<TILES>(f + 4 * q, lg, o);
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) F[t][q] = o[t];
+  }
+}
+
+// Layer 3 (fp32 16-block 4x4x1, one product per layer-2 result register: block
+// b takes that register's unit for its lane group and 4 envs as B, the
+// unit's 4 output weights as A, row o = lane & 3) from the layer-2 results h2
+// (ReLU applied): z3 of the lane's own env in every lane.  Each lane group
+// ends with the partial sum over its units; swapping 32 lanes and adding,
+// then 16 lanes and adding, completes them ((0 + 2) + (1 + 3)).
+template <int TILES>
+__device__ inline void tile_layer3(const float* w3, const float* b3p, const f4t (&h2)[4][TILES],
+                                   float z3[NA]) {
+  const int lane = threadIdx.x & 63, lg = lane >> 4;
+  f4t b3;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) b3[r] = lg == 0 ? b3p[r] : 0.0f;
+  f4t acc[TILES];
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    const f4t w = *reinterpret_cast<const f4t*>(&w3[(lane & 3) * T_W3_LD + 16 * n + 4 * lg]);
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int b = 0; b < TILES; ++b)
+        acc[b] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[v], h2[n][b][v],
+                                                    (n == 0 && v == 0) ? b3 : acc[b], 0, 0, 0);
+  }
+#pragma unroll
+  for (int o = 0; o < NA; ++o) {
+    uint32_t s[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const uint32_t v = __float_as_uint(acc[b % TILES][o]);
+      const auto p = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+      s[b] = __float_as_uint(__uint_as_float(p[0]) + __uint_as_float(p[1]));
+    }
+    const auto q = __builtin_amdgcn_permlane16_swap(s[0], s[1], false, false);
+    z3[o] = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+  }
+}
+
+template <int NN, int TILES>
+__device__ inline void relu_tiles(f4t (&a)[NN][TILES]) {
+#pragma unroll
+  for (int n = 0; n < NN; ++n)
+#pragma unroll
+    for (int b = 0; b < TILES; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) a[n][b][r] = relu_bits(a[n][b][r]);
+}
+
+// Action history of a wave's tiles: component lg of slots 2 q, 2 q + 1 packed in
+// word q (of 16), one word array per part.
+template <int TILES>
+struct TileHist {
+  u4t h[TILES][T_P][4];
+
+  // slots (2 q, 2 q + 1) of tile b
+  __device__ inline void set_pair(int b, int q, float s0, float s1) {
+    uint32_t p[T_P];
+    split_pair(s0, s1, p);
+#pragma unroll
+    for (int s = 0; s < T_P; ++s) h[b][s][q >> 2][q & 3] = p[s];
+  }
+  // One slot older: every slot moves down by one, p[b] (the parts of a value
+  // in the low halves) becomes slot 31.  Words of chunk c only; chunks in
+  // ascending order.
+  __device__ inline void push_chunk(int c, const uint32_t (&p)[TILES][T_P]) {
+#pragma unroll
+    for (int b = 0; b < TILES; ++b)
+#pragma unroll
+      for (int s = 0; s < T_P; ++s) {
+        u4t v = h[b][s][c];
+        const uint32_t next = c < 3 ? (uint32_t)h[b][s][c < 3 ? c + 1 : 3][0] : p[b][s];
+        v[0] = __builtin_amdgcn_alignbit(v[1], v[0], 16);
+        v[1] = __builtin_amdgcn_alignbit(v[2], v[1], 16);
+        v[2] = __builtin_amdgcn_alignbit(v[3], v[2], 16);
+        v[3] = __builtin_amdgcn_alignbit(next, v[3], 16);
+        h[b][s][c] = v;
+      }
+  }
+  // where on[b]: every slot of the lane's env in tile b becomes v[b]
+  __device__ inline void fill(const bool on[TILES], const float v[TILES]) {
+#pragma unroll
+    for (int b = 0; b < TILES; ++b) {
+      uint32_t p[T_P];
+      split_pair(v[b], v[b], p);
+#pragma unroll
+      for (int s = 0; s < T_P; ++s)
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+          h[b][s][q >> 2][q & 3] = on[b] ? p[s] : h[b][s][q >> 2][q & 3];
+    }
+  }
+  // the value of slot sl (the sum of its parts, exact)
+  __device__ inline float get(int b, int sl) const {
+    const int q = sl >> 1;
+    float p[3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      const uint32_t w = h[b][s][q >> 2][q & 3];
+      p[s] = sl & 1 ? bf_hi(w) : bf_lo(w);
+    }
+    return p[0] + (p[1] + p[2]);
+  }
+};
+
+// Layer 1's bias and history products.  They need the actions only, so a step's
+// share is evaluated while the step before integrates its dynamics: the
+// matrix products and the vector instructions of one wave overlap.
+template <int TILES>
+__device__ inline void tile_bias1(const float* lds, f4t (&a1)[4][TILES]) {
+  const int lg = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    const f4t b1 = *reinterpret_cast<const f4t*>(&lds[T_B1 + 16 * n + 4 * lg]);
+#pragma unroll
+    for (int b = 0; b < TILES; ++b) a1[n][b] = b1;
+  }
+}
+template <int TILES>
+__device__ inline void tile_history_chunk(const float* lds, const TileHist<TILES>& H, int c,
+                                          f4t (&a1)[4][TILES], Frags<T_NN<TILES>>& next) {
+  u4t x[TILES][T_P];
+#pragma unroll
+  for (int b = 0; b < TILES; ++b)
+#pragma unroll
+    for (int s = 0; s < T_P; ++s) x[b][s] = H.h[b][s][c];
+  unit_products<TILES>(reinterpret_cast<const u4t*>(lds), 4 * c, threadIdx.x & 63, x, a1, next);
+}
+template <int TILES>
+__device__ inline void tile_history(const float* lds, const TileHist<TILES>& H,
+                                    f4t (&a1)[4][TILES], Frags<T_NN<TILES>>& next) {
+  tile_bias1<TILES>(lds, a1);
+  next.load(reinterpret_cast<const u4t*>(lds), 0, threadIdx.x & 63);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    tile_history_chunk<TILES>(lds, H, c, a1, next);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// The rest of the actor for the wave's tiles: z3 (pre-tanh) of the lane's own
+// env in every lane.  a1: layer 1's bias and history products (consumed); F:
+// the state features 4 e + lg of each tile's env.  rec takes the layer results
+// before the ReLU and the ReLU masks (the record of taped rollouts).
+template <int TILES, typename Rec>
+__device__ inline void tile_actor(const float* lds, f4t (&a1)[4][TILES],
+                                  const float (&F)[TILES][5], float z3[NA], Rec&& rec,
+                                  Frags<T_NN<TILES>>& next) {
+  const int lane = threadIdx.x & 63, lg = lane >> 4;
+  const u4t* w = reinterpret_cast<const u4t*>(lds);
+  {
+    u4t x[TILES][T_P];
+#pragma unroll
+    for (int b = 0; b < TILES; ++b) state_operand(F[b], x[b]);
+    unit_products<TILES>(w, 16, lane, x, a1, next);
+  }
+  f4t a2[4][TILES];
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    const f4t b2 = *reinterpret_cast<const f4t*>(&lds[T_B2 + 16 * n + 4 * lg]);
+#pragma unroll
+    for (int b = 0; b < TILES; ++b) a2[n][b] = b2;
+  }
+  rec.layer1(a1);
+  relu_tiles(a1);
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    u4t x[TILES][T_P];
+#pragma unroll
+    for (int b = 0; b < TILES; ++b) hidden_operand(a1[2 * m][b], a1[2 * m + 1][b], x[b]);
+    unit_products<TILES>(w, T_G1 + 4 * m, lane, x, a2, next);
+  }
+  rec.layer2(a2);
+  relu_tiles(a2);
+  rec.masks(a1, a2);
+  tile_layer3<TILES>(lds + T_W3, lds + T_B3, a2, z3);
+}
+
+// No record.
+struct NoRec {
+  template <typename A>
+  __device__ inline void layer1(const A&) {}
+  template <typename A>
+  __device__ inline void layer2(const A&) {}
+  template <typename A>
+  __device__ inline void masks(const A&, const A&) {}
+};
+
+// ReLU mask word of a record (row REC_M + lg of the env's column, lg the
+// lane group): bit 8 n + r is set when layer-1 unit 16 n + 4 lg + r of the
+// env has a positive pre-activation, bit 8 n + 4 + r the same for layer 2.
+// z1, z2: the lane's result tiles of one env tile, before or after the ReLU (z
+// > 0 and relu(z) > 0 agree, NaN included).
+template <int TILES>
+__device__ inline uint32_t tile_mask(const f4t (&z1)[4][TILES], const f4t (&z2)[4][TILES], int b) {
+  uint32_t m = 0u;
+#pragma unroll
+  for (int n = 0; n < 4; ++n)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      m |= (z1[n][b][r] > 0.0f ? 1u : 0u) << (8 * n + r);
+      m |= (z2[n][b][r] > 0.0f ? 1u : 0u) << (8 * n + 4 + r);
+    }
+  return m;
+}
+
+}  // namespace qs

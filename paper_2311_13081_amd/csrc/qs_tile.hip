@@ -1,0 +1,351 @@
+// Fused multi-step kernel with the actor on bf16 matrix cores (fp32 products
+// by splitting, qs_tile.h): each wave advances 16 or 32 envs (one or two
+// 16-env tiles) for T steps of observation, actor, action map, RK4, reward,
+// history push, termination and reset in one launch, state and history in
+// registers.
+//
+// The dynamics of an env run replicated on its 4 / TILES lanes (identical
+// inputs and arithmetic, identical results); memory writes are split among
+// them.
+// Fused multiply-adds only where one expression of the source holds the
+// product and the sum: the kernels that promise equal results then round the
+// shared arithmetic the same way (left to the optimiser, fusing depends on what
+// surrounds the inlined code).
+#pragma clang fp contract(on)
+#include "qs_forward.h"
+#include "qs_tile.h"
+
+namespace qs {
+
+// Layer results and masks of a recorded step (the backward's record): rows of
+// the wave's tiles at base + 64 row + zoff[b], zoff[b] the lane's offset of
+// row 4 lg of its env in tile b; nothing for envs past the batch.
+template <int TILES>
+struct StepRec {
+  float* base;  // NULL: the step is not recorded
+  uint32_t zoff[TILES];
+  bool on[TILES];
+  uint32_t mask[TILES];
+  template <int ROW>
+  __device__ inline void rows(const f4t (&z)[4][TILES]) {
+#pragma unroll
+    for (int b = 0; b < TILES; ++b)
+      if (on[b])
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            base[(size_t)(ROW + 16 * n + r) * RB + zoff[b]] = z[n][b][r];
+  }
+  __device__ inline void layer1(const f4t (&z)[4][TILES]) {
+    if (base) rows<REC_Z1>(z);
+  }
+  __device__ inline void layer2(const f4t (&z)[4][TILES]) {
+    if (base) rows<REC_Z2>(z);
+  }
+  __device__ inline void masks(const f4t (&h1)[4][TILES], const f4t (&h2)[4][TILES]) {
+    if (base)
+#pragma unroll
+      for (int b = 0; b < TILES; ++b) mask[b] = tile_mask<TILES>(h1, h2, b);
+  }
+};
+
+constexpr int T_MAX_THREADS = 512;
+
+// T steps; outputs indexed by t_base + t.  Lanes of envs past the batch
+// shadow the wave's first env (loads only) so every operand is finite.
+// EXTRAS: the training extras or a set point are on.  TAPE: the modes of
+// differentiable rollouts: with tape != NULL a CK_F-row checkpoint every
+// ckpt_every steps; with ck_in != NULL the launch starts from that checkpoint
+// and leaves the env state alone (the backward's recompute); with rs.buf[0] !=
+// NULL it writes the backward's record of the span rs.
+//
+// Two waves per SIMD (256 registers each): the matrix products of one wave
+// overlap the vector instructions of the other.
+template <int TILES, bool EXTRAS, bool TAPE>
+__global__ void __launch_bounds__(T_MAX_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
+       float* __restrict__ rewards, uint8_t* __restrict__ dones, float* __restrict__ states,
+       float* __restrict__ tape, int ckpt_every, const float* __restrict__ ck_in, RecSpan rs) {
+  constexpr int SUB = 4 / TILES;  // lanes per env
+  __shared__ __attribute__((aligned(16))) float lds[T_TOTAL + NRES * T_MAX_THREADS];
+  const int N = c.n_envs;
+  stage_tile(W, lds);
+  __syncthreads();
+  const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+  const int wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const int env0 = __builtin_amdgcn_readfirstlane(wave * 16 * TILES);
+  if (env0 >= N) return;
+  // own env (dynamics): tile lg % TILES, this lane the sub-th of its SUB
+  const int sub = lg / TILES;
+  const int env = env0 + 16 * (lg % TILES) + li;
+  const bool active = env < N;
+  const int e = active ? env : env0;
+  int et[TILES];  // the lane's env in each tile
+#pragma unroll
+  for (int t = 0; t < TILES; ++t) et[t] = env0 + 16 * t + li < N ? env0 + 16 * t + li : env0;
+  const bool REC = TAPE && ck_in != nullptr;
+
+  float th[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) th[i] = b.theta[(size_t)i * N + e];
+  Body<float> B = make_body<float>(th);
+  const bool renorm = (c.flags & F_RENORM_Q) != 0;
+
+  float x[NS];
+  TileHist<TILES> H;
+  int head0 = 0, t_ep = 0, ep = 0;
+  EpAcc acc;
+  if (REC) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) x[i] = ck_in[(size_t)i * N + e];
+#pragma unroll
+    for (int t = 0; t < TILES; ++t)
+#pragma unroll
+      for (int q = 0; q < 16; ++q)
+        H.set_pair(t, q, ck_in[(size_t)(NS + 2 * q * NA + lg) * N + et[t]],
+                   ck_in[(size_t)(NS + (2 * q + 1) * NA + lg) * N + et[t]]);
+    t_ep = __float_as_int(ck_in[(size_t)CK_TEP * N + e]);
+    ep = __float_as_int(ck_in[(size_t)CK_EP * N + e]);
+    acc.cur = acc.last = 0.0f, acc.len = 0;
+  } else {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) x[i] = b.state[(size_t)i * N + e];
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) {
+      const int hd = b.head[et[t]];
+      float v[NH];
+#pragma unroll
+      for (int s = 0; s < NH; ++s)
+        v[s] = b.ring[(size_t)(((hd + s) & (NH - 1)) * NA + lg) * N + et[t]];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) H.set_pair(t, q, v[2 * q], v[2 * q + 1]);
+    }
+    head0 = b.head[e];
+    t_ep = b.t_ep[e];
+    ep = b.ep[e];
+    acc.load(b, N, e);
+  }
+  SetPoint sp;
+  if (EXTRAS) sp.load(c, N, e);
+  bool was_reset = false;
+  const float wh = hover_rpm(c, th[0], th[4], th[5], th[6]);
+  const float ah = rpm_to_action(c, wh);
+  float aht[TILES];
+  {
+    const float v[4] = {ah, ah, ah, ah};
+    to_tiles<TILES>(v, lg, aht);
+  }
+  if (EXTRAS) {
+    float d[6];
+    disturbance(c, (uint32_t)e, (uint32_t)ep, d);
+    set_disturbance(B, d);
+  }
+  // next episode's start state drawn ahead (long launches only)
+  const bool ahead = T >= 2 * RESERVE_PERIOD && (c.flags & F_AUTORESET) != 0;
+  // (kept in LDS, one column per lane: it is touched at resets only)
+  float* nxp = lds + T_TOTAL + threadIdx.x;
+  const auto draw_next = [&]() {
+    float nx[NRES];
+    draw_ahead<0>(c, (uint32_t)e, (uint32_t)(ep + 1), wh, nx);
+#pragma unroll
+    for (int i = 0; i < NRES; ++i) nxp[i * T_MAX_THREADS] = nx[i];
+  };
+  bool have = ahead;
+  if (ahead) draw_next();
+
+  const uint32_t osub = 4u * (uint32_t)(sub * N + e);  // row sub of the env
+  if (states && t_base == 0 && active) store_rows<SUB, NS>(states, N, osub, sub, x);
+
+  f4t a1[4][TILES];  // layer 1 of the coming step: bias and history products
+  Frags<T_NN<TILES>> next;
+  tile_history<TILES>(lds, H, a1, next);
+  for (int t = 0; t < T; ++t) {
+    // keeps the weight reads inside the step (hoisted out of the time loop
+    // they would pin the registers)
+    __asm__ volatile("" ::: "memory");
+    const uint32_t so = opaque(osub);
+    const int gt = t_base + t;
+    RecAt ra;
+    const bool rec_on = TAPE && rec_at(rs, gt, ra);  // wave uniform
+    if (TAPE && tape && (gt % ckpt_every) == 0) {
+      float* ck = tape + (size_t)(gt / ckpt_every) * CK_F * N;
+      if (active) {
+        store_rows<SUB, NS>(ck, N, so, sub, x);
+        if (sub == 0) {
+          at_byte(ck + (size_t)CK_TEP * N, so) = __int_as_float(t_ep);
+          at_byte(ck + (size_t)CK_EP * N, so) = __int_as_float(ep);
+        }
+      }
+#pragma unroll
+      for (int tl = 0; tl < TILES; ++tl) {
+        const uint32_t kc = opaque(4u * (uint32_t)(lg * N + et[tl]));
+        if (env0 + 16 * tl + li < N)
+#pragma unroll
+          for (int s = 0; s < NH; ++s) at_byte(ck + (size_t)(NS + s * NA) * N, kc) = H.get(tl, s);
+      }
+    }
+    float F[TILES][5];
+    tile_features<TILES, EXTRAS>(c, sp, (uint32_t)e, (uint32_t)ep, t_ep, x, lg, F);
+    // the wave in its actor goes first: its products are the serial part, the
+    // other wave's vector instructions fill in
+    __builtin_amdgcn_s_setprio(1);
+    float z3[NA];
+    float* rt = nullptr;  // the step's record
+    StepRec<TILES> sr;
+    if constexpr (TAPE) {
+      rt = rec_on ? ra.base + rec_step(ra.step, N) : nullptr;
+      sr.base = rt;
+#pragma unroll
+      for (int tl = 0; tl < TILES; ++tl) {
+        sr.on[tl] = env0 + 16 * tl + li < N;
+        sr.zoff[tl] = opaque((uint32_t)(rb_at(env0 + 16 * tl + li, REC_F) + 4 * lg * RB));
+        sr.mask[tl] = 0u;
+      }
+      tile_actor<TILES>(lds, a1, F, z3, sr, next);
+    } else {
+      tile_actor<TILES>(lds, a1, F, z3, NoRec{}, next);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    float a[NA], at[TILES];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) a[i] = tanh_act(z3[i]);
+    to_tiles<TILES>(a, lg, at);
+    if (TAPE && rec_on) {
+      const uint32_t koff = opaque((uint32_t)lg * RB);
+      float* act = ra.base + rec_act(ra.n, N);
+#pragma unroll
+      for (int tl = 0; tl < TILES; ++tl) {
+        if (!sr.on[tl]) continue;
+        // the state features, masks and actions; the history features are
+        // earlier actions, kept on the segment's action tape (the
+        // checkpoint's history first, then a_t)
+        const uint32_t ko = koff + (uint32_t)rb_at(env0 + 16 * tl + li, REC_F);
+        const uint32_t ao = koff + (uint32_t)rb_at(env0 + 16 * tl + li, (NH + ra.n) * NA);
+#pragma unroll
+        for (int q = 0; q < 5; ++q)
+          if (4 * q + lg < 18) rt[(size_t)(REC_O + 4 * q) * RB + ko] = F[tl][q];
+        rt[(size_t)REC_A * RB + ko] = at[tl];
+        rt[(size_t)REC_M * RB + ko] = __uint_as_float(sr.mask[tl]);
+        if (ra.step == 0) {
+#pragma unroll
+          for (int s = 0; s < NH; ++s) act[(size_t)(s * NA) * RB + ao] = H.get(tl, s);
+        }
+        act[(size_t)((NH + ra.step) * NA) * RB + ao] = at[tl];
+      }
+      if (active)
+        store_rows<SUB, NS>(rt + REC_X * RB, RB,
+                            opaque(4u * (uint32_t)(rb_at(e, REC_F) + sub * RB)), sub, x);
+    }
+    // the action goes to the history ring in memory as it is applied (the
+    // last 32 of a launch; the older ones would be overwritten)
+    if (!REC && t >= T - NH && active)
+      store_ring<SUB>(b.ring, N, (head0 + t) & (NH - 1), so, sub, a);
+    uint32_t ap[TILES][T_P];
+#pragma unroll
+    for (int tl = 0; tl < TILES; ++tl) split_pair(at[tl], 0.0f, ap[tl]);
+    tile_bias1<TILES>(lds, a1);
+    float u[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) u[i] = action_to_rpm(c, a[i]);
+    // ahead of each right-hand side a quarter of the history products of the
+    // next step
+    rk4_step<float, EXTRAS>(B, c.arm, c.km, c.g, c.dt, renorm, x, u, [&](int k) {
+      __builtin_amdgcn_sched_barrier(0);
+      H.push_chunk(k, ap);
+      tile_history_chunk<TILES>(lds, H, k, a1, next);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    const float r = reward(c, x, a);
+    ++t_ep;
+    const uint32_t d = episode_end(c, x, t_ep);
+    const bool rst = d && (c.flags & F_AUTORESET);
+    acc.add(r, rst, t_ep);
+    const uint64_t any = __ballot(rst);
+    if (any) {  // wave uniform
+      bool on[TILES];
+#pragma unroll
+      for (int tl = 0; tl < TILES; ++tl) on[tl] = (any >> (16 * tl + li)) & 1u;
+      H.fill(on, aht);
+      tile_history<TILES>(lds, H, a1, next);
+      if (rst) {
+        ++ep;
+        t_ep = 0;
+        was_reset = true;
+        if (have) {
+#pragma unroll
+          for (int i = 0; i < NRES; ++i) x[i] = nxp[i * T_MAX_THREADS];
+#pragma unroll
+          for (int i = NRES; i < NS; ++i) x[i] = wh;
+          have = false;
+        } else {
+          reset_draw<0>(c, (uint32_t)e, (uint32_t)ep, wh, x);
+        }
+        if (EXTRAS) {
+          float dd[6];
+          disturbance(c, (uint32_t)e, (uint32_t)ep, dd);
+          set_disturbance(B, dd);
+        }
+      }
+    }
+    if (ahead && (t & (RESERVE_PERIOD - 1)) == RESERVE_PERIOD - 1 && !have) {
+      draw_next();
+      have = true;
+    }
+    if (active) {
+      if (sub == 0) {
+        if (rewards) at_byte(rewards + (size_t)gt * N, so) = r;
+        if (dones) at_byte(dones + (size_t)gt * N, so >> 2) = (uint8_t)d;
+      }
+      if (states) store_rows<SUB, NS>(states + (size_t)(gt + 1) * NS * N, N, so, sub, x);
+    }
+  }
+  if (!active || REC) return;
+  const uint32_t ef = opaque((uint32_t)e);
+  store_rows<SUB, NS>(b.state, N, osub, sub, x);
+  const int head1 = (head0 + T) & (NH - 1);
+  // after a reset in this launch the slots older than the episode's t_ep
+  // actions hold the hover action
+  if (was_reset)
+#pragma unroll 1
+    for (int s = 0; s < NH - t_ep; ++s) {
+      const float v[NA] = {ah, ah, ah, ah};
+      store_ring<SUB>(b.ring, N, (head1 + s) & (NH - 1), osub, sub, v);
+    }
+  if (sub == 0) {
+    b.head[ef] = head1;
+    b.t_ep[ef] = t_ep;
+    b.ep[ef] = ep;
+    acc.store(b, N, ef);
+  }
+}
+
+template <int TILES, bool EXTRAS>
+static hipError_t launch(const DevCfg& c, const SimBufs& b, const float* W, int T, int t_base,
+                         float* rewards, uint8_t* dones, float* states, float* tape,
+                         int ckpt_every, const float* ck_in, const RecSpan& rs, hipStream_t st) {
+  // A CU holds one workgroup (the staged weights take more than half of its
+  // LDS).  The batch is spread over the 256 CUs with 4 to 8 waves each: fewer
+  // than 4 would leave SIMDs idle, more than 8 do not fit.
+  const int waves = (c.n_envs + 16 * TILES - 1) / (16 * TILES);
+  int per = (waves + 255) / 256;
+  per = per < 4 ? 4 : per > 8 ? 8 : per;
+  const dim3 g((unsigned)((waves + per - 1) / per)), blk((unsigned)per * 64);
+  auto k = tape || ck_in || rs.buf[0] ? k_tile<TILES, EXTRAS, true>
+                                      : k_tile<TILES, EXTRAS, false>;
+  hipLaunchKernelGGL(k, g, blk, 0, st, c, b, W, T, t_base, rewards, dones, states, tape,
+                     ckpt_every, ck_in, rs);
+  return hipGetLastError();
+}
+
+hipError_t launch_tile(int tiles, const DevCfg& c, const SimBufs& b, const float* W, int T,
+                       int t_base, float* rewards, uint8_t* dones, float* states, float* tape,
+                       int ckpt_every, const float* ck_in, const RecSpan& rs, hipStream_t st) {
+  if (!rec_span_ok(rs)) return hipErrorInvalidValue;
+  const bool ex = (c.flags & (F_DISTURB | F_OBS_NOISE)) != 0 || c.target != nullptr;
+  auto f = tiles == 2 ? (ex ? launch<2, true> : launch<2, false>)
+                      : (ex ? launch<1, true> : launch<1, false>);
+  return f(c, b, W, T, t_base, rewards, dones, states, tape, ckpt_every, ck_in, rs, st);
+}
+
+}  // namespace qs
