@@ -107,7 +107,9 @@ enum {
 
 /* Execution variants of the forward step. */
 enum {
-  SIM_V_AUTO = 0,        /* the autotuned choice (fused MFMA until tuned)         */
+  SIM_V_AUTO = 0,        /* the autotuned choice; until tuned, by the batch size:
+                            SPLIT up to 4096 envs, MFMA4 up to 32768, else MFMA
+                            (bf16 actor: MFMA4)                                   */
   SIM_V_PLAIN = 1,       /* five kernels per step, intermediates through HBM      */
   SIM_V_FUSED_VALU = 2,  /* one fused kernel, actor on the vector ALUs            */
   SIM_V_FUSED_MFMA = 3,  /* one fused kernel, actor on matrix cores, 32 envs per wave:
@@ -178,7 +180,7 @@ int sim_step(sim_handle* h, const float* actor, const float* actions, float* rew
  * record_tape != 0 stores checkpoints for sim_backward; it requires
  * T <= max_tape_horizon and flags without TERMINATE and AUTORESET, else
  * SIM_E_STATE / SIM_E_INVAL.  A taped rollout runs on the kernel its
- * backward recomputes with (fp32 actor: split-actor below 16384 envs, 32 envs
+ * backward recomputes with (fp32 actor: split-actor up to 4096 envs, 32 envs
  * per wave from 32769 envs, else 16 envs per wave; the quarter-lane kernel
  * for the bf16 actor), whatever variant is set or tuned, and also writes the
  * backward's records of its last segments (the last one on the split-actor

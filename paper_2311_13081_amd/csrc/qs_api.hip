@@ -382,7 +382,12 @@ int sim_create(const sim_config* cfg, int device, sim_handle** out) {
   rc = SIM_OK;
   h->fp64 = (cfg->flags & SIM_F_FP64) != 0;
   h->bf16 = (cfg->flags & SIM_F_ACTOR_BF16) != 0;
-  if (h->bf16) h->tuned_variant = SIM_V_FUSED_MFMA4;  // the taped rollouts' kernel
+  // until tuned: the taped rollouts' kernel, which the size decides
+  switch (taped_kernel(h->dc)) {
+    case TAPED_SPLIT: h->tuned_variant = SIM_V_FUSED_SPLIT; break;
+    case TAPED_TILE2: h->tuned_variant = SIM_V_FUSED_MFMA; break;
+    default: h->tuned_variant = SIM_V_FUSED_MFMA4;
+  }
   if (h->fp64) {
     h->pc = make_precise(*cfg, cfg->seed);
     rc = rc ? rc : alloc((void**)&h->pb.state, N * NS * 8);
@@ -553,8 +558,9 @@ int sim_rollout(sim_handle* h, const float* actor, int32_t T, float* rewards, ui
   // for bit): the split-actor kernel for small fp32 batches, else the tile
   // kernel.
   const TapedKernel tk = taped_kernel(h->dc);
-  const int v = record_tape ? (tk == TAPED_SPLIT ? SIM_V_FUSED_SPLIT
-                               : tk == TAPED_TILE2 ? SIM_V_FUSED_MFMA : SIM_V_FUSED_MFMA4)
+  const int v = record_tape ? (tk == TAPED_SPLIT   ? SIM_V_FUSED_SPLIT
+                               : tk == TAPED_TILE2 ? SIM_V_FUSED_MFMA
+                                                   : SIM_V_FUSED_MFMA4)
                             : effective_variant(h);
   const int spl = effective_spl(h);
   float* tape = record_tape ? h->tape : nullptr;

@@ -416,7 +416,7 @@ __device__ inline void deriv(const Body<R>& B, R arm, R km, R g, const R x[NS], 
 }
 
 // One classical RK4 step, set points held.  Optional renormalisation of q.
-// between(k), k = 0 .. 3, is called ahead of each right-hand side: work that a
+// between(i), i = 0 .. 3, is called ahead of each right-hand side: work that a
 // kernel interleaves with the integration.
 struct Nothing {
   __device__ inline void operator()(int) const {}

@@ -137,18 +137,21 @@ hipError_t launch_bf16_quarter(const DevCfg& c, const SimBufs& b, const float* W
 hipError_t launch_split(const DevCfg& c, const SimBufs& b, const float* W, int T, int t_base,
                         float* rewards, uint8_t* dones, float* states, float* tape,
                         int ckpt_every, const float* ck_in, const RecSpan& rs, hipStream_t st);
-// The kernel of taped rollouts and of their backward recompute (the two must
-// agree bit for bit): with the fp32 actor the split-actor kernel below 16384
-// envs (the tile kernel leaves SIMDs idle there), two tiles per wave from
-// 32769 envs (with one, more than two waves per SIMD would be needed), one
-// tile between them; the quarter-lane kernel for the bf16 actor.
-constexpr int TAPE_SPLIT_MAX_ENVS = 16384;
-constexpr int TAPE_TILE2_MIN_ENVS = 32769;
+// Which kernel a batch runs on unless a variant is set or tuned, and which one
+// its taped rollouts and their recompute run on (the fp32 kernels agree bit
+// for bit).  us per step of a 256-step rollout:
+//   up to 4096 envs the split-actor kernel (2.35 at 4096; its workgroup takes
+//     16 envs and a CU, so 6000 envs take two rounds, 4.57, against 3.36 for
+//     one tile per wave),
+//   up to 32768 envs one tile per wave (5.5 at 32768 against 5.8 for two; 10.4
+//     at 33000, where it would need more than two waves per SIMD, against 7.5),
+//   beyond two tiles per wave (8.9 at 65536).
+constexpr int SPLIT_MAX_ENVS = 4096, TILE1_MAX_ENVS = 32768;
 enum TapedKernel { TAPED_SPLIT, TAPED_TILE1, TAPED_TILE2, TAPED_BF16 };
 inline TapedKernel taped_kernel(const DevCfg& c) {
   if (c.flags & F_ACTOR_BF16) return TAPED_BF16;
-  if (c.n_envs < TAPE_SPLIT_MAX_ENVS) return TAPED_SPLIT;
-  return c.n_envs >= TAPE_TILE2_MIN_ENVS ? TAPED_TILE2 : TAPED_TILE1;
+  if (c.n_envs <= SPLIT_MAX_ENVS) return TAPED_SPLIT;
+  return c.n_envs <= TILE1_MAX_ENVS ? TAPED_TILE1 : TAPED_TILE2;
 }
 // One-env-per-lane fused kernel (qs_fused.hip): the actor on the vector ALUs,
 // or the bf16 actor under its flag, or given actions (ext_act, [T][4][N]).

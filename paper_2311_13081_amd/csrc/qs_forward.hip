@@ -164,7 +164,7 @@ constexpr int P_ENVS = 128;  // envs of a workgroup (4 waves of 2 tiles)
 __global__ void __launch_bounds__(256) k_plain_l1(int N, const float* __restrict__ W,
                                                   const float* __restrict__ in,
                                                   float* __restrict__ out) {
-  __shared__ u4t sW[T_G1 * 3 * 64];
+  __shared__ u4t sW[T_G2 * T_P * 64];
   const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
   const int first = blockIdx.x * P_ENVS + 32 * (threadIdx.x >> 6);
   // every input load in flight before the weights are staged
@@ -181,34 +181,32 @@ __global__ void __launch_bounds__(256) k_plain_l1(int N, const float* __restrict
     if (lg >= 2) F[b][4] = 0.0f;  // features 18, 19: padding
   }
   __builtin_amdgcn_sched_barrier(0);
-  stage_fragments<4>(W, sW, 0, T_G1);
+  stage_fragments<4>(W, sW, 0, T_G2);
   __syncthreads();
   if (first >= N) return;
-  f4t a1[4][2];
+  u4t x[4][2][T_P], xs[1][2][T_P];
 #pragma unroll
-  for (int n = 0; n < 4; ++n)
+  for (int b = 0; b < 2; ++b) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a1[n][0][r] = a1[n][1][r] = W[OFF_B1 + 16 * n + 4 * lg + r];
-#pragma unroll
-  for (int c = 0; c < 5; ++c) {
-    u4t x[2][3];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      if (c == 4) {
-        state_operand(F[b], x[b]);
-        continue;
-      }
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        uint32_t p[3];
-        split_pair(v[b][c & 3][2 * q], v[b][c & 3][2 * q + 1], p);
+        uint32_t p[T_P];
+        split_pair(v[b][c][2 * q], v[b][c][2 * q + 1], p);
 #pragma unroll
-        for (int s = 0; s < 3; ++s) x[b][s][q] = p[s];
+        for (int s = 0; s < T_P; ++s) x[c][b][s][q] = p[s];
       }
-    }
-    Frags<4> f;
-    f.load(sW, 4 * c, lane);
-    tile_products<4, 2>(f, x, a1);
+    state_operand(F[b], xs[0][b]);
+  }
+  f4t a1[4][2];
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    f4t h[1][2], as[1][2];
+    Frags<1> f;
+    split_sum<4, 1, 2>([&](int c) { f.load(sW, 4 * n + c, 0, lane); return f; }, x, h);
+    split_sum<1, 1, 2>([&](int) { f.load(sW, T_GS + n, 0, lane); return f; }, xs, as);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) a1[n][b] = h[0][b] + as[0][b];
   }
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
@@ -226,7 +224,7 @@ __global__ void __launch_bounds__(256) k_plain_l1(int N, const float* __restrict
 __global__ void __launch_bounds__(256) k_plain_l2(int N, const float* __restrict__ W,
                                                   const float* __restrict__ in,
                                                   float* __restrict__ out) {
-  __shared__ u4t sW[(T_G - T_G1) * 3 * 64];
+  __shared__ u4t sW[(T_G - T_G2) * T_P * 64];
   const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
   const int first = blockIdx.x * P_ENVS + 32 * (threadIdx.x >> 6);
   f4t h1[4][2];
@@ -239,22 +237,24 @@ __global__ void __launch_bounds__(256) k_plain_l2(int N, const float* __restrict
       for (int r = 0; r < 4; ++r) h1[n][b][r] = in[(size_t)(16 * n + 4 * lg + r) * N + e];
   }
   __builtin_amdgcn_sched_barrier(0);
-  stage_fragments<4>(W, sW, T_G1, T_G);
+  stage_fragments<4>(W, sW, T_G2, T_G);
   __syncthreads();
   if (first >= N) return;
+  u4t x[2][2][T_P];
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) hidden_operand(h1[2 * m][b], h1[2 * m + 1][b], x[m][b]);
   f4t a2[4][2];
 #pragma unroll
-  for (int n = 0; n < 4; ++n)
+  for (int n = 0; n < 4; ++n) {
+    f4t acc[1][2], b2;
+    Frags<1> f;
+    split_sum<2, 1, 2>([&](int m) { f.load(sW, 2 * n + m, 0, lane); return f; }, x, acc);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a2[n][0][r] = a2[n][1][r] = W[OFF_B2 + 16 * n + 4 * lg + r];
+    for (int r = 0; r < 4; ++r) b2[r] = W[OFF_B2 + 16 * n + 4 * lg + r];
 #pragma unroll
-  for (int m = 0; m < 2; ++m) {
-    u4t x[2][3];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) hidden_operand(h1[2 * m][b], h1[2 * m + 1][b], x[b]);
-    Frags<4> f;
-    f.load(sW, 4 * m, lane);
-    tile_products<4, 2>(f, x, a2);
+    for (int b = 0; b < 2; ++b) a2[n][b] = acc[0][b] + b2;
   }
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
@@ -292,7 +292,9 @@ __global__ void __launch_bounds__(256) k_plain_l3(int N, const float* __restrict
   __syncthreads();
   if (first >= N) return;
   float z3[NA];
-  tile_layer3<2>(sW, sW + NA * T_W3_LD, h2, z3);
+  Layer3 l3;
+  l3.load(sW, sW + NA * T_W3_LD);
+  tile_layer3<2>(l3.w, l3.b, h2, z3);
   const int oe = first + 16 * (lg & 1) + li;
   if (oe < N)
 #pragma unroll

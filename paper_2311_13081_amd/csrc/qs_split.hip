@@ -4,13 +4,23 @@
 //
 // A workgroup advances one 16-env tile.  Each of its 4 waves holds it in the
 // tile layout (qs_tile.h), so every env sits on 16 lanes.  Wave w evaluates
-// unit tile w (16 units) of layers 1 and 2, a quarter of the matrix work; the
-// layer-1 results are split into their bf16 parts by the wave that owns them
-// and exchanged through LDS as layer-2 operands, the layer-2 results as fp32
-// tiles, with one barrier per layer.  Every wave then evaluates layer 3 and
-// the dynamics of the 16 envs: the same arithmetic on identical inputs, so
-// the copies agree bit for bit, and the products are the tile kernel's in its
-// order, so its results are the same too.  Wave 0 writes the outputs.
+// unit tile w (16 units) of layers 1 and 2, a quarter of the matrix work, from
+// weight fragments that it keeps in registers (84 of them: no staging of
+// the actor in LDS and no weight reads in the loop); the layer-1 results are split into their bf16 parts by the wave that
+// owns them and exchanged through LDS as layer-2 operands, the layer-2 results
+// as fp32 tiles, with one barrier per layer.  Every wave then evaluates layer
+// 3 and the dynamics of the 16 envs: the same arithmetic on identical inputs,
+// so the copies agree bit for bit, and the products are the tile kernel's in
+// its order, so its results are the same too.  Wave 0 writes the outputs.
+//
+// What bounds it is the serial chain of a step: features, 6 dependent matrix
+// products, exchange, 12 products, exchange, layer 3, tanh, four right-hand
+// sides.  The history products of layer 1 (24 of its 30) are off the chain:
+// they run beside the right-hand sides of the step before.  4096 envs: 2.35 us
+// per step (3.15 us with fp32 products, the actor in LDS and every product on
+// the chain).  One wave per SIMD with up to 512 registers; two waves of 256
+// spill and take 2.67 us there, 3.96 us at 8192 envs against 3.38 us for the
+// tile kernel.
 // Fused multiply-adds only where one expression of the source holds the
 // product and the sum: the kernels that promise equal results then round the
 // shared arithmetic the same way (left to the optimiser, fusing depends on what
@@ -28,32 +38,54 @@ struct SplitXch {
   f4t x2[4][64];
 };
 
-// Layers 1 to 3 of the workgroup's 16 envs: z3 of the lane's env in every lane
-// of every wave.  When rec != NULL (the step's record), writes this wave's
-// tile of the layer pre-activations (rows 16 w + 4 lg + r; zoff addresses row
-// 4 lg of this lane's env) and its byte of the ReLU mask word (tile_mask; moff
-// addresses the word), for lanes with on set.
-__device__ inline void actor_split(const float* lds, SplitXch& xc, const TileHist<1>& H,
-                                   const float F[5], float z3[NA], float* __restrict__ rec,
-                                   bool on, uint32_t zoff, uint32_t moff) {
-  const int lane = threadIdx.x & 63, lg = lane >> 4;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const u4t* frag = reinterpret_cast<const u4t*>(lds);
-  f4t a1[1][1], a2[1][1];
-  a1[0][0] = *reinterpret_cast<const f4t*>(&lds[T_B1 + 16 * w + 4 * lg]);
-  a2[0][0] = *reinterpret_cast<const f4t*>(&lds[T_B2 + 16 * w + 4 * lg]);
+// A wave's share of the actor: the fragments of unit tile w, its biases, and
+// layer 3.
+struct SplitActor {
+  Frags<1> hist[4], state, l2[2];
+  f4t b2, b3, w3[4];
+
+  __device__ inline void load(const float* __restrict__ W, int w, int lane) {
+    const int lg = lane >> 4;
 #pragma unroll
-  for (int c = 0; c < 5; ++c) {
-    u4t x[1][3];
-    if (c < 4) {
+    for (int c = 0; c < 4; ++c) load_fragment(W, 4 * w + c, lane, hist[c].a[0]);
+    load_fragment(W, T_GS + w, lane, state.a[0]);
 #pragma unroll
-      for (int s = 0; s < 3; ++s) x[0][s] = H.h[0][s][c];
-    } else {
-      state_operand(F, x[0]);
+    for (int m = 0; m < 2; ++m) load_fragment(W, T_G2 + 2 * w + m, lane, l2[m].a[0]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      b2[r] = W[OFF_B2 + 16 * w + 4 * lg + r];
+      b3[r] = lg == 0 ? W[OFF_B3 + r] : 0.0f;
+#pragma unroll
+      for (int n = 0; n < 4; ++n) w3[n][r] = W[OFF_W3 + (lane & 3) * NHID + 16 * n + 4 * lg + r];
     }
-    Frags<1> f;
-    f.load(frag, 4 * c + w, lane);
-    tile_products<1, 1>(f, x, a1);
+  }
+  // layer 1's history sums of the wave's unit tile
+  __device__ inline void history(const TileHist<1>& H, f4t (&a1)[1][1]) const {
+    u4t x[4][1][T_P];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int s = 0; s < T_P; ++s) x[c][0][s] = H.h[0][s][c];
+    split_sum<4, 1, 1>([&](int c) { return hist[c]; }, x, a1);
+  }
+};
+
+// The rest of layer 1 (the state features and the bias; a1 holds the history
+// sums), layers 2 and 3 of the workgroup's 16 envs: z3 of the lane's env
+// in every lane of every wave.  When rec != NULL (the step's record), writes
+// this wave's tile of the layer pre-activations (rows 16 w + 4 lg + r; zoff
+// addresses row 4 lg of this lane's env) and its byte of the ReLU mask word
+// (tile_mask; moff addresses the word), for lanes with on set.
+__device__ inline void actor_split(const SplitActor& A, SplitXch& xc, f4t (&a1)[1][1],
+                                   const float F[5], float z3[NA], float* __restrict__ rec,
+                                   bool on, uint32_t zoff, uint32_t moff, int w) {
+  const int lane = threadIdx.x & 63;
+  {
+    u4t x[1][1][T_P];
+    state_operand(F, x[0][0]);
+    f4t as[1][1];
+    split_sum<1, 1, 1>([&](int) { return A.state; }, x, as);
+    a1[0][0] += as[0][0];
   }
   uint32_t mask = 0u;
   if (rec) {
@@ -73,14 +105,15 @@ __device__ inline void actor_split(const float* lds, SplitXch& xc, const TileHis
       *(reinterpret_cast<uint2*>(&xc.x1[s][w >> 1][lane]) + (w & 1)) = uint2{p[s], q[s]};
   }
   __syncthreads();
+  f4t a2[1][1];
+  {
+    u4t x[2][1][T_P];
 #pragma unroll
-  for (int m = 0; m < 2; ++m) {
-    u4t x[1][3];
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int s = 0; s < 3; ++s) x[0][s] = xc.x1[s][m][lane];
-    Frags<1> f;
-    f.load(frag, T_G1 + 4 * m + w, lane);
-    tile_products<1, 1>(f, x, a2);
+      for (int s = 0; s < T_P; ++s) x[m][0][s] = xc.x1[s][m][lane];
+    split_sum<2, 1, 1>([&](int m) { return A.l2[m]; }, x, a2);
+    a2[0][0] += A.b2;
   }
   if (rec) {
 #pragma unroll
@@ -96,39 +129,39 @@ __device__ inline void actor_split(const float* lds, SplitXch& xc, const TileHis
   f4t h2[4][1];
 #pragma unroll
   for (int n = 0; n < 4; ++n) h2[n][0] = xc.x2[n][lane];
-  tile_layer3<1>(lds + T_W3, lds + T_B3, h2, z3);
+  tile_layer3<1>(A.w3, A.b3, h2, z3);
 }
 
 // T steps of the whole env step for 16 envs per workgroup (blockDim 256).
 // A barrier separates each layer's writes of the exchange buffers from the
 // reads, and the next step's writes of a buffer come after the barrier that
 // follows every wave's reads of it, so two barriers per step suffice.
-// As the tile kernel: with tape != NULL, checkpoints every ckpt_every steps;
-// with ck_in != NULL the launch starts from that checkpoint (no write-back of
-// the env state); with rs.buf[0] != NULL the record of the span rs.  Wave 0
-// writes everything except the layer pre-activations and the mask bytes,
-// which each wave writes for its own tile.
-template <bool EXTRAS>
-__global__ void __launch_bounds__(256)
+// TAPE: as the tile kernel: with tape != NULL, checkpoints every ckpt_every
+// steps; with ck_in != NULL the launch starts from that checkpoint (no
+// write-back of the env state); with rs.buf[0] != NULL the record of the span
+// rs.  Wave 0 writes everything except the layer pre-activations and the mask
+// bytes, which each wave writes for its own tile.
+template <bool EXTRAS, bool TAPE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 k_split(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
         float* __restrict__ rewards, uint8_t* __restrict__ dones, float* __restrict__ states,
         float* __restrict__ tape, int ckpt_every, const float* __restrict__ ck_in,
         RecSpan rs) {
-  __shared__ __attribute__((aligned(16))) float lds[T_TOTAL];
   __shared__ SplitXch xc;
+  __shared__ float next_start[NRES * 256];
   const int N = c.n_envs;
   const int env0 = blockIdx.x * 16;
-  if (env0 >= N) return;  // the whole workgroup (no barrier is reached)
-  stage_tile(W, lds);
-  __syncthreads();
   const int lane = threadIdx.x & 63, j = lane & 15, k = lane >> 4;
-  const bool writer = threadIdx.x < 64;  // wave 0
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  SplitActor A;
+  A.load(W, w, lane);
+  const bool writer = w == 0;
   const int env = env0 + j;
   const bool active = env < N;
   const int e = active ? env : env0;
   // from a checkpoint (the backward's recompute): no write-back of the env
   // state; the steps of the span rs are recorded (rec_at)
-  const bool REC = ck_in != nullptr;
+  const bool REC = TAPE && ck_in != nullptr;
 
   float th[NP];
 #pragma unroll
@@ -139,6 +172,7 @@ k_split(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
   float x[NS];
   TileHist<1> H;
   int head0 = 0, t_ep = 0, ep = 0;
+  EpAcc acc;
   if (REC) {
 #pragma unroll
     for (int i = 0; i < NS; ++i) x[i] = ck_in[(size_t)i * N + e];
@@ -148,6 +182,7 @@ k_split(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
                  ck_in[(size_t)(NS + (2 * q + 1) * NA + k) * N + e]);
     t_ep = __float_as_int(ck_in[(size_t)CK_TEP * N + e]);
     ep = __float_as_int(ck_in[(size_t)CK_EP * N + e]);
+    acc.cur = acc.last = 0.0f, acc.len = 0;
   } else {
 #pragma unroll
     for (int i = 0; i < NS; ++i) x[i] = b.state[(size_t)i * N + e];
@@ -160,13 +195,8 @@ k_split(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     for (int q = 0; q < 16; ++q) H.set_pair(0, q, v[2 * q], v[2 * q + 1]);
     t_ep = b.t_ep[e];
     ep = b.ep[e];
-  }
-  // episode accumulators: the recompute from a checkpoint leaves them alone
-  EpAcc acc;
-  if (REC)
-    acc.cur = acc.last = 0.0f, acc.len = 0;
-  else
     acc.load(b, N, e);
+  }
   SetPoint sp;
   if (EXTRAS) sp.load(c, N, e);
   bool was_reset = false;
@@ -177,75 +207,73 @@ k_split(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     disturbance(c, (uint32_t)e, (uint32_t)ep, d);
     set_disturbance(B, d);
   }
-  // next episode's start state drawn ahead (long launches only)
+  // next episode's start state drawn ahead (long launches only), kept in LDS
   const bool ahead = T >= 2 * RESERVE_PERIOD && (c.flags & F_AUTORESET) != 0;
-  float nx[NRES];
-  bool have = ahead;
-  if (ahead) draw_ahead<0>(c, (uint32_t)e, (uint32_t)(ep + 1), wh, nx);
-
-  if (states && t_base == 0 && active && writer)
+  float* nxp = next_start + threadIdx.x;
+  const auto draw_next = [&]() {
+    float nx[NRES];
+    draw_ahead<0>(c, (uint32_t)e, (uint32_t)(ep + 1), wh, nx);
 #pragma unroll
-    for (int i = 0; i < NS; ++i)
-      if ((i & 3) == k) states[(size_t)i * N + e] = x[i];
+    for (int i = 0; i < NRES; ++i) nxp[i * 256] = nx[i];
+  };
+  bool have = ahead;
+  if (ahead) draw_next();
+
+  const uint32_t ok = 4u * (uint32_t)(k * N + e);  // byte offset of row k of the env
+  if (states && t_base == 0 && active && writer) store_rows<4, NS>(states, N, ok, k, x);
+
+  f4t a1[1][1];  // layer 1's history sums of the coming step
+  A.history(H, a1);
 
   for (int t = 0; t < T; ++t) {
-    __asm__ volatile("" ::: "memory");
-    const uint32_t eo = opaque((uint32_t)e);
+    const uint32_t so = opaque(ok);
     const int gt = t_base + t;
     RecAt ra;
-    const bool rec_on = rec_at(rs, gt, ra);  // wave uniform
-    const int rt_step = ra.step;
-    if (tape && (gt % ckpt_every) == 0 && active && writer) {
+    const bool rec_on = TAPE && rec_at(rs, gt, ra);  // wave uniform
+    if (TAPE && tape && (gt % ckpt_every) == 0 && active && writer) {
       float* ck = tape + (size_t)(gt / ckpt_every) * CK_F * N;
+      store_rows<4, NS>(ck, N, so, k, x);
 #pragma unroll
-      for (int i = 0; i < NS; ++i)
-        if ((i & 3) == k) ck[(size_t)i * N + eo] = x[i];
-      const uint32_t kc = opaque((uint32_t)(k * N + e));
-#pragma unroll
-      for (int s = 0; s < NH; ++s) ck[(size_t)(NS + s * NA) * N + kc] = H.get(0, s);
+      for (int s = 0; s < NH; ++s) at_byte(ck + (size_t)(NS + s * NA) * N, so) = H.get(0, s);
       if (k == 0) {
-        ck[(size_t)CK_TEP * N + eo] = __int_as_float(t_ep);
-        ck[(size_t)CK_EP * N + eo] = __int_as_float(ep);
+        at_byte(ck + (size_t)CK_TEP * N, so) = __int_as_float(t_ep);
+        at_byte(ck + (size_t)CK_EP * N, so) = __int_as_float(ep);
       }
     }
     float F[1][5];
     tile_features<1, EXTRAS>(c, sp, (uint32_t)e, (uint32_t)ep, t_ep, x, k, F);
-    float* rt = rec_on ? ra.base + rec_step(rt_step, N) : nullptr;
-    const uint32_t zoff = opaque((uint32_t)(rb_at(env0 + j, REC_F) + 4 * k * RB));
-    const uint32_t moff = opaque((uint32_t)(rb_at(env0 + j, REC_F) + k * RB));
+    float* rt = rec_on ? ra.base + rec_step(ra.step, N) : nullptr;
+    const uint32_t zoff = TAPE ? opaque((uint32_t)(rb_at(env0 + j, REC_F) + 4 * k * RB)) : 0u;
+    const uint32_t moff = TAPE ? opaque((uint32_t)(rb_at(env0 + j, REC_F) + k * RB)) : 0u;
     float z3[NA];
-    actor_split(lds, xc, H, F[0], z3, rt, active, zoff, moff);
-    float a[NA];
+    actor_split(A, xc, a1, F[0], z3, TAPE ? rt : nullptr, active, zoff, moff, w);
+    float a[NA], ak[1];
 #pragma unroll
     for (int i = 0; i < NA; ++i) a[i] = tanh_act(z3[i]);
-    float ak[1];
     to_tiles<1>(a, k, ak);
-    if (rec_on && active && writer) {
-      const uint32_t koff = opaque((uint32_t)(rb_at(e, REC_F) + k * RB));
-      const uint32_t roff = opaque((uint32_t)rb_at(e, REC_F));
+    if (TAPE && rec_on && active && writer) {
 #pragma unroll
-      for (int cc = 0; cc < 5; ++cc)
-        if (4 * cc + k < 18) rt[(size_t)(REC_O + 4 * cc) * RB + koff] = F[0][cc];
+      for (int q = 0; q < 5; ++q)
+        if (4 * q + k < 18) rt[(size_t)(REC_O + 4 * q) * RB + moff] = F[0][q];
       float* act = ra.base + rec_act(ra.n, N);
       const uint32_t aoff = opaque((uint32_t)(rb_at(e, (NH + ra.n) * NA) + k * RB));
-      if (rt_step == 0) {
+      if (ra.step == 0) {
 #pragma unroll
         for (int s = 0; s < NH; ++s) act[(size_t)(s * NA) * RB + aoff] = H.get(0, s);
       }
-      act[(size_t)((NH + rt_step) * NA) * RB + aoff] = ak[0];
-#pragma unroll
-      for (int i = 0; i < NS; ++i)
-        if ((i & 3) == k) rt[(size_t)(REC_X + i) * RB + roff] = x[i];
-      rt[(size_t)REC_A * RB + koff] = ak[0];
+      act[(size_t)((NH + ra.step) * NA) * RB + aoff] = ak[0];
+      rt[(size_t)REC_A * RB + moff] = ak[0];
+      store_rows<4, NS>(rt + REC_X * RB, RB, 4u * moff, k, x);
     }
     // the action goes to the history ring in memory as it is applied (the
     // last 32 of a launch; the older ones would be overwritten)
     if (!REC && t >= T - NH && active && writer)
-      b.ring[(size_t)(((head0 + t) & (NH - 1)) * NA + k) * N + eo] = ak[0];
+      b.ring[(size_t)(((head0 + t) & (NH - 1)) * NA) * N + (so >> 2)] = ak[0];
     uint32_t ap[1][T_P];
     split_pair(ak[0], 0.0f, ap[0]);
-#pragma unroll
-    for (int c4 = 0; c4 < 4; ++c4) H.push_chunk(c4, ap);
+    H.push(ap);
+    // beside the right-hand sides (no dependence between the two)
+    A.history(H, a1);
     float u[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) u[i] = action_to_rpm(c, a[i]);
@@ -258,11 +286,20 @@ k_split(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     if (__ballot(rst)) {  // wave uniform
       const float ahk[1] = {ah};
       H.fill(&rst, ahk);
+      A.history(H, a1);
       if (rst) {
         ++ep;
         t_ep = 0;
         was_reset = true;
-        reset_from_reserve<0>(c, (uint32_t)e, (uint32_t)ep, wh, nx, have, x);
+        if (have) {
+#pragma unroll
+          for (int i = 0; i < NRES; ++i) x[i] = nxp[i * 256];
+#pragma unroll
+          for (int i = NRES; i < NS; ++i) x[i] = wh;
+          have = false;
+        } else {
+          reset_draw<0>(c, (uint32_t)e, (uint32_t)ep, wh, x);
+        }
         if (EXTRAS) {
           float dd[6];
           disturbance(c, (uint32_t)e, (uint32_t)ep, dd);
@@ -271,35 +308,31 @@ k_split(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
       }
     }
     if (ahead && (t & (RESERVE_PERIOD - 1)) == RESERVE_PERIOD - 1 && !have) {
-      draw_ahead<0>(c, (uint32_t)e, (uint32_t)(ep + 1), wh, nx);
+      draw_next();
       have = true;
     }
     if (active && writer) {
-      if (k == 0 && rewards) rewards[(size_t)gt * N + eo] = r;
-      if (k == 1 && dones) dones[(size_t)gt * N + eo] = (uint8_t)d;
-      if (states)
-#pragma unroll
-        for (int i = 0; i < NS; ++i)
-          if ((i & 3) == k) states[((size_t)(gt + 1) * NS + i) * N + eo] = x[i];
+      if (k == 0) {
+        if (rewards) at_byte(rewards + (size_t)gt * N, so) = r;
+        if (dones) at_byte(dones + (size_t)gt * N, so >> 2) = (uint8_t)d;
+      }
+      if (states) store_rows<4, NS>(states + (size_t)(gt + 1) * NS * N, N, so, k, x);
     }
   }
   if (!active || !writer || REC) return;
-  const uint32_t ef = opaque((uint32_t)e);
-#pragma unroll
-  for (int i = 0; i < NS; ++i)
-    if ((i & 3) == k) b.state[(size_t)i * N + ef] = x[i];
+  store_rows<4, NS>(b.state, N, ok, k, x);
   const int head1 = (head0 + T) & (NH - 1);
   // after a reset in this launch the slots older than the episode's t_ep
   // actions hold the hover action
   if (was_reset)
 #pragma unroll 1
     for (int s = 0; s < NH - t_ep; ++s)
-      b.ring[(size_t)(((head1 + s) & (NH - 1)) * NA + k) * N + ef] = ah;
+      b.ring[(size_t)(((head1 + s) & (NH - 1)) * NA) * N + (ok >> 2)] = ah;
   if (k == 0) {
-    b.head[ef] = head1;
-    b.t_ep[ef] = t_ep;
-    b.ep[ef] = ep;
-    acc.store(b, N, ef);
+    b.head[e] = head1;
+    b.t_ep[e] = t_ep;
+    b.ep[e] = ep;
+    acc.store(b, N, e);
   }
 }
 
@@ -309,7 +342,9 @@ hipError_t launch_split(const DevCfg& c, const SimBufs& b, const float* W, int T
   if (!rec_span_ok(rs)) return hipErrorInvalidValue;
   const unsigned grid = (unsigned)((c.n_envs + 15) / 16);
   const bool ex = (c.flags & (F_DISTURB | F_OBS_NOISE)) != 0 || c.target != nullptr;
-  auto k = ex ? k_split<true> : k_split<false>;
+  const bool tp = tape || ck_in || rs.buf[0];
+  auto k = ex ? (tp ? k_split<true, true> : k_split<true, false>)
+              : (tp ? k_split<false, true> : k_split<false, false>);
   hipLaunchKernelGGL(k, dim3(grid), dim3(256), 0, st, c, b, W, T, t_base, rewards, dones, states,
                      tape, ckpt_every, ck_in, rs);
   return hipGetLastError();

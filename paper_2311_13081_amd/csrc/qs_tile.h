@@ -8,7 +8,8 @@
 //   chunk c = 0..3 of layer 1: element e is history slot 8 c + e (oldest
 //       first), component lg;
 //   chunk 4: element e < 5 is state feature 4 e + lg (p, R row-major, v, w; 0
-//       past feature 17), the rest 0;
+//       past feature 17), element 5 the constant one of the bias (weight b1 in
+//       lane group 0, 0 elsewhere), the rest 0;
 //   chunk m of layer 2: element e is hidden unit 32 m + 16 (e / 4) + 4 lg + e %
 //       4, the order in which the layer-1 result registers arrive (register r
 //       of result tile n: unit 16 n + 4 lg + r of env 16 b + li).
@@ -19,11 +20,14 @@
 // 2^-16 of the leading one; the three left out are below 2^-25.  The six
 // products run at 16 times the rate of the fp32 shapes, 2.7 times per fp32
 // product, and overlap with vector instructions, which the fp32 shapes do
-// not.  Against 64 bits the result is closer than the fp32 chain's, because
-// each instruction rounds its 32 products once: relative rms error at K =
-// 160 1.7e-7 against 2.3e-7, at K = 64 9e-8 against 1.4e-7.
-// The order of the terms is the same in every kernel, so they agree bit for
-// bit.
+// not.  A sum takes the five small terms of all its inputs first and the
+// leading ones last, so it is rounded at its own size only once per leading
+// product, and biases are added at the end: against 64 bits that is closer than
+// the fp32 chain (relative rms error at K = 160 6e-8 against 2.3e-7) and
+// without the bias of a chain that rounds 30 times at full size (2.6 times the
+// rms error, and a mean error of 1e-8 in the actions, which a closed loop turns
+// into an offset).  The order of the terms is the same in every kernel, so they
+// agree bit for bit.
 #pragma once
 #include "qs_device.h"
 
@@ -38,23 +42,26 @@ typedef float f2t __attribute__((ext_vector_type(2)));
 constexpr int T_P = 3;  // bf16 parts of a value
 
 // LDS: operand fragments of 64 lanes x 16 bytes ([group][part][lane], so a
-// read is one conflict-free b128 per lane), then the fp32 biases and layer 3.
-// Groups: layer 1 chunk c, unit tile n at 4 c + n; layer 2 chunk m at 20 + 4 m + n.
-constexpr int T_C1 = 5, T_C2 = 2, T_G1 = 4 * T_C1, T_G = T_G1 + 4 * T_C2;
+// read is one conflict-free b128 per lane), then layer 2's and 3's biases and
+// layer 3's weights.  Groups, in the order a step reads them: layer 1's history
+// chunk c of unit tile n at 4 n + c, its state chunk at 16 + n, layer 2's chunk m
+// of unit tile n at 20 + 2 n + m.
+constexpr int T_GS = 16, T_G2 = 20, T_G = 28;
 constexpr int T_W3_LD = 68;  // layer-3 row pitch: the 16-byte reads stay aligned
-constexpr int T_B1 = T_G * T_P * 256, T_B2 = T_B1 + NHID, T_W3 = T_B2 + NHID,
-              T_B3 = T_W3 + NA * T_W3_LD, T_TOTAL = T_B3 + 4;  // floats
+constexpr int T_B2 = T_G * T_P * 256, T_W3 = T_B2 + NHID, T_B3 = T_W3 + NA * T_W3_LD,
+              T_TOTAL = T_B3 + 4;  // floats
 
 // Source index (into the flat actor) of element e of lane l in group g, -1
 // for padding.
 __device__ inline int tile_src(int g, int l, int e) {
   const int li = l & 15, lg = l >> 4;
-  if (g < T_G1) {
-    const int c = g >> 2, row = OFF_W1 + (16 * (g & 3) + li) * NO;
-    if (c < 4) return row + 18 + NA * (8 * c + e) + lg;
-    return 4 * e + lg < 18 ? row + 4 * e + lg : -1;
+  if (g < T_GS) return OFF_W1 + (16 * (g >> 2) + li) * NO + 18 + NA * (8 * (g & 3) + e) + lg;
+  if (g < T_G2) {
+    const int unit = 16 * (g - T_GS) + li;
+    if (e == 5 && lg == 0) return OFF_B1 + unit;
+    return e < 5 && 4 * e + lg < 18 ? OFF_W1 + unit * NO + 4 * e + lg : -1;
   }
-  const int m = (g - T_G1) >> 2, n = (g - T_G1) & 3;
+  const int n = (g - T_G2) >> 1, m = (g - T_G2) & 1;
   return OFF_W2 + (16 * n + li) * NHID + 32 * m + 16 * (e >> 2) + 4 * lg + (e & 3);
 }
 
@@ -72,6 +79,24 @@ __device__ inline void split_pair(float a, float b, uint32_t p[T_P]) {
   b -= bf_hi(p[0]);
   p[1] = pack_bf16(a, b);
   p[2] = pack_bf16(a - bf_lo(p[1]), b - bf_hi(p[1]));
+}
+
+// The fragment of group g of lane l, straight from the actor.
+__device__ inline void load_fragment(const float* __restrict__ W, int g, int l, u4t (&a)[T_P]) {
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int s = tile_src(g, l, e);
+    v[e] = W[s < 0 ? 0 : s];
+    if (s < 0) v[e] = 0.0f;
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint32_t p[T_P];
+    split_pair(v[2 * q], v[2 * q + 1], p);
+#pragma unroll
+    for (int s = 0; s < T_P; ++s) a[s][q] = p[s];
+  }
 }
 
 // Stages groups [g0, g1) of the actor's fragments at dst (u4t), every thread
@@ -113,14 +138,14 @@ __device__ inline void stage_fragments(const float* __restrict__ W, u4t* dst, in
 // The whole actor into LDS.
 __device__ inline void stage_tile(const float* __restrict__ W, float* lds) {
   stage_fragments<4>(W, reinterpret_cast<u4t*>(lds), 0, T_G);
-  for (int i = threadIdx.x; i < NA * T_W3_LD + 2 * NHID + NA; i += blockDim.x) {
-    if (i < 2 * NHID) {
-      lds[T_B1 + i] = W[i < NHID ? OFF_B1 + i : OFF_B2 + i - NHID];
-    } else if (i < 2 * NHID + NA * T_W3_LD) {
-      const int r = (i - 2 * NHID) / T_W3_LD, k = (i - 2 * NHID) % T_W3_LD;
-      lds[T_W3 + i - 2 * NHID] = k < NHID ? W[OFF_W3 + r * NHID + k] : 0.0f;
+  for (int i = threadIdx.x; i < NHID + NA * T_W3_LD + NA; i += blockDim.x) {
+    if (i < NHID) {
+      lds[T_B2 + i] = W[OFF_B2 + i];
+    } else if (i < NHID + NA * T_W3_LD) {
+      const int r = (i - NHID) / T_W3_LD, k = (i - NHID) % T_W3_LD;
+      lds[T_W3 + i - NHID] = k < NHID ? W[OFF_W3 + r * NHID + k] : 0.0f;
     } else {
-      const int o = i - 2 * NHID - NA * T_W3_LD;
+      const int o = i - NHID - NA * T_W3_LD;
       lds[T_B3 + o] = W[OFF_B3 + o];
     }
   }
@@ -131,32 +156,55 @@ __device__ inline f4t mfma_bf(u4t a, u4t b, f4t c) {
                                                  __builtin_bit_cast(bf8t, b), c, 0, 0, 0);
 }
 
-// The weight fragments of a step are read in the order of their groups, one
-// read ahead: while the products of NN unit tiles run, the next NN tiles'
-// fragments (12 registers each) are on their way from LDS.
+// Fragments of NN unit tiles, group g + stride j for tile j.
 template <int NN>
 struct Frags {
   u4t a[NN][T_P];
-  __device__ inline void load(const u4t* w, int g, int lane) {
+  __device__ inline void load(const u4t* w, int g, int stride, int lane) {
 #pragma unroll
     for (int j = 0; j < NN; ++j)
 #pragma unroll
-      for (int s = 0; s < T_P; ++s) a[j][s] = w[((g + j) * T_P + s) * 64 + lane];
+      for (int s = 0; s < T_P; ++s) a[j][s] = w[((g + stride * j) * T_P + s) * 64 + lane];
   }
 };
 
-// acc[j][b] += fragment j x operand x[b] for NN unit tiles and TILES env
-// tiles: the six terms from the smallest to the largest.
+// The five small terms of fragment j x operand x[b], from the smallest up, for NN
+// unit tiles and TILES env tiles.
 template <int NN, int TILES>
-__device__ inline void tile_products(const Frags<NN>& f, const u4t (&x)[TILES][T_P],
-                                     f4t (&acc)[NN][TILES]) {
-  constexpr int WP[6] = {2, 0, 1, 1, 0, 0}, XP[6] = {0, 2, 1, 0, 1, 0};
+__device__ inline void small_terms(const Frags<NN>& f, const u4t (&x)[TILES][T_P],
+                                   f4t (&acc)[NN][TILES]) {
+  constexpr int WP[5] = {2, 0, 1, 1, 0}, XP[5] = {0, 2, 1, 0, 1};
 #pragma unroll
-  for (int k = 0; k < 6; ++k)
+  for (int k = 0; k < 5; ++k)
 #pragma unroll
     for (int j = 0; j < NN; ++j)
 #pragma unroll
       for (int b = 0; b < TILES; ++b) acc[j][b] = mfma_bf(f.a[j][WP[k]], x[b][XP[k]], acc[j][b]);
+}
+
+// The sum over CH chunks of fragment x operand: the small terms of every chunk,
+// then the leading products.  frag(c): chunk c's fragments; x[c]: its operands.
+template <int CH, int NN, int TILES, typename F>
+__device__ inline void split_sum(F&& frag, const u4t (&x)[CH][TILES][T_P],
+                                 f4t (&acc)[NN][TILES]) {
+  u4t lead[CH][NN];
+#pragma unroll
+  for (int j = 0; j < NN; ++j)
+#pragma unroll
+    for (int b = 0; b < TILES; ++b) acc[j][b] = f4t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const Frags<NN> f = frag(c);
+    small_terms<NN, TILES>(f, x[c], acc);
+#pragma unroll
+    for (int j = 0; j < NN; ++j) lead[c][j] = f.a[j][0];
+  }
+#pragma unroll
+  for (int c = 0; c < CH; ++c)
+#pragma unroll
+    for (int j = 0; j < NN; ++j)
+#pragma unroll
+      for (int b = 0; b < TILES; ++b) acc[j][b] = mfma_bf(lead[c][j], x[c][b][0], acc[j][b]);
 }
 
 // Unit tiles taken together: enough independent sums (NN x TILES >= 2) for the
@@ -164,21 +212,41 @@ __device__ inline void tile_products(const Frags<NN>& f, const u4t (&x)[TILES][T
 template <int TILES>
 constexpr int T_NN = TILES == 1 ? 2 : 1;
 
-// The four unit tiles of the chunk whose fragments start at group g (28 of
-// them, in the order of a step, then the next step's first).  next: the
-// fragments read ahead.
+// The fragments of a step, read from LDS in its order, one read ahead: while
+// the products of NN unit tiles run, the next ones' fragments (12 registers
+// each) are on their way.
 template <int TILES>
-__device__ inline void unit_products(const u4t* w, int g, int lane, const u4t (&x)[TILES][T_P],
-                                     f4t (&acc)[4][TILES], Frags<T_NN<TILES>>& next) {
-  constexpr int NN = T_NN<TILES>;
-#pragma unroll
-  for (int n = 0; n < 4; n += NN) {
-    const Frags<NN> cur = next;
-    next.load(w, g + n + NN < T_G ? g + n + NN : 0, lane);
-    __builtin_amdgcn_sched_barrier(0);
-    tile_products<NN, TILES>(cur, x, reinterpret_cast<f4t(&)[NN][TILES]>(acc[n]));
+struct FragPipe {
+  static constexpr int NN = T_NN<TILES>;
+  const u4t* w;
+  int lane;
+  Frags<NN> next;
+  // read i of the step (28 / NN of them): NN = 1 every group in turn; NN = 2 the
+  // history chunks of tiles 0, 1, of tiles 2, 3, the state chunks, layer 2
+  __device__ inline void read(int i) {
+    if constexpr (NN == 1) {
+      next.load(w, i % T_G, 0, lane);
+    } else {
+      i %= T_G / 2;
+      const int g = i < 8 ? 8 * (i >> 2) + (i & 3)
+                    : i < 10 ? T_GS + 2 * (i - 8)
+                             : T_G2 + 4 * ((i - 10) >> 1) + ((i - 10) & 1);
+      next.load(w, g, i < 8 ? 4 : i < 10 ? 1 : 2, lane);
+    }
   }
-}
+  __device__ inline void start(const float* lds) {
+    w = reinterpret_cast<const u4t*>(lds);
+    lane = threadIdx.x & 63;
+    read(0);
+  }
+  // fragments of read i; the one after it is issued
+  __device__ inline Frags<NN> take(int i) {
+    const Frags<NN> f = next;
+    read(i + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    return f;
+  }
+};
 
 // Operand of layer-2 chunk m from two layer-1 result tiles (ReLU applied).
 __device__ inline void hidden_operand(const f4t& lo, const f4t& hi, u4t (&x)[T_P]) {
@@ -192,12 +260,13 @@ __device__ inline void hidden_operand(const f4t& lo, const f4t& hi, u4t (&x)[T_P
   }
 }
 
-// State operand (chunk 4) of one tile from its five features.
+// State operand (chunk 4) of one tile from its five features, with the constant
+// one of the bias.
 __device__ inline void state_operand(const float F[5], u4t (&x)[T_P]) {
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     uint32_t p[T_P];
-    split_pair(F[2 * q], q < 2 ? F[2 * q + 1] : 0.0f, p);
+    split_pair(F[2 * q], q < 2 ? F[2 * q + 1] : 1.0f, p);
 #pragma unroll
     for (int s = 0; s < T_P; ++s) x[s][q] = p[s];
   }
@@ -314,22 +383,19 @@ __device__ inline void tile_features(const DevCfg& c, const SetPoint& sp, uint32
 // (ReLU applied): z3 of the lane's own env in every lane.  Each lane group
 // ends with the partial sum over its units; swapping 32 lanes and adding,
 // then 16 lanes and adding, completes them ((0 + 2) + (1 + 3)).
+// w3[n]: weights of units 16 n + 4 lg .. + 3 for output lane & 3; b3: the bias in
+// lane group 0, zero in the others.
 template <int TILES>
-__device__ inline void tile_layer3(const float* w3, const float* b3p, const f4t (&h2)[4][TILES],
+__device__ inline void tile_layer3(const f4t w3[4], const f4t& b3, const f4t (&h2)[4][TILES],
                                    float z3[NA]) {
-  const int lane = threadIdx.x & 63, lg = lane >> 4;
-  f4t b3;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) b3[r] = lg == 0 ? b3p[r] : 0.0f;
   f4t acc[TILES];
 #pragma unroll
   for (int n = 0; n < 4; ++n) {
-    const f4t w = *reinterpret_cast<const f4t*>(&w3[(lane & 3) * T_W3_LD + 16 * n + 4 * lg]);
 #pragma unroll
     for (int v = 0; v < 4; ++v)
 #pragma unroll
       for (int b = 0; b < TILES; ++b)
-        acc[b] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[v], h2[n][b][v],
+        acc[b] = __builtin_amdgcn_mfma_f32_4x4x1f32(w3[n][v], h2[n][b][v],
                                                     (n == 0 && v == 0) ? b3 : acc[b], 0, 0, 0);
   }
 #pragma unroll
@@ -345,6 +411,19 @@ __device__ inline void tile_layer3(const float* w3, const float* b3p, const f4t 
     z3[o] = __uint_as_float(q[0]) + __uint_as_float(q[1]);
   }
 }
+
+// Layer 3's operands from LDS (rows of pitch T_W3_LD).
+struct Layer3 {
+  f4t w[4], b;
+  __device__ inline void load(const float* w3, const float* b3) {
+    const int lane = threadIdx.x & 63, lg = lane >> 4;
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+      w[n] = *reinterpret_cast<const f4t*>(&w3[(lane & 3) * T_W3_LD + 16 * n + 4 * lg]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) b[r] = lg == 0 ? b3[r] : 0.0f;
+  }
+};
 
 template <int NN, int TILES>
 __device__ inline void relu_tiles(f4t (&a)[NN][TILES]) {
@@ -370,21 +449,22 @@ struct TileHist {
     for (int s = 0; s < T_P; ++s) h[b][s][q >> 2][q & 3] = p[s];
   }
   // One slot older: every slot moves down by one, p[b] (the parts of a value
-  // in the low halves) becomes slot 31.  Words of chunk c only; chunks in
-  // ascending order.
-  __device__ inline void push_chunk(int c, const uint32_t (&p)[TILES][T_P]) {
+  // in the low halves) becomes slot 31.
+  __device__ inline void push(const uint32_t (&p)[TILES][T_P]) {
 #pragma unroll
     for (int b = 0; b < TILES; ++b)
 #pragma unroll
-      for (int s = 0; s < T_P; ++s) {
-        u4t v = h[b][s][c];
-        const uint32_t next = c < 3 ? (uint32_t)h[b][s][c < 3 ? c + 1 : 3][0] : p[b][s];
-        v[0] = __builtin_amdgcn_alignbit(v[1], v[0], 16);
-        v[1] = __builtin_amdgcn_alignbit(v[2], v[1], 16);
-        v[2] = __builtin_amdgcn_alignbit(v[3], v[2], 16);
-        v[3] = __builtin_amdgcn_alignbit(next, v[3], 16);
-        h[b][s][c] = v;
-      }
+      for (int s = 0; s < T_P; ++s)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          u4t v = h[b][s][c];
+          const uint32_t next = c < 3 ? (uint32_t)h[b][s][c < 3 ? c + 1 : 3][0] : p[b][s];
+          v[0] = __builtin_amdgcn_alignbit(v[1], v[0], 16);
+          v[1] = __builtin_amdgcn_alignbit(v[2], v[1], 16);
+          v[2] = __builtin_amdgcn_alignbit(v[3], v[2], 16);
+          v[3] = __builtin_amdgcn_alignbit(next, v[3], 16);
+          h[b][s][c] = v;
+        }
   }
   // where on[b]: every slot of the lane's env in tile b becomes v[b]
   __device__ inline void fill(const bool on[TILES], const float v[TILES]) {
@@ -412,77 +492,75 @@ struct TileHist {
   }
 };
 
-// Layer 1's bias and history products.  They need the actions only, so a step's
-// share is evaluated while the step before integrates its dynamics: the
-// matrix products and the vector instructions of one wave overlap.
+// Layer 1's history sums of unit tiles n0 .. n0 + NN - 1.  They need the actions
+// only, so a step's share is evaluated while the step before integrates its
+// dynamics: the matrix products and the vector instructions of one wave
+// overlap.
 template <int TILES>
-__device__ inline void tile_bias1(const float* lds, f4t (&a1)[4][TILES]) {
-  const int lg = (threadIdx.x & 63) >> 4;
+__device__ inline void tile_history(FragPipe<TILES>& fp, const TileHist<TILES>& H, int n0,
+                                    f4t (&a1)[4][TILES]) {
+  constexpr int NN = T_NN<TILES>;
+  u4t x[4][TILES][T_P];
 #pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    const f4t b1 = *reinterpret_cast<const f4t*>(&lds[T_B1 + 16 * n + 4 * lg]);
+  for (int c = 0; c < 4; ++c)
 #pragma unroll
-    for (int b = 0; b < TILES; ++b) a1[n][b] = b1;
-  }
-}
-template <int TILES>
-__device__ inline void tile_history_chunk(const float* lds, const TileHist<TILES>& H, int c,
-                                          f4t (&a1)[4][TILES], Frags<T_NN<TILES>>& next) {
-  u4t x[TILES][T_P];
+    for (int b = 0; b < TILES; ++b)
 #pragma unroll
-  for (int b = 0; b < TILES; ++b)
-#pragma unroll
-    for (int s = 0; s < T_P; ++s) x[b][s] = H.h[b][s][c];
-  unit_products<TILES>(reinterpret_cast<const u4t*>(lds), 4 * c, threadIdx.x & 63, x, a1, next);
-}
-template <int TILES>
-__device__ inline void tile_history(const float* lds, const TileHist<TILES>& H,
-                                    f4t (&a1)[4][TILES], Frags<T_NN<TILES>>& next) {
-  tile_bias1<TILES>(lds, a1);
-  next.load(reinterpret_cast<const u4t*>(lds), 0, threadIdx.x & 63);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    tile_history_chunk<TILES>(lds, H, c, a1, next);
-    __builtin_amdgcn_sched_barrier(0);
-  }
+      for (int s = 0; s < T_P; ++s) x[c][b][s] = H.h[b][s][c];
+  split_sum<4, NN, TILES>([&](int c) { return fp.take(4 * (n0 / NN) + c); }, x,
+                          reinterpret_cast<f4t(&)[NN][TILES]>(a1[n0]));
 }
 
 // The rest of the actor for the wave's tiles: z3 (pre-tanh) of the lane's own
-// env in every lane.  a1: layer 1's bias and history products (consumed); F:
-// the state features 4 e + lg of each tile's env.  rec takes the layer results
-// before the ReLU and the ReLU masks (the record of taped rollouts).
+// env in every lane.  a1: layer 1's history sums (consumed); F: the state
+// features 4 e + lg of each tile's env.  rec takes the layer results before the
+// ReLU and the ReLU masks (the record of taped rollouts).
 template <int TILES, typename Rec>
-__device__ inline void tile_actor(const float* lds, f4t (&a1)[4][TILES],
-                                  const float (&F)[TILES][5], float z3[NA], Rec&& rec,
-                                  Frags<T_NN<TILES>>& next) {
-  const int lane = threadIdx.x & 63, lg = lane >> 4;
-  const u4t* w = reinterpret_cast<const u4t*>(lds);
+__device__ inline void tile_actor(const float* lds, FragPipe<TILES>& fp, f4t (&a1)[4][TILES],
+                                  const float (&F)[TILES][5], float z3[NA], Rec&& rec) {
+  constexpr int NN = T_NN<TILES>;
+  const int lg = (threadIdx.x & 63) >> 4;
   {
-    u4t x[TILES][T_P];
+    u4t x[1][TILES][T_P];
 #pragma unroll
-    for (int b = 0; b < TILES; ++b) state_operand(F[b], x[b]);
-    unit_products<TILES>(w, 16, lane, x, a1, next);
-  }
-  f4t a2[4][TILES];
+    for (int b = 0; b < TILES; ++b) state_operand(F[b], x[0][b]);
 #pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    const f4t b2 = *reinterpret_cast<const f4t*>(&lds[T_B2 + 16 * n + 4 * lg]);
+    for (int n = 0; n < 4; n += NN) {
+      f4t as[NN][TILES];
+      split_sum<1, NN, TILES>([&](int) { return fp.take((T_GS + n) / NN); }, x, as);
 #pragma unroll
-    for (int b = 0; b < TILES; ++b) a2[n][b] = b2;
+      for (int j = 0; j < NN; ++j)
+#pragma unroll
+        for (int b = 0; b < TILES; ++b) a1[n + j][b] += as[j][b];
+    }
   }
   rec.layer1(a1);
   relu_tiles(a1);
+  f4t a2[4][TILES];
+  {
+    u4t x[2][TILES][T_P];
 #pragma unroll
-  for (int m = 0; m < 2; ++m) {
-    u4t x[TILES][T_P];
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int b = 0; b < TILES; ++b) hidden_operand(a1[2 * m][b], a1[2 * m + 1][b], x[b]);
-    unit_products<TILES>(w, T_G1 + 4 * m, lane, x, a2, next);
+      for (int b = 0; b < TILES; ++b) hidden_operand(a1[2 * m][b], a1[2 * m + 1][b], x[m][b]);
+#pragma unroll
+    for (int n = 0; n < 4; n += NN) {
+      split_sum<2, NN, TILES>([&](int m) { return fp.take((T_G2 + 2 * n) / NN + m); }, x,
+                              reinterpret_cast<f4t(&)[NN][TILES]>(a2[n]));
+#pragma unroll
+      for (int j = 0; j < NN; ++j) {
+        const f4t b2 = *reinterpret_cast<const f4t*>(&lds[T_B2 + 16 * (n + j) + 4 * lg]);
+#pragma unroll
+        for (int b = 0; b < TILES; ++b) a2[n + j][b] += b2;
+      }
+    }
   }
   rec.layer2(a2);
-  relu_tiles(a2);
   rec.masks(a1, a2);
-  tile_layer3<TILES>(lds + T_W3, lds + T_B3, a2, z3);
+  relu_tiles(a2);
+  Layer3 l3;
+  l3.load(lds + T_W3, lds + T_B3);
+  tile_layer3<TILES>(l3.w, l3.b, a2, z3);
 }
 
 // No record.

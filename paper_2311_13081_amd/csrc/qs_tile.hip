@@ -157,9 +157,14 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
   const uint32_t osub = 4u * (uint32_t)(sub * N + e);  // row sub of the env
   if (states && t_base == 0 && active) store_rows<SUB, NS>(states, N, osub, sub, x);
 
-  f4t a1[4][TILES];  // layer 1 of the coming step: bias and history products
-  Frags<T_NN<TILES>> next;
-  tile_history<TILES>(lds, H, a1, next);
+  f4t a1[4][TILES];  // layer 1's history sums of the coming step
+  FragPipe<TILES> fp;
+  const auto history = [&]() {
+    fp.start(lds);
+#pragma unroll
+    for (int n = 0; n < 4; n += T_NN<TILES>) tile_history<TILES>(fp, H, n, a1);
+  };
+  history();
   for (int t = 0; t < T; ++t) {
     // keeps the weight reads inside the step (hoisted out of the time loop
     // they would pin the registers)
@@ -202,9 +207,9 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
         sr.zoff[tl] = opaque((uint32_t)(rb_at(env0 + 16 * tl + li, REC_F) + 4 * lg * RB));
         sr.mask[tl] = 0u;
       }
-      tile_actor<TILES>(lds, a1, F, z3, sr, next);
+      tile_actor<TILES>(lds, fp, a1, F, z3, sr);
     } else {
-      tile_actor<TILES>(lds, a1, F, z3, NoRec{}, next);
+      tile_actor<TILES>(lds, fp, a1, F, z3, NoRec{});
     }
     __builtin_amdgcn_s_setprio(0);
     float a[NA], at[TILES];
@@ -244,16 +249,15 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     uint32_t ap[TILES][T_P];
 #pragma unroll
     for (int tl = 0; tl < TILES; ++tl) split_pair(at[tl], 0.0f, ap[tl]);
-    tile_bias1<TILES>(lds, a1);
+    H.push(ap);
     float u[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) u[i] = action_to_rpm(c, a[i]);
-    // ahead of each right-hand side a quarter of the history products of the
-    // next step
+    // ahead of each (two tiles) or every other (one tile) right-hand side the
+    // history sums of one or two unit tiles for the next step
     rk4_step<float, EXTRAS>(B, c.arm, c.km, c.g, c.dt, renorm, x, u, [&](int k) {
       __builtin_amdgcn_sched_barrier(0);
-      H.push_chunk(k, ap);
-      tile_history_chunk<TILES>(lds, H, k, a1, next);
+      if (k % T_NN<TILES> == 0) tile_history<TILES>(fp, H, k, a1);
     });
     __builtin_amdgcn_sched_barrier(0);
     const float r = reward(c, x, a);
@@ -267,7 +271,7 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
 #pragma unroll
       for (int tl = 0; tl < TILES; ++tl) on[tl] = (any >> (16 * tl + li)) & 1u;
       H.fill(on, aht);
-      tile_history<TILES>(lds, H, a1, next);
+      history();
       if (rst) {
         ++ep;
         t_ep = 0;
