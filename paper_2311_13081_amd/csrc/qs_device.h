@@ -460,6 +460,136 @@ __device__ inline void rk4_step(const Body<R>& B, R arm, R km, R g, R h, bool re
   x[6] *= r;
 }
 
+// ---------------------------------------------------------------------------
+// The same RK4 step in fewer instructions (about 360 against 400), for given
+// actions (the actor's kernels keep rk4_step: this form holds four derivatives
+// at once, which costs them registers).  The velocity enters nothing but the
+// position, whose increment is h v + h^2/6 (k1 + k2 + k3); inertias are folded
+// into the torque arms and the gyroscopic factors.  The rotor speeds are stored
+// to 1e-3 RPM, and open-loop flights integrate that rounding twice: their
+// arithmetic is rk4_step's to the bit.  Every product that meets a sum is an
+// explicit fused multiply-add, so the kernels round alike.
+// ---------------------------------------------------------------------------
+struct Quad {
+  float inv_m, c0, c1, c2;
+  float ax, ay, az;      // torque arms over inertia
+  float kx, ky, kz;      // gyroscopic factors (Jz - Jy) / Jx, ...
+  float inv_Tm;
+  float inv_J[3];
+  float f[3], t[3];      // episode disturbance: force over mass, torque over inertia
+};
+
+__device__ inline Quad make_quad(const DevCfg& c, const float th[NP]) {
+  Quad q;
+  q.inv_m = 1.0f / th[0];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    q.inv_J[i] = 1.0f / th[1 + i];
+    q.f[i] = q.t[i] = 0.0f;
+  }
+  q.c0 = th[4];
+  q.c1 = th[5];
+  q.c2 = th[6];
+  q.ax = c.arm * q.inv_J[0];
+  q.ay = c.arm * q.inv_J[1];
+  q.az = c.km * q.inv_J[2];
+  q.kx = (th[3] - th[2]) * q.inv_J[0];
+  q.ky = (th[1] - th[3]) * q.inv_J[1];
+  q.kz = (th[2] - th[1]) * q.inv_J[2];
+  q.inv_Tm = 1.0f / th[7];
+  return q;
+}
+
+// Sets the episode disturbance d = {f_r, tau_r}.
+__device__ inline void set_disturbance(Quad& q, const float d[6]) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    q.f[i] = d[i] * q.inv_m;
+    q.t[i] = d[3 + i] * q.inv_J[i];
+  }
+}
+
+// Right-hand side without the trivial parts: k = {dq (4), dv (3), dw (3)} at
+// attitude q, body rates o and rotor speeds w.
+template <bool DIST>
+__device__ __forceinline__ void quad_rhs(const Quad& B, float g, const float q[4],
+                                         const float o[3], const float w[4], float k[10]) {
+  float T[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) T[i] = fmaf(w[i], fmaf(B.c2, w[i], B.c1), B.c0);
+  const float s02 = T[0] + T[2], s13 = T[1] + T[3], d02 = T[0] - T[2], d13 = T[1] - T[3];
+  const float F = s02 + s13;
+  const float hx = 0.5f * o[0], hy = 0.5f * o[1], hz = 0.5f * o[2];
+  k[0] = fmaf(-q[1], hx, fmaf(-q[2], hy, -(q[3] * hz)));
+  k[1] = fmaf(q[0], hx, fmaf(q[2], hz, -(q[3] * hy)));
+  k[2] = fmaf(q[0], hy, fmaf(q[3], hx, -(q[1] * hz)));
+  k[3] = fmaf(q[0], hz, fmaf(q[1], hy, -(q[2] * hx)));
+  const float n2 = fmaf(q[0], q[0], fmaf(q[1], q[1], fmaf(q[2], q[2], q[3] * q[3])));
+  const float s = (F * B.inv_m) * recip_r(n2), s2 = s + s;
+  const float px = fmaf(q[1], q[3], q[0] * q[2]), py = fmaf(q[2], q[3], -(q[0] * q[1]));
+  const float pz = fmaf(-2.0f, fmaf(q[1], q[1], q[2] * q[2]), n2);
+  k[4] = DIST ? fmaf(px, s2, B.f[0]) : px * s2;
+  k[5] = DIST ? fmaf(py, s2, B.f[1]) : py * s2;
+  k[6] = fmaf(pz, s, DIST ? B.f[2] - g : -g);
+  // J w' = tau + tau_r - w x (J w)
+  const float tx = -(d02 + d13), ty = d13 - d02, tz = s13 - s02;
+  k[7] = fmaf(-(B.kx * o[1]), o[2], DIST ? fmaf(B.ax, tx, B.t[0]) : B.ax * tx);
+  k[8] = fmaf(-(B.ky * o[2]), o[0], DIST ? fmaf(B.ay, ty, B.t[1]) : B.ay * ty);
+  k[9] = fmaf(-(B.kz * o[0]), o[1], DIST ? fmaf(B.az, tz, B.t[2]) : B.az * tz);
+}
+
+// One step under normalised actions a.
+template <bool DIST>
+__device__ inline void quad_step(const Quad& B, const DevCfg& c, bool renorm, float x[NS],
+                                 const float a[NA]) {
+  const float h = c.dt, hh = 0.5f * h, h6 = h / 6.0f;
+  float k1[10], k2[10], k3[10], k4[10], q[4], o[3], w[4], u[4], kw[4], aw[4];
+  const auto lag = [&](const float* ws) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) kw[i] = (u[i] - ws[i]) * B.inv_Tm;
+  };
+  const auto stage = [&](float hs, const float* k) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q[i] = fmaf(hs, k[i], x[3 + i]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) o[i] = fmaf(hs, k[7 + i], x[10 + i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = fmaf(hs, kw[i], x[13 + i]);
+  };
+#pragma unroll
+  for (int i = 0; i < 4; ++i) u[i] = fmaf(a[i] + 1.0f, c.rpm_half_range, c.rpm_min);
+  quad_rhs<DIST>(B, c.g, x + 3, x + 10, x + 13, k1);
+  lag(x + 13);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) aw[i] = kw[i];
+  stage(hh, k1);
+  quad_rhs<DIST>(B, c.g, q, o, w, k2);
+  lag(w);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) aw[i] = fmaf(2.0f, kw[i], aw[i]);
+  stage(hh, k2);
+  quad_rhs<DIST>(B, c.g, q, o, w, k3);
+  lag(w);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) aw[i] = fmaf(2.0f, kw[i], aw[i]);
+  stage(h, k3);
+  quad_rhs<DIST>(B, c.g, q, o, w, k4);
+  lag(w);
+#pragma unroll
+  for (int i = 0; i < 10; ++i) {
+    const float s23 = k2[i] + k3[i], sum = fmaf(2.0f, s23, k1[i]) + k4[i];
+    // rows 3 + i: q, v, w
+    if (i >= 4 && i < 7) x[i - 4] += fmaf(h * h6, k1[i] + s23, h * x[3 + i]);
+    x[3 + i] = fmaf(h6, sum, x[3 + i]);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) x[13 + i] = fmaf(h6, aw[i] + kw[i], x[13 + i]);
+  const float rq = rsqrt_r(fmaf(x[3], x[3], fmaf(x[4], x[4], fmaf(x[5], x[5], x[6] * x[6]))));
+  const float r = renorm ? rq : 1.0f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) x[3 + i] *= r;
+}
+
 // Row-major rotation matrix of q/|q| (Hamilton, body to world).
 __device__ inline void rotmat(const float q[4], float Rm[9]) {
   const float n2 = q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3];

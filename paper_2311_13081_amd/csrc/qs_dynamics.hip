@@ -23,7 +23,7 @@ k_dyn_rollout(DevCfg c, SimBufs b, const float* __restrict__ act, int a_tstride,
   float th[NP];
 #pragma unroll
   for (int i = 0; i < NP; ++i) th[i] = b.theta[(size_t)i * N + e];
-  Body<float> B = make_body<float>(th);
+  Quad B = make_quad(c, th);
   const bool renorm = (c.flags & F_RENORM_Q) != 0;
   float x[NS];
 #pragma unroll
@@ -57,17 +57,14 @@ k_dyn_rollout(DevCfg c, SimBufs b, const float* __restrict__ act, int a_tstride,
     // per-step opaque env index: keeps the 64-bit output addresses from being
     // hoisted out of the loop and held in registers
     const uint32_t eo = opaque((uint32_t)e);
-    float a[NA], u[NA];
+    float a[NA];
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      a[i] = an[i];
-      u[i] = action_to_rpm(c, a[i]);
-    }
+    for (int i = 0; i < NA; ++i) a[i] = an[i];
     if (!HELD && t + 1 < T) {
 #pragma unroll
       for (int i = 0; i < NA; ++i) an[i] = act[((size_t)(t + 1) * a_tstride + i) * N + eo];
     }
-    rk4_step<float, DIST>(B, c.arm, c.km, c.g, c.dt, renorm, x, u);
+    quad_step<DIST>(B, c, renorm, x, a);
     const float r = reward(c, x, a);
     ++t_ep;
     const uint32_t d = episode_end(c, x, t_ep);

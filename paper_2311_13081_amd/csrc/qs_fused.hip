@@ -5,6 +5,8 @@
 // Layout: struct-of-arrays in HBM ([K][N]) so every global access of a wave is
 // a contiguous 256-byte segment; actor weights are staged in LDS once per
 // workgroup.
+#include <type_traits>
+
 #include "qs_actor.h"
 #include "qs_forward.h"
 
@@ -52,7 +54,12 @@ k_fused(DevCfg c, SimBufs b, const float* __restrict__ W, const float* __restric
   float th[NP];
 #pragma unroll
   for (int i = 0; i < NP; ++i) th[i] = b.theta[i * N + e];
-  Body<float> B = make_body<float>(th);
+  // given actions take the dynamics-only rollout's form of the step
+  std::conditional_t<ACT == ACT_GIVEN, Quad, Body<float>> B;
+  if constexpr (ACT == ACT_GIVEN)
+    B = make_quad(c, th);
+  else
+    B = make_body<float>(th);
   const bool renorm = (c.flags & F_RENORM_Q) != 0;
 
   float x[NS];
@@ -131,10 +138,14 @@ k_fused(DevCfg c, SimBufs b, const float* __restrict__ W, const float* __restric
 #pragma unroll
       for (int i = 0; i < NA; ++i) a[i] = tanh_act(z3[i]);
     }
-    float u[NA];
+    if constexpr (ACT == ACT_GIVEN) {
+      quad_step<EXTRAS>(B, c, renorm, x, a);
+    } else {
+      float u[NA];
 #pragma unroll
-    for (int i = 0; i < NA; ++i) u[i] = action_to_rpm(c, a[i]);
-    rk4_step<float, EXTRAS>(B, c.arm, c.km, c.g, c.dt, renorm, x, u);
+      for (int i = 0; i < NA; ++i) u[i] = action_to_rpm(c, a[i]);
+      rk4_step<float, EXTRAS>(B, c.arm, c.km, c.g, c.dt, renorm, x, u);
+    }
     const float r = reward(c, x, a);
     ++t_ep;
     const uint32_t d = episode_end(c, x, t_ep);
