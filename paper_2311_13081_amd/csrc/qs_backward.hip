@@ -2,7 +2,7 @@
 //
 // The taped forward stored checkpoints (state, history) every K steps.  The
 // backward walks the segments last to first; per segment:
-//   1. recompute: the fused MFMA kernel restarts from the checkpoint and
+//   1. recompute: the taped forward's kernel restarts from the checkpoint and
 //      records x_t, a_t, the layer pre-activations z1, z2 and the state
 //      features of o_t per step (the history features are earlier actions);
 //   2. reverse sweep (k_bwd_reverse): four lanes per env, the adjoints of
@@ -17,6 +17,10 @@
 //      input column.
 // Finally k_bwd_reduce adds the workgroup partials in a fixed order, so the
 // result does not depend on scheduling.
+//
+// Fused multiply-adds only where one expression of the source holds the product
+// and the sum, so kernels that promise equal results round alike.
+#pragma clang fp contract(on)
 #include "qs_actor.h"
 #include "qs_backward.h"
 #include "qs_forward.h"
@@ -46,22 +50,23 @@ __global__ void k_bwd_init(int N, const float* __restrict__ dS_T, float* __restr
 // or the split-actor kernel, which compute the same values).  Per lane:
 // the state adjoint (17) and the dynamics VJP, replicated over the 4 quarters
 // of an env; the history adjoint of action component k (32 slots).  The actor
-// VJP runs on 16x16x4 fp32 MFMAs:
-//   dh2 = W3^T dz3: one K=4 MFMA per 16-neuron tile (quarter k supplies
+// VJP runs on matrix cores:
+//   dz2 = W3^T dz3: one K=4 fp32 product per 16-neuron tile (quarter k supplies
 //         dz3[k]);
-//   dh1 = W2^T dz2, do = W1^T dz1: chained through the result registers.
+//   dz1 = W2^T dz2, do = W1^T dz1: bf16 products of split operands (qs_tile.h),
+//         each layer's result registers split into the next one's operands.
 // The rows of W1^T are taken in the forward's observation order, so tile p
 // of do leaves in quarter k exactly the features PHI(4p + r, k): history
 // slot 4p + r - 5, component k (the lane's own history adjoint) or, for
 // chunks 0..4, state features 4c + k, gathered across quarters with 20
-// lane shuffles.
+// lane shuffles.  One wave per SIMD, bound by the serial chain of a step (the
+// stages of the dynamics, then the layers): 16 steps of 16384 envs took 164 us
+// with fp32 products and a branch around each load and store, now 107 (the
+// split form at 1024 envs 100 and 83).
 //
-// LDS (floats):
-//   R_W3 [4][64] = W3;
-//   R_W2P[((n*4 + g)*4 + m)*16 + i][v] = W2[16n + 4g + v][16m + i];
-//   R_W1P[((m*4 + g)*10 + p)*16 + i][v] = W1[16m + 4g + v][PHI(4p + i%4, i/4)] (0 if pad).
-constexpr int R_W3 = 0, R_W2P = R_W3 + NA * NHID, R_W1P = R_W2P + NHID * NHID,
-              R_TOTAL = R_W1P + 10 * 16 * NHID;
+// LDS (floats): R_W3 [4][64] = W3; R_FRAG the transposed layers' fragments
+// (stage_transposed).
+constexpr int R_W3 = 0, R_FRAG = R_W3 + NA * NHID, R_TOTAL = R_FRAG + 4 * RT_FRAGS;
 
 __host__ __device__ constexpr int r_phi(int c, int k) {
   return c < 5 ? (4 * c + k < 18 ? 4 * c + k : -1) : c < 37 ? 18 + 4 * (c - 5) + k : -1;
@@ -69,17 +74,8 @@ __host__ __device__ constexpr int r_phi(int c, int k) {
 
 __device__ inline void stage_reverse(const float* __restrict__ W, float* lds, bool bf16) {
   stage_lds(lds + R_W3, NA * NHID, W, [](int i) { return OFF_W3 + i; }, bf16);
-  stage_lds(lds + R_W2P, NHID * NHID, W, [](int idx) {
-    const int v = idx & 3, i = (idx >> 2) & 15, m = (idx >> 6) & 3, g = (idx >> 8) & 3,
-              n = idx >> 10;
-    return OFF_W2 + (16 * n + 4 * g + v) * NHID + 16 * m + i;
-  }, bf16);
-  stage_lds(lds + R_W1P, 10 * 16 * NHID, W, [](int idx) {
-    const int v = idx & 3, i = (idx >> 2) & 15, rest = idx >> 6;  // rest = (m*4 + g)*10 + p
-    const int p = rest % 10, g = (rest / 10) & 3, m = rest / 40;
-    const int feat = r_phi(4 * p + (i & 3), i >> 2);
-    return feat >= 0 ? OFF_W1 + (16 * m + 4 * g + v) * NO + feat : -1;
-  }, bf16);
+  stage_transposed(W, reinterpret_cast<u4t*>(lds + R_FRAG),
+                   [](int p, int i) { return r_phi(4 * p + (i & 3), i >> 2); }, bf16);
 }
 
 // Inputs of one reverse step: the recorded state and action, this lane's
@@ -90,26 +86,19 @@ struct StepIn {
   uint32_t zm;
 };
 
-__device__ inline void load_step(StepIn& in, const float* __restrict__ rec,
-                                 const float* __restrict__ d_rewards,
-                                 const float* __restrict__ d_states, int tl, int t0, int N, int e,
-                                 int k) {
-  const uint32_t eo = opaque((uint32_t)e);
-  const uint32_t roff = opaque((uint32_t)rb_at(e, REC_F));
-  const uint32_t koff = opaque((uint32_t)(rb_at(e, REC_F) + k * RB));
-  const int t = t0 + tl;
-  const float* rt = rec + rec_step(tl, N);
+// vx, vk: the lane's byte offsets of its env's column and of row k of it in a
+// step's record, sr the step's; ve = 4 e.
+__device__ __forceinline__ void load_step(StepIn& in, __amdgpu_buffer_rsrc_t rrec, uint32_t sr,
+                                          uint32_t vx, uint32_t vk, uint32_t ve,
+                                          const float* __restrict__ d_rewards,
+                                          const float* __restrict__ d_states, int t, int N) {
 #pragma unroll
-  for (int i = 0; i < NS; ++i) in.x[i] = rt[(size_t)(REC_X + i) * RB + roff];
+  for (int i = 0; i < NS; ++i) in.x[i] = bld1(rrec, vx, sr + 4u * (REC_X + i) * RB);
 #pragma unroll
-  for (int i = 0; i < NA; ++i) in.a[i] = rt[(size_t)(REC_A + i) * RB + roff];
-  in.zm = __float_as_uint(rt[(size_t)REC_M * RB + koff]);
-  in.dR = d_rewards ? d_rewards[(size_t)t * N + eo] : 1.0f;
-#pragma unroll
-  for (int i = 0; i < NS; ++i)
-    in.dS[i] = d_states ? d_states[((size_t)t * NS + i) * N + eo] : 0.0f;
+  for (int i = 0; i < NA; ++i) in.a[i] = bld1(rrec, vx, sr + 4u * (REC_A + i) * RB);
+  in.zm = __float_as_uint(bld1(rrec, vk, sr + 4u * REC_M * RB));
+  load_cotangents(in.dS, in.dR, d_rewards, d_states, t, N, ve);
 }
-
 
 // The observation's share of the adjoints, from do (dob: tile p, register r
 // of quarter k = the cotangent of feature PHI(4p + r, k)): shifts the
@@ -147,9 +136,10 @@ __device__ __forceinline__ void reverse_observation(const float dob[40], const f
   for (int i = 0; i < NS; ++i) ls[i] = gx[i] + dS[i];
 }
 
-// Exchange space of the split sweep, after the staged weights: dz2 and dz1
-// tiles [4][64] and do tiles [10][64] (f4 each).
-constexpr int R_XCH = (4 + 4 + 10) * 64 * 4;
+// Exchange space of the split sweep, after the staged weights: dz2 and dz1 as
+// operands [part][chunk][64] (16 bytes, a tile filling half of each) and do tiles
+// [10][64] (f4).
+constexpr int R_XCH = (2 * T_P + 2 * T_P + 10) * 64 * 4;
 // Batches up to this size run the split sweep (four times the waves; the
 // quarter-lane sweep leaves most SIMDs idle there).
 constexpr int REVERSE_SPLIT_MAX_ENVS = 4096;
@@ -183,20 +173,35 @@ k_bwd_reverse(DevCfg c, const float* __restrict__ theta, const float* __restrict
   const int env = env0 + j;
   const bool active = env < N;
   const int e = active ? env : env0;
-  f4* xd2 = reinterpret_cast<f4*>(lds + R_TOTAL);
-  f4* xd1 = xd2 + 4 * 64;
-  f4* xdo = xd1 + 4 * 64;
+  const u4t* frag = reinterpret_cast<const u4t*>(lds + R_FRAG);
+  u4t(*xd2)[2][64] = reinterpret_cast<u4t(*)[2][64]>(lds + R_TOTAL);
+  u4t(*xd1)[2][64] = xd2 + T_P;
+  f4t* xdo = reinterpret_cast<f4t*>(xd1 + T_P);
+  // this wave's tile of a layer as half of the next layer's operands, and the
+  // whole operands after the barrier
+  const auto put = [&](u4t(*xc)[2][64], const f4t& d) {
+    uint32_t p[T_P], q[T_P];
+    split_pair(d[0], d[1], p);
+    split_pair(d[2], d[3], q);
+#pragma unroll
+    for (int s = 0; s < T_P; ++s)
+      *(reinterpret_cast<uint2*>(&xc[s][w >> 1][lane]) + (w & 1)) = uint2{p[s], q[s]};
+  };
+  const auto get = [&](u4t(*xc)[2][64], u4t(&x)[2][1][T_P]) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int s = 0; s < T_P; ++s) x[m][0][s] = xc[s][m][lane];
+  };
 
   float th[NP];
 #pragma unroll
   for (int i = 0; i < NP; ++i) th[i] = theta[(size_t)i * N + e];
-  Body<float> B = make_body<float>(th);
-  {
-    // the episode disturbance of the segment (no resets in a taped rollout)
-    float d[6];
-    disturbance(c, (uint32_t)e, (uint32_t)__float_as_int(ck[(size_t)CK_EP * N + e]), d);
-    set_disturbance(B, d);
-  }
+  // the episode disturbance of the segment (no resets in a taped rollout)
+  float dist[6];
+  disturbance(c, (uint32_t)e, (uint32_t)__float_as_int(ck[(size_t)CK_EP * N + e]), dist);
+  const Quad B = make_rev_quad(c, th, dist);
+  const RevStep rs = make_rev_step(c);
   const bool renorm = (c.flags & F_RENORM_Q) != 0;
 
   float ls[NS], lH[NH], gth[NP];
@@ -209,15 +214,25 @@ k_bwd_reverse(DevCfg c, const float* __restrict__ theta, const float* __restrict
 
   // The per-step inputs (record rows and cotangents) of step tl - 1 are
   // loaded while step tl is processed, so their latency hides behind it.
+  // Byte offsets.  Lanes of envs >= N store zeros into their slots of the padded
+  // block, so no store is under a branch.
+  const uint32_t rbp = (uint32_t)rb_pad(N);
+  const __amdgpu_buffer_rsrc_t rrec = span_rsrc(rec, 4u * (uint32_t)rec_floats(n, N));
+  const __amdgpu_buffer_rsrc_t rdz = span_rsrc(dz, 4u * (uint32_t)n * DZ_F * rbp);
+  const uint32_t vx = 4u * (uint32_t)rb_at(e, REC_F), vk = vx + 4u * (uint32_t)(k * RB);
+  const uint32_t ve = 4u * (uint32_t)e, vz = 4u * (uint32_t)rb_at(env, DZ_F);
+  const uint32_t vz1 = vz + 4u * (uint32_t)(k * RB), vz4 = vz + 4u * (uint32_t)(4 * k * RB);
   StepIn cur, nxt;
-  load_step(cur, rec, d_rewards, d_states, n - 1, t0, N, e, k);
+  load_step(cur, rrec, 4u * (uint32_t)(n - 1) * (REC_F * rbp), vx, vk, ve, d_rewards, d_states,
+            t0 + n - 1, N);
+  drain_loads();
   for (int tl = n - 1; tl >= 0; --tl) {
     __asm__ volatile("" ::: "memory");
-    load_step(nxt, rec, d_rewards, d_states, tl > 0 ? tl - 1 : 0, t0, N, e, k);
-    // blocked cotangent rows of this env: row k and row 4k
-    const uint32_t koff = opaque((uint32_t)(rb_at(e, DZ_F) + k * RB));
-    const uint32_t zoff = opaque((uint32_t)(rb_at(e, DZ_F) + 4 * k * RB));
-    float* dzt = dz + (size_t)tl * DZ_F * rb_pad(N);
+    const int tp = tl > 0 ? tl - 1 : 0;
+    load_step(nxt, rrec, 4u * (uint32_t)tp * (REC_F * rbp), vx, vk, ve, d_rewards, d_states,
+              t0 + tp, N);
+    const uint32_t sz = 4u * (uint32_t)tl * (DZ_F * rbp);  // the step's cotangents
+    const uint32_t zm = active ? cur.zm : 0u;
 
     float gx[NS], ga[NA];
     // newest history slot: component i lives in quarter i of the same env
@@ -226,14 +241,15 @@ k_bwd_reverse(DevCfg c, const float* __restrict__ theta, const float* __restrict
     for (int i = 0; i < NA; ++i)
       hn[i] = __int_as_float(
           __builtin_amdgcn_ds_bpermute((j + 16 * i) << 2, __float_as_int(lH[NH - 1])));
-    reverse_dynamics(c, B, th, renorm, cur.x, cur.a, cur.dR, ls, hn, gx, ga, gth);
+    reverse_dynamics(c, rs, B, renorm, cur.x, cur.a, d_rewards ? cur.dR : 1.0f, ls, hn, gx, ga, gth);
 
     // --- actor VJP on matrix cores --------------------------------------------
     float d3[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) d3[i] = ga[i] * (1.0f - cur.a[i] * cur.a[i]);
-    const float d3k = k == 0 ? d3[0] : k == 1 ? d3[1] : k == 2 ? d3[2] : d3[3];
-    if (active && w == 0) dzt[(size_t)(2 * NHID) * RB + koff] = d3k;
+    const float d3e = k == 0 ? d3[0] : k == 1 ? d3[1] : k == 2 ? d3[2] : d3[3];
+    const float d3k = active ? d3e : 0.0f;
+    if (!SPLIT || w == 0) bst1(d3k, rdz, vz1, sz + 4u * (2 * NHID) * RB);
     // do = W1^T dz1 in observation order: tile p, register r of quarter k is
     // the cotangent of feature PHI(4p + r, k)
     float dob[40];
@@ -246,42 +262,35 @@ k_bwd_reverse(DevCfg c, const float* __restrict__ theta, const float* __restrict
                                                       f4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          dz2[q][r] = (cur.zm >> (8 * q + 4 + r)) & 1u ? dz2[q][r] : 0.0f;
-          if (active) dzt[(size_t)(NHID + 16 * q + r) * RB + zoff] = dz2[q][r];
+          dz2[q][r] = (zm >> (8 * q + 4 + r)) & 1u ? dz2[q][r] : 0.0f;
+          bst1(dz2[q][r], rdz, vz4, sz + 4u * (NHID + 16 * q + r) * RB);
         }
       }
       // dz1 = (W2^T dz2) * [z1 > 0]
-      f4 dz1[4];
+      u4t xo[2][1][T_P];
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        f4 accm = f4{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int m = 0; m < 2; ++m) hidden_operand(dz2[2 * m], dz2[2 * m + 1], xo[m][0]);
+      f4t dz1[4][1];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f4 wv = *reinterpret_cast<const f4*>(
-              &lds[R_W2P + (((q * 4 + k) * 4 + mt) * 16 + j) * 4]);
+      for (int mt = 0; mt < 4; mt += 2)
+        transposed_sum<2, 1>(frag, 2 * mt, lane, xo, reinterpret_cast<f4t(&)[2][1]>(dz1[mt]));
 #pragma unroll
-          for (int v = 0; v < 4; ++v)
-            accm = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[v], dz2[q][v], accm, 0, 0, 0);
-        }
+      for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          dz1[mt][r] = (cur.zm >> (8 * mt + r)) & 1u ? accm[r] : 0.0f;
-          if (active) dzt[(size_t)(16 * mt + r) * RB + zoff] = dz1[mt][r];
-        }
-      }
-#pragma unroll
-      for (int p = 0; p < 10; ++p) {
-        f4 accp = f4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-          const f4 wv = *reinterpret_cast<const f4*>(
-              &lds[R_W1P + (((mt * 4 + k) * 10 + p) * 16 + j) * 4]);
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            accp = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[v], dz1[mt][v], accp, 0, 0, 0);
+          dz1[mt][0][r] = (zm >> (8 * mt + r)) & 1u ? dz1[mt][0][r] : 0.0f;
+          bst1(dz1[mt][0][r], rdz, vz4, sz + 4u * (16 * mt + r) * RB);
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) dob[4 * p + r] = accp[r];
+      for (int m = 0; m < 2; ++m) hidden_operand(dz1[2 * m][0], dz1[2 * m + 1][0], xo[m][0]);
+#pragma unroll
+      for (int p = 0; p < 10; p += 2) {
+        f4t o[2][1];
+        transposed_sum<2, 1>(frag, RT_G1 + 2 * p, lane, xo, o);
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) dob[4 * (p + q) + r] = o[q][0][r];
       }
     } else {
       // dz2 tile w
@@ -289,56 +298,38 @@ k_bwd_reverse(DevCfg c, const float* __restrict__ theta, const float* __restrict
                                                    f4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        d2[r] = (cur.zm >> (8 * w + 4 + r)) & 1u ? d2[r] : 0.0f;
-        if (active) dzt[(size_t)(NHID + 16 * w + r) * RB + zoff] = d2[r];
+        d2[r] = (zm >> (8 * w + 4 + r)) & 1u ? d2[r] : 0.0f;
+        bst1(d2[r], rdz, vz4, sz + 4u * (NHID + 16 * w + r) * RB);
       }
-      xd2[w * 64 + lane] = d2;
+      put(xd2, d2);
       __syncthreads();
-      f4 dz2[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) dz2[q] = xd2[q * 64 + lane];
+      u4t xo[2][1][T_P];
+      get(xd2, xo);
       // dz1 tile w
-      f4 accm = f4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f4 wv =
-            *reinterpret_cast<const f4*>(&lds[R_W2P + (((q * 4 + k) * 4 + w) * 16 + j) * 4]);
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          accm = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[v], dz2[q][v], accm, 0, 0, 0);
-      }
-      f4 d1;
+      f4t d1[1][1];
+      transposed_sum<1, 1>(frag, 2 * w, lane, xo, d1);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        d1[r] = (cur.zm >> (8 * w + r)) & 1u ? accm[r] : 0.0f;
-        if (active) dzt[(size_t)(16 * w + r) * RB + zoff] = d1[r];
+        d1[0][0][r] = (zm >> (8 * w + r)) & 1u ? d1[0][0][r] : 0.0f;
+        bst1(d1[0][0][r], rdz, vz4, sz + 4u * (16 * w + r) * RB);
       }
-      xd1[w * 64 + lane] = d1;
+      put(xd1, d1[0][0]);
       __syncthreads();
-      f4 dz1[4];
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) dz1[mt] = xd1[mt * 64 + lane];
+      get(xd1, xo);
       // do tiles w, w + 4, w + 8
 #pragma unroll
       for (int pi = 0; pi < 3; ++pi) {
         const int p = w + 4 * pi;
         if (p < 10) {
-          f4 accp = f4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-          for (int mt = 0; mt < 4; ++mt) {
-            const f4 wv = *reinterpret_cast<const f4*>(
-                &lds[R_W1P + (((mt * 4 + k) * 10 + p) * 16 + j) * 4]);
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-              accp = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[v], dz1[mt][v], accp, 0, 0, 0);
-          }
-          xdo[p * 64 + lane] = accp;
+          f4t o[1][1];
+          transposed_sum<1, 1>(frag, RT_G1 + 2 * p, lane, xo, o);
+          xdo[p * 64 + lane] = o[0][0];
         }
       }
       __syncthreads();
 #pragma unroll
       for (int p = 0; p < 10; ++p) {
-        const f4 v = xdo[p * 64 + lane];
+        const f4t v = xdo[p * 64 + lane];
 #pragma unroll
         for (int r = 0; r < 4; ++r) dob[4 * p + r] = v[r];
       }
@@ -958,9 +949,9 @@ hipError_t bwd_alloc(BwdBufs& bw, int N, int K, int H) {
     if ((e = hipEventCreateWithFlags(&bw.e_rev[i], hipEventDisableTiming)) != hipSuccess) return e;
     if ((e = hipEventCreateWithFlags(&bw.e_dw[i], hipEventDisableTiming)) != hipSuccess) return e;
     if (i >= nseg) continue;
-    // zeroed once: the quarter-lane and split kernels never write the slots
-    // of envs >= N in the last 64-env block, which must then read as finite
-    // (record) and zero (cotangents) in the weight-gradient pass
+    // zeroed once: whole wavefronts past the last env never write their slots
+    // of the last 64-env block, which must read as finite (record) and zero
+    // (cotangents) in the weight-gradient pass
     if ((e = hipMalloc(&bw.seg[i], rec_floats(K, N) * 4)) != hipSuccess) return e;
     if ((e = hipMemset(bw.seg[i], 0, rec_floats(K, N) * 4)) != hipSuccess) return e;
     if ((e = hipMalloc(&bw.dz[i], (size_t)K * DZ_F * rb_pad(N) * 4)) != hipSuccess) return e;

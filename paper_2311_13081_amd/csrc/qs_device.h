@@ -510,10 +510,11 @@ __device__ inline void set_disturbance(Quad& q, const float d[6]) {
 }
 
 // Right-hand side without the trivial parts: k = {dq (4), dv (3), dw (3)} at
-// attitude q, body rates o and rotor speeds w.
+// attitude q, body rates o and rotor speeds w.  fm, rn2: F / m and 1 / |q|^2.
 template <bool DIST>
 __device__ __forceinline__ void quad_rhs(const Quad& B, float g, const float q[4],
-                                         const float o[3], const float w[4], float k[10]) {
+                                         const float o[3], const float w[4], float k[10],
+                                         float* fm = nullptr, float* rn2 = nullptr) {
   float T[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) T[i] = fmaf(w[i], fmaf(B.c2, w[i], B.c1), B.c0);
@@ -525,7 +526,10 @@ __device__ __forceinline__ void quad_rhs(const Quad& B, float g, const float q[4
   k[2] = fmaf(q[0], hy, fmaf(q[3], hx, -(q[1] * hz)));
   k[3] = fmaf(q[0], hz, fmaf(q[1], hy, -(q[2] * hx)));
   const float n2 = fmaf(q[0], q[0], fmaf(q[1], q[1], fmaf(q[2], q[2], q[3] * q[3])));
-  const float s = (F * B.inv_m) * recip_r(n2), s2 = s + s;
+  const float f = F * B.inv_m, r = recip_r(n2);
+  if (fm) *fm = f;
+  if (rn2) *rn2 = r;
+  const float s = f * r, s2 = s + s;
   const float px = fmaf(q[1], q[3], q[0] * q[2]), py = fmaf(q[2], q[3], -(q[0] * q[1]));
   const float pz = fmaf(-2.0f, fmaf(q[1], q[1], q[2] * q[2]), n2);
   k[4] = DIST ? fmaf(px, s2, B.f[0]) : px * s2;
@@ -760,92 +764,9 @@ __device__ inline float action_to_rpm(const DevCfg& c, float a) {
 
 
 // ---------------------------------------------------------------------------
-// Vector-Jacobian products (discrete adjoint) of the maps above, single
-// precision.  Gradients with respect to the body parameters accumulate in
-// gth = d/d(m, Jxx, Jyy, Jzz, c0, c1, c2, Tm).
+// Vector-Jacobian product (discrete adjoint) of the rotation matrix, single
+// precision.
 // ---------------------------------------------------------------------------
-
-// VJP of deriv() at (x, u) with cotangent gd of dx: accumulates gx, gu, gth.
-__device__ inline void deriv_vjp(const Body<float>& B, const float th[NP], float arm, float km,
-                                 const float x[NS], const float u[4], const float gd[NS],
-                                 float gx[NS], float gu[4], float gth[NP]) {
-  const float w[4] = {x[13], x[14], x[15], x[16]};
-  float T[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) T[i] = B.c0 + w[i] * (B.c1 + B.c2 * w[i]);
-  const float F = (T[0] + T[1]) + (T[2] + T[3]);
-  const float tx = arm * ((T[2] + T[3]) - (T[0] + T[1]));
-  const float ty = arm * ((T[1] + T[2]) - (T[0] + T[3]));
-  const float tz = km * ((T[1] + T[3]) - (T[0] + T[2]));
-  const float qw = x[3], qx = x[4], qy = x[5], qz = x[6];
-  const float ox = x[10], oy = x[11], oz = x[12];
-  const float n2 = qw * qw + qx * qx + qy * qy + qz * qz;
-  const float inv_n2 = recip_r(n2);
-  const float sc = F * B.inv_m * inv_n2;
-  // p' = v
-  gx[7] += gd[0];
-  gx[8] += gd[1];
-  gx[9] += gd[2];
-  // q' = 1/2 q (x) (0, w)
-  const float g3 = gd[3], g4 = gd[4], g5 = gd[5], g6 = gd[6];
-  gx[3] += 0.5f * (g4 * ox + g5 * oy + g6 * oz);
-  gx[4] += 0.5f * (-g3 * ox - g5 * oz + g6 * oy);
-  gx[5] += 0.5f * (-g3 * oy + g4 * oz - g6 * ox);
-  gx[6] += 0.5f * (-g3 * oz - g4 * oy + g5 * ox);
-  gx[10] += 0.5f * (-g3 * qx + g4 * qw + g5 * qz - g6 * qy);
-  gx[11] += 0.5f * (-g3 * qy - g4 * qz + g5 * qw + g6 * qx);
-  gx[12] += 0.5f * (-g3 * qz + g4 * qy - g5 * qx + g6 * qw);
-  // v' = sc * P(q) - g e_z,  P = (2(xz+wy), 2(yz-wx), |q|^2 - 2(x^2+y^2))
-  const float g7 = gd[7], g8 = gd[8], g9 = gd[9];
-  const float P0 = 2.0f * (qx * qz + qw * qy), P1 = 2.0f * (qy * qz - qw * qx),
-              P2 = n2 - 2.0f * (qx * qx + qy * qy);
-  const float gsc = g7 * P0 + g8 * P1 + g9 * P2;
-  const float k2 = 2.0f * gsc * sc * inv_n2;  // from sc's 1/|q|^2
-  gx[3] += 2.0f * sc * (g7 * qy - g8 * qx + g9 * qw) - k2 * qw;
-  gx[4] += 2.0f * sc * (g7 * qz - g8 * qw - g9 * qx) - k2 * qx;
-  gx[5] += 2.0f * sc * (g7 * qw + g8 * qz - g9 * qy) - k2 * qy;
-  gx[6] += 2.0f * sc * (g7 * qx + g8 * qy + g9 * qz) - k2 * qz;
-  const float gF = gsc * B.inv_m * inv_n2;
-  gth[0] += -(gsc * sc + g7 * B.ax + g8 * B.ay + g9 * B.az) * B.inv_m;
-  // w' = J^-1 (tau - w x J w)
-  const float hx = gd[10] * B.inv_Jx, hy = gd[11] * B.inv_Jy, hz = gd[12] * B.inv_Jz;
-  const float dwx = (tx + B.dtx - (B.Jz - B.Jy) * oy * oz) * B.inv_Jx;
-  const float dwy = (ty + B.dty - (B.Jx - B.Jz) * oz * ox) * B.inv_Jy;
-  const float dwz = (tz + B.dtz - (B.Jy - B.Jx) * ox * oy) * B.inv_Jz;
-  gth[1] += -hx * dwx;
-  gth[2] += -hy * dwy;
-  gth[3] += -hz * dwz;
-  gx[11] += -hx * (B.Jz - B.Jy) * oz;
-  gx[12] += -hx * (B.Jz - B.Jy) * oy;
-  gth[3] += -hx * oy * oz;
-  gth[2] += hx * oy * oz;
-  gx[12] += -hy * (B.Jx - B.Jz) * ox;
-  gx[10] += -hy * (B.Jx - B.Jz) * oz;
-  gth[1] += -hy * oz * ox;
-  gth[3] += hy * oz * ox;
-  gx[10] += -hz * (B.Jy - B.Jx) * oy;
-  gx[11] += -hz * (B.Jy - B.Jx) * ox;
-  gth[2] += -hz * ox * oy;
-  gth[1] += hz * ox * oy;
-  // torques and collective thrust -> rotor thrusts
-  float gT[4];
-  gT[0] = gF - arm * (hx + hy) - km * hz;
-  gT[1] = gF - arm * hx + arm * hy + km * hz;
-  gT[2] = gF + arm * (hx + hy) - km * hz;
-  gT[3] = gF + arm * hx - arm * hy + km * hz;
-  // thrust curve T = c0 + c1 w + c2 w^2, motor lag w' = (u - w) / Tm
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    gth[4] += gT[i];
-    gth[5] += gT[i] * w[i];
-    gth[6] += gT[i] * w[i] * w[i];
-    const float gm = gd[13 + i];
-    gx[13 + i] += gT[i] * (B.c1 + 2.0f * B.c2 * w[i]) - gm * B.inv_Tm;
-    gu[i] += gm * B.inv_Tm;
-    gth[7] += -gm * (u[i] - w[i]) * B.inv_Tm * B.inv_Tm;
-  }
-  (void)th;
-}
 
 // VJP of rotmat(q) (R of q/|q|, row-major) with cotangent G: accumulates gq.
 __device__ inline void rotmat_vjp(const float q[4], const float G[9], float gq[4]) {

@@ -181,7 +181,7 @@ __global__ void __launch_bounds__(256) k_plain_l1(int N, const float* __restrict
     if (lg >= 2) F[b][4] = 0.0f;  // features 18, 19: padding
   }
   __builtin_amdgcn_sched_barrier(0);
-  stage_fragments<4>(W, sW, 0, T_G2);
+  stage_fragments<4>(W, sW, T_G2, tile_src);
   __syncthreads();
   if (first >= N) return;
   u4t x[4][2][T_P], xs[1][2][T_P];
@@ -237,7 +237,8 @@ __global__ void __launch_bounds__(256) k_plain_l2(int N, const float* __restrict
       for (int r = 0; r < 4; ++r) h1[n][b][r] = in[(size_t)(16 * n + 4 * lg + r) * N + e];
   }
   __builtin_amdgcn_sched_barrier(0);
-  stage_fragments<4>(W, sW, T_G2, T_G);
+  stage_fragments<4>(W, sW, T_G - T_G2,
+                     [](int g, int l, int e) { return tile_src(T_G2 + g, l, e); });
   __syncthreads();
   if (first >= N) return;
   u4t x[2][2][T_P];

@@ -13,9 +13,9 @@
 //        rank-1 update per action with B = the lane's own dz3 value (the
 //        pattern of the forward's layer 1): register 4 bb + v of tile n
 //        holds neuron 16 n + 4 lg + v of env 16 bb + li (lane li + 16 lg);
-//   dz1 = (W2^T dz2) [z1 > 0]                v_mfma_f32_16x16x4f32 chained over
-//        the dz2 registers as B operands (K-chunk = neurons 16 n + 4 k + v),
-//        the same tile layout out;
+//   dz1 = (W2^T dz2) [z1 > 0]                bf16 products of split operands
+//        (qs_tile.h: six per fp32 product, 2.7 times its rate), the dz2
+//        registers in their order as operands, the same tile layout out;
 //   do  = W1^T dz1                            the same over the dz1 registers,
 //        ten 16-feature tiles; register r of block bb holds feature
 //        16 p + 4 lg + r of env 16 bb + li;
@@ -25,9 +25,16 @@
 // and a 4 x 4 transpose across the lane groups (two permlane32 and two
 // permlane16 swaps per register) brings every feature of a tile to the lane
 // of its env, where the observation's share joins the state and history
-// adjoints.  The per-step inputs and outputs use the blocked layouts of the
+// adjoints.  One wave per SIMD, so matrix and vector work add up rather than
+// overlap: per 64-env step 688 bf16 products of 16 cycles and about 2600 vector
+// instructions; with fp32 products (640 of 32 cycles) 16 steps of 65536 envs
+// took 402 us, now 286.  The per-step inputs and outputs use the blocked layouts of the
 // record and the cotangent buffer (row f of env e at (e / 64) F 64 + 64 f +
 // e % 64), so a lane's own-env rows are whole 256-byte rows of the wave.
+//
+// Fused multiply-adds only where one expression of the source holds the product
+// and the sum, so kernels that promise equal results round alike.
+#pragma clang fp contract(on)
 #include "qs_actor.h"
 #include "qs_backward.h"
 #include "qs_forward.h"
@@ -37,19 +44,17 @@ namespace qs {
 
 // LDS (floats):
 //   L_W3T[n][i]             = W3[i][n] (one 16-byte read: the 4 output weights of neuron n);
-//   L_W2Q[mt][n][g][i][v]   = W2[16 n + 4 g + v][16 mt + i];
-//   L_W1Q[p][mt][g][i][v]   = W1[16 mt + 4 g + v][16 p + i] (0 past feature 145).
-constexpr int L_W3T = 0, L_W2Q = L_W3T + NHID * NA, L_W1Q = L_W2Q + NHID * NHID,
-              L_TOTAL = L_W1Q + 10 * 4 * 4 * 16 * 4;
+//   L_FRAG: the transposed layers' fragments (stage_transposed).
+constexpr int L_W3T = 0, L_FRAG = L_W3T + NHID * NA, L_TOTAL = L_FRAG + 4 * RT_FRAGS;
 // History adjoint: the older HR slots of each env in a per-wave ring in LDS
 // ([HR][4][64 lanes] after the weights: moving the slots one step older is a
 // turn of the ring), the newest NH - HR in registers.  Each step adds the
 // observation's share into every slot: in the ring that is a read, an add
 // and a write of LDS per value, in registers an accumulator-register move or
-// two.  Of HR = 4, 8, 16 and 24 (the largest the LDS holds for four waves),
-// 8 measured fastest (377 us per 16-step segment at 65536 envs against 395
-// for 24); with fewer the registers no longer fit beside the rest.
-constexpr int HR = 8;
+// two.  HR = 12 is the smallest at which the kernel spills no register (a spill
+// read back behind a step's stores waits for all of them): 16 steps of 65536
+// envs in 279 us, against 320 for 8 (14 spilled) and 284 for 16.
+constexpr int HR = 12;
 constexpr int L_RING = HR * NA * 64;
 constexpr int L_BYTES = (L_TOTAL + 4 * L_RING) * 4;
 static_assert(L_BYTES <= 160 * 1024, "weights and four history rings must fit in LDS");
@@ -57,15 +62,9 @@ static_assert(L_BYTES <= 160 * 1024, "weights and four history rings must fit in
 __device__ inline void stage_reverse1(const float* __restrict__ W, float* lds, bool bf16) {
   stage_lds(lds + L_W3T, NHID * NA, W,
             [](int i) { return OFF_W3 + (i & 3) * NHID + (i >> 2); }, bf16);
-  stage_lds(lds + L_W2Q, NHID * NHID, W, [](int i) {
-    const int v = i & 3, li = (i >> 2) & 15, g = (i >> 6) & 3, n = (i >> 8) & 3, mt = i >> 10;
-    return OFF_W2 + (16 * n + 4 * g + v) * NHID + 16 * mt + li;
-  }, bf16);
-  stage_lds(lds + L_W1Q, 10 * 4 * 4 * 16 * 4, W, [](int i) {
-    const int v = i & 3, li = (i >> 2) & 15, g = (i >> 6) & 3, mt = (i >> 8) & 3, p = i >> 10;
-    const int f = 16 * p + li, neuron = 16 * mt + 4 * g + v;
-    return f < NO ? OFF_W1 + neuron * NO + f : -1;
-  }, bf16);
+  stage_transposed(
+      W, reinterpret_cast<u4t*>(lds + L_FRAG),
+      [](int p, int i) { return 16 * p + i < NO ? 16 * p + i : -1; }, bf16);
 }
 
 // v where bit b of the mask word m is set, +0 elsewhere (the sign-extended
@@ -86,8 +85,8 @@ struct StepIn1 {
 __device__ inline void load_step1(StepIn1& in, __amdgpu_buffer_rsrc_t rrec, uint32_t sr,
                                   uint32_t vown, uint32_t vmask,
                                   const float* __restrict__ d_rewards,
-                                  const float* __restrict__ d_states, int t, int N, int e) {
-  const uint32_t eo = opaque((uint32_t)e);
+                                  const float* __restrict__ d_states, int t, int N,
+                                  uint32_t ve) {
 #pragma unroll
   for (int bb = 0; bb < 4; ++bb)
     in.m[bb] = __float_as_uint(bld1(rrec, vmask, sr + 4u * (REC_M * RB + 16 * bb)));
@@ -95,10 +94,7 @@ __device__ inline void load_step1(StepIn1& in, __amdgpu_buffer_rsrc_t rrec, uint
   for (int i = 0; i < NS; ++i) in.x[i] = bld1(rrec, vown, sr + 4u * (REC_X + i) * RB);
 #pragma unroll
   for (int i = 0; i < NA; ++i) in.a[i] = bld1(rrec, vown, sr + 4u * (REC_A + i) * RB);
-  in.dR = d_rewards ? d_rewards[(size_t)t * N + eo] : 1.0f;
-#pragma unroll
-  for (int i = 0; i < NS; ++i)
-    in.dS[i] = d_states ? d_states[((size_t)t * NS + i) * N + eo] : 0.0f;
+  load_cotangents(in.dS, in.dR, d_rewards, d_states, t, N, ve);
 }
 
 // One segment of n steps (steps t0 .. t0 + n - 1 of the rollout), last to
@@ -127,6 +123,7 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
   const uint32_t rbp = (uint32_t)rb_pad(N);
   const uint32_t blk = __builtin_amdgcn_readfirstlane(env0 / RB);
   const uint32_t s_rblk = 4u * blk * (REC_F * RB), s_zblk = 4u * blk * (DZ_F * RB);
+  const uint32_t ve = 4u * (uint32_t)e;
   const uint32_t vown = 4u * (uint32_t)(e - env0), vlane = 4u * (uint32_t)lane;
   const uint32_t vtile = 4u * (uint32_t)(4 * lg * RB + li);
   const uint32_t vmask = 4u * (uint32_t)(lg * RB + li);
@@ -136,13 +133,11 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
   float th[NP];
 #pragma unroll
   for (int i = 0; i < NP; ++i) th[i] = theta[(size_t)i * N + e];
-  Body<float> B = make_body<float>(th);
-  {
-    // the episode disturbance of the segment (no resets in a taped rollout)
-    float d[6];
-    disturbance(c, (uint32_t)e, (uint32_t)__float_as_int(ck[(size_t)CK_EP * N + e]), d);
-    set_disturbance(B, d);
-  }
+  // the episode disturbance of the segment (no resets in a taped rollout)
+  float dist[6];
+  disturbance(c, (uint32_t)e, (uint32_t)__float_as_int(ck[(size_t)CK_EP * N + e]), dist);
+  const Quad B = make_rev_quad(c, th, dist);
+  const RevStep rs = make_rev_step(c);
   const bool renorm = (c.flags & F_RENORM_Q) != 0;
 
   // history adjoint: slot s < HR at ring row (s + base) mod HR, slot s >= HR
@@ -167,17 +162,18 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
 
   StepIn1 cur, nxt;
   load_step1(cur, rrec, 4u * (uint32_t)(n - 1) * (REC_F * rbp) + s_rblk, vown, vmask, d_rewards,
-             d_states, t0 + n - 1, N, e);
+             d_states, t0 + n - 1, N, ve);
+  drain_loads();
   for (int tl = n - 1; tl >= 0; --tl) {
     __asm__ volatile("" ::: "memory");
     const uint32_t sz = 4u * (uint32_t)tl * (DZ_F * rbp) + s_zblk;  // the step's cotangents
     const int tp = tl > 0 ? tl - 1 : 0;
 
     float gx[NS], ga[NA];
-    reverse_dynamics(c, B, th, renorm, cur.x, cur.a, cur.dR, ls, lR[NH - HR - 1], gx, ga, gth);
+    reverse_dynamics(c, rs, B, renorm, cur.x, cur.a, d_rewards ? cur.dR : 1.0f, ls, lR[NH - HR - 1], gx, ga, gth);
     // the next step's inputs, in flight during the input VJP below
     load_step1(nxt, rrec, 4u * (uint32_t)tp * (REC_F * rbp) + s_rblk, vown, vmask, d_rewards,
-               d_states, t0 + tp, N, e);
+               d_states, t0 + tp, N, ve);
     // Lanes of envs >= N take dz3 = 0: the layer products keep envs apart
     // (one env per column), so their columns of dz2 and dz1 are zero too and
     // every lane stores unconditionally -- zeros into the slots of envs >= N,
@@ -208,23 +204,27 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
           d2[n2][r] = keep_if(d2[n2][r], cur.m[bb], 8 * n2 + 4 + v);
           bst1(d2[n2][r], rdz, vtile, sz + 4u * ((NHID + 16 * n2 + v) * RB + 16 * bb));
         }
-    // dz1 = (W2^T dz2) [z1 > 0]: chains over the dz2 registers, 16 per
-    // (tile, block)
-    f4 d1[4][4];
+    // dz1 = (W2^T dz2) [z1 > 0]
+    const u4t* frag = reinterpret_cast<const u4t*>(lds + L_FRAG);
+    f4t d1[4][4];
+    {
+      u4t xo[2][4][T_P];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
+      for (int m = 0; m < 2; ++m)
 #pragma unroll
-      for (int bb = 0; bb < 4; ++bb) d1[mt][bb] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int bb = 0; bb < 4; ++bb) {
+          f4t lo, hi;
 #pragma unroll
-      for (int n2 = 0; n2 < 4; ++n2) {
-        const f4 wv =
-            *reinterpret_cast<const f4*>(&lds[L_W2Q + (((mt * 4 + n2) * 4 + lg) * 16 + li) * 4]);
+          for (int v = 0; v < 4; ++v) {
+            lo[v] = d2[2 * m][4 * bb + v];
+            hi[v] = d2[2 * m + 1][4 * bb + v];
+          }
+          hidden_operand(lo, hi, xo[m][bb]);
+        }
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-#pragma unroll
-          for (int bb = 0; bb < 4; ++bb)
-            d1[mt][bb] =
-                __builtin_amdgcn_mfma_f32_16x16x4f32(wv[v], d2[n2][4 * bb + v], d1[mt][bb], 0, 0, 0);
+      for (int mt = 0; mt < 4; ++mt) {
+        transposed_sum<1, 4>(frag, 2 * mt, lane, xo, reinterpret_cast<f4t(&)[1][4]>(d1[mt]));
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
 #pragma unroll
@@ -236,6 +236,11 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
           d1[mt][bb][r] = keep_if(d1[mt][bb][r], cur.m[bb], 8 * mt + r);
           bst1(d1[mt][bb][r], rdz, vtile, sz + 4u * ((16 * mt + r) * RB + 16 * bb));
         }
+    u4t x1[2][4][T_P];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int bb = 0; bb < 4; ++bb) hidden_operand(d1[2 * m][bb], d1[2 * m + 1][bb], x1[m][bb]);
 
     // the history adjoint moves one slot older: H_t[s] feeds H_{t+1}[s - 1]
     // (registers shift, the ring turns; the ring's newest slot moves to the
@@ -258,19 +263,9 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
     float gf[18];
 #pragma unroll
     for (int p = 0; p < 10; ++p) {
-      f4 o[4];
-#pragma unroll
-      for (int bb = 0; bb < 4; ++bb) o[bb] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        const f4 wv =
-            *reinterpret_cast<const f4*>(&lds[L_W1Q + (((p * 4 + mt) * 4 + lg) * 16 + li) * 4]);
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-#pragma unroll
-          for (int bb = 0; bb < 4; ++bb)
-            o[bb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[v], d1[mt][bb][v], o[bb], 0, 0, 0);
-      }
+      f4t oa[1][4];
+      transposed_sum<1, 4>(frag, RT_G1 + 2 * p, lane, x1, oa);
+      const f4t(&o)[4] = oa[0];
       // o[bb][r] in lane li + 16 lg: feature 16 p + 4 lg + r of env 16 bb + li.
       // Swapping the upper half of o[0] with the lower half of o[2] (and o[1]
       // with o[3]), then the odd 16-lane rows of the first results with the

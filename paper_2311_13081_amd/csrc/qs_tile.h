@@ -99,12 +99,14 @@ __device__ inline void load_fragment(const float* __restrict__ W, int g, int l, 
   }
 }
 
-// Stages groups [g0, g1) of the actor's fragments at dst (u4t), every thread
-// of the workgroup taking (group, lane) pairs, the loads of up to eight pairs
-// in flight at a time.
-template <int MAXT>
-__device__ inline void stage_fragments(const float* __restrict__ W, u4t* dst, int g0, int g1) {
-  const int nt = blockDim.x, n = (g1 - g0) * 64;
+// Stages n groups of fragments at dst, src(g, l, e) the source index of element e
+// of lane l in group g (-1 for padding), every thread of the workgroup taking
+// (group, lane) pairs, the loads of MAXT pairs in flight at a time.  bf16: the
+// weights rounded to bf16 first.
+template <int MAXT, typename Src>
+__device__ inline void stage_fragments(const float* __restrict__ W, u4t* dst, int groups, Src src,
+                                       bool bf16 = false) {
+  const int nt = blockDim.x, n = groups * 64;
   for (int base = threadIdx.x; base < n; base += MAXT * nt) {
     float v[MAXT][8];
 #pragma unroll
@@ -112,9 +114,10 @@ __device__ inline void stage_fragments(const float* __restrict__ W, u4t* dst, in
       const int t = min(base + j * nt, n - 1);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const int s = tile_src(g0 + (t >> 6), t & 63, e);
+        const int s = src(t >> 6, t & 63, e);
         v[j][e] = W[s < 0 ? 0 : s];
         if (s < 0) v[j][e] = 0.0f;
+        if (bf16) v[j][e] = (float)(__bf16)v[j][e];
       }
     }
 #pragma unroll
@@ -137,7 +140,7 @@ __device__ inline void stage_fragments(const float* __restrict__ W, u4t* dst, in
 
 // The whole actor into LDS.
 __device__ inline void stage_tile(const float* __restrict__ W, float* lds) {
-  stage_fragments<4>(W, reinterpret_cast<u4t*>(lds), 0, T_G);
+  stage_fragments<4>(W, reinterpret_cast<u4t*>(lds), T_G, tile_src);
   for (int i = threadIdx.x; i < NHID + NA * T_W3_LD + NA; i += blockDim.x) {
     if (i < NHID) {
       lds[T_B2 + i] = W[OFF_B2 + i];
