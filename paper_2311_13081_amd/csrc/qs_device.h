@@ -652,6 +652,11 @@ __device__ __forceinline__ uint32_t opaque(uint32_t v) {
   return v;
 }
 
+// Waits for every vector load issued so far.  Ahead of a time loop: at its head the
+// compiler otherwise takes the loads before the loop, the youngest on the way in,
+// as the count to wait down to, which on the way back drains the step's stores.
+__device__ __forceinline__ void drain_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
 // c ? a : b by value.  (The conditional operator on two array elements is an
 // lvalue, which the compiler may lower to a load through a selected address;
 // the array then leaves the registers.)

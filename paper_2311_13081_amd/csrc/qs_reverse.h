@@ -57,12 +57,6 @@ __device__ __forceinline__ void load_cotangents(float dS[NS], float& dR,
 #pragma unroll
   for (int i = 0; i < NS; ++i) dS[i] = bld1(rs, ve, (uint32_t)i * row);
 }
-// Waits for every vector load issued so far.  Ahead of a loop that loads one step
-// ahead: at the loop's head the compiler otherwise takes the first iteration's
-// loads, the youngest there, as the count to wait down to, which on the way back
-// drains all stores of the step.
-__device__ __forceinline__ void drain_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
-
 // Step sizes of the reverse step, in scalar registers.
 struct RevStep {
   float h, hh, h6, h26;  // h, h / 2, h / 6, h^2 / 6

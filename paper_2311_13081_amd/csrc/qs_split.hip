@@ -224,7 +224,7 @@ k_split(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
 
   f4t a1[1][1];  // layer 1's history sums of the coming step
   A.history(H, a1);
-
+  drain_loads();
   for (int t = 0; t < T; ++t) {
     const uint32_t so = opaque(ok);
     const int gt = t_base + t;

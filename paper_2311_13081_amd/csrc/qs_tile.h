@@ -222,24 +222,33 @@ template <int TILES>
 struct FragPipe {
   static constexpr int NN = T_NN<TILES>;
   const u4t* w;
-  int lane;
   Frags<NN> next;
+  // An LDS read reaches 64 KB past its address: the groups further out get an
+  // address of their own, formed where it is used (hoisted out of the time loop
+  // it would cost a register, or a spill).
+  __device__ inline void load(int g, int stride) {
+    constexpr int FAR = 20;  // T_P KB a group
+    const int lane = threadIdx.x & 63;
+    if (g + stride * (NN - 1) > FAR)
+      next.load(w, g, stride, (int)opaque((uint32_t)lane));
+    else
+      next.load(w, g, stride, lane);
+  }
   // read i of the step (28 / NN of them): NN = 1 every group in turn; NN = 2 the
   // history chunks of tiles 0, 1, of tiles 2, 3, the state chunks, layer 2
   __device__ inline void read(int i) {
     if constexpr (NN == 1) {
-      next.load(w, i % T_G, 0, lane);
+      load(i % T_G, 0);
     } else {
       i %= T_G / 2;
       const int g = i < 8 ? 8 * (i >> 2) + (i & 3)
                     : i < 10 ? T_GS + 2 * (i - 8)
                              : T_G2 + 4 * ((i - 10) >> 1) + ((i - 10) & 1);
-      next.load(w, g, i < 8 ? 4 : i < 10 ? 1 : 2, lane);
+      load(g, i < 8 ? 4 : i < 10 ? 1 : 2);
     }
   }
   __device__ inline void start(const float* lds) {
     w = reinterpret_cast<const u4t*>(lds);
-    lane = threadIdx.x & 63;
     read(0);
   }
   // fragments of read i; the one after it is issued
@@ -517,12 +526,12 @@ __device__ inline void tile_history(FragPipe<TILES>& fp, const TileHist<TILES>& 
 // The rest of the actor for the wave's tiles: z3 (pre-tanh) of the lane's own
 // env in every lane.  a1: layer 1's history sums (consumed); F: the state
 // features 4 e + lg of each tile's env.  rec takes the layer results before the
-// ReLU and the ReLU masks (the record of taped rollouts).
+// ReLU (the record of taped rollouts).
 template <int TILES, typename Rec>
 __device__ inline void tile_actor(const float* lds, FragPipe<TILES>& fp, f4t (&a1)[4][TILES],
                                   const float (&F)[TILES][5], float z3[NA], Rec&& rec) {
   constexpr int NN = T_NN<TILES>;
-  const int lg = (threadIdx.x & 63) >> 4;
+  const int lg = (int)opaque((threadIdx.x & 63) >> 4);
   {
     u4t x[1][TILES][T_P];
 #pragma unroll
@@ -559,7 +568,6 @@ __device__ inline void tile_actor(const float* lds, FragPipe<TILES>& fp, f4t (&a
     }
   }
   rec.layer2(a2);
-  rec.masks(a1, a2);
   relu_tiles(a2);
   Layer3 l3;
   l3.load(lds + T_W3, lds + T_B3);
@@ -572,25 +580,19 @@ struct NoRec {
   __device__ inline void layer1(const A&) {}
   template <typename A>
   __device__ inline void layer2(const A&) {}
-  template <typename A>
-  __device__ inline void masks(const A&, const A&) {}
 };
 
 // ReLU mask word of a record (row REC_M + lg of the env's column, lg the
 // lane group): bit 8 n + r is set when layer-1 unit 16 n + 4 lg + r of the
 // env has a positive pre-activation, bit 8 n + 4 + r the same for layer 2.
-// z1, z2: the lane's result tiles of one env tile, before or after the ReLU (z
-// > 0 and relu(z) > 0 agree, NaN included).
+// z: the lane's result tiles of one layer; layer 2's bits are these << 4.
 template <int TILES>
-__device__ inline uint32_t tile_mask(const f4t (&z1)[4][TILES], const f4t (&z2)[4][TILES], int b) {
+__device__ inline uint32_t tile_mask(const f4t (&z)[4][TILES], int b) {
   uint32_t m = 0u;
 #pragma unroll
   for (int n = 0; n < 4; ++n)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      m |= (z1[n][b][r] > 0.0f ? 1u : 0u) << (8 * n + r);
-      m |= (z2[n][b][r] > 0.0f ? 1u : 0u) << (8 * n + 4 + r);
-    }
+    for (int r = 0; r < 4; ++r) m |= (z[n][b][r] > 0.0f ? 1u : 0u) << (8 * n + r);
   return m;
 }
 

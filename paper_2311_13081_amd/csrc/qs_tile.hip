@@ -17,40 +17,69 @@
 
 namespace qs {
 
-// Layer results and masks of a recorded step (the backward's record): rows of
-// the wave's tiles at base + 64 row + zoff[b], zoff[b] the lane's offset of
-// row 4 lg of its env in tile b; nothing for envs past the batch.
+// The record of a step (the backward's): rows through a buffer view of the
+// segment's record, s[b] the byte offset of tile b's envs in the step and z the
+// lane's of row 4 lg of its env there, so that an address costs no vector
+// instruction.  Envs past the batch record their shadow into the padding of the
+// last block.
 template <int TILES>
 struct StepRec {
-  float* base;  // NULL: the step is not recorded
-  uint32_t zoff[TILES];
-  bool on[TILES];
-  uint32_t mask[TILES];
-  template <int ROW>
-  __device__ inline void rows(const f4t (&z)[4][TILES]) {
+  __amdgpu_buffer_rsrc_t buf;
+  bool on;  // wave uniform
+  uint32_t s[TILES], z, mask[TILES];
+  template <int ROW, int SHIFT>
+  __device__ inline void rows(const f4t (&v)[4][TILES]) {
+    if (!on) return;
 #pragma unroll
-    for (int b = 0; b < TILES; ++b)
-      if (on[b])
+    for (int b = 0; b < TILES; ++b) {
 #pragma unroll
-        for (int n = 0; n < 4; ++n)
+      for (int n = 0; n < 4; ++n)
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            base[(size_t)(ROW + 16 * n + r) * RB + zoff[b]] = z[n][b][r];
+        for (int r = 0; r < 4; ++r)
+          bst1(v[n][b][r], buf, z, s[b] + 4u * (ROW + 16 * n + r) * RB);
+      mask[b] = opaque(mask[b] | tile_mask<TILES>(v, b) << SHIFT);
+    }
   }
-  __device__ inline void layer1(const f4t (&z)[4][TILES]) {
-    if (base) rows<REC_Z1>(z);
-  }
-  __device__ inline void layer2(const f4t (&z)[4][TILES]) {
-    if (base) rows<REC_Z2>(z);
-  }
-  __device__ inline void masks(const f4t (&h1)[4][TILES], const f4t (&h2)[4][TILES]) {
-    if (base)
-#pragma unroll
-      for (int b = 0; b < TILES; ++b) mask[b] = tile_mask<TILES>(h1, h2, b);
-  }
+  __device__ inline void layer1(const f4t (&v)[4][TILES]) { rows<REC_Z1, 0>(v); }
+  __device__ inline void layer2(const f4t (&v)[4][TILES]) { rows<REC_Z2, 4>(v); }
 };
 
 constexpr int T_MAX_THREADS = 512;
+
+// Values of a lane that a step needs once, in columns of LDS (one per lane)
+// instead of the registers of the actor: the body, the episode accumulators, the
+// hover speed and each tile's hover action, and the next start state.  Left to
+// the compiler they are spilled to memory, and reading a spill back waits for
+// every store issued before it: recorded steps of 65536 envs took 19.1 us with 85
+// spills (and 1.1 GB written for 0.64 GB of record per 16 steps), now 12.
+enum { PK_NEXT = 0, PK_ACC = NRES, PK_HOVER = PK_ACC + 3, PK_AH = PK_HOVER + 1, PK_BODY = PK_AH + 2 };
+constexpr int PK_F = PK_BODY + sizeof(Body<float>) / 4;
+struct Park {
+  float* p;
+  __device__ inline float& operator[](int i) const { return p[i * T_MAX_THREADS]; }
+  // the members a body has without (11) or with the episode disturbance
+  template <bool DIST>
+  __device__ inline Body<float> body() const {
+    struct { float v[PK_F - PK_BODY]; } f = {};
+#pragma unroll
+    for (int i = 0; i < (DIST ? PK_F - PK_BODY : 11); ++i) f.v[i] = (*this)[PK_BODY + i];
+    return __builtin_bit_cast(Body<float>, f);
+  }
+  __device__ inline void put(const Body<float>& b) const {
+    struct F { float v[PK_F - PK_BODY]; };
+    const F f = __builtin_bit_cast(F, b);
+#pragma unroll
+    for (int i = 0; i < PK_F - PK_BODY; ++i) (*this)[PK_BODY + i] = f.v[i];
+  }
+  __device__ inline EpAcc acc() const {
+    return {(*this)[PK_ACC], (*this)[PK_ACC + 1], __float_as_int((*this)[PK_ACC + 2])};
+  }
+  __device__ inline void put(const EpAcc& a) const {
+    (*this)[PK_ACC] = a.cur;
+    (*this)[PK_ACC + 1] = a.last;
+    (*this)[PK_ACC + 2] = __int_as_float(a.len);
+  }
+};
 
 // T steps; outputs indexed by t_base + t.  Lanes of envs past the batch
 // shadow the wave's first env (loads only) so every operand is finite.
@@ -68,7 +97,8 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
        float* __restrict__ rewards, uint8_t* __restrict__ dones, float* __restrict__ states,
        float* __restrict__ tape, int ckpt_every, const float* __restrict__ ck_in, RecSpan rs) {
   constexpr int SUB = 4 / TILES;  // lanes per env
-  __shared__ __attribute__((aligned(16))) float lds[T_TOTAL + NRES * T_MAX_THREADS];
+  __shared__ __attribute__((aligned(16))) float lds[T_TOTAL + PK_F * T_MAX_THREADS];
+  static_assert((T_TOTAL + PK_F * T_MAX_THREADS) * 4 <= 160 * 1024, "weights and columns fit in LDS");
   const int N = c.n_envs;
   stage_tile(W, lds);
   __syncthreads();
@@ -89,13 +119,12 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
   float th[NP];
 #pragma unroll
   for (int i = 0; i < NP; ++i) th[i] = b.theta[(size_t)i * N + e];
-  Body<float> B = make_body<float>(th);
+  const Park park{lds + T_TOTAL + threadIdx.x};
   const bool renorm = (c.flags & F_RENORM_Q) != 0;
 
   float x[NS];
   TileHist<TILES> H;
   int head0 = 0, t_ep = 0, ep = 0;
-  EpAcc acc;
   if (REC) {
 #pragma unroll
     for (int i = 0; i < NS; ++i) x[i] = ck_in[(size_t)i * N + e];
@@ -107,7 +136,7 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
                    ck_in[(size_t)(NS + (2 * q + 1) * NA + lg) * N + et[t]]);
     t_ep = __float_as_int(ck_in[(size_t)CK_TEP * N + e]);
     ep = __float_as_int(ck_in[(size_t)CK_EP * N + e]);
-    acc.cur = acc.last = 0.0f, acc.len = 0;
+    park.put(EpAcc{0.0f, 0.0f, 0});
   } else {
 #pragma unroll
     for (int i = 0; i < NS; ++i) x[i] = b.state[(size_t)i * N + e];
@@ -124,32 +153,36 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     head0 = b.head[e];
     t_ep = b.t_ep[e];
     ep = b.ep[e];
+    EpAcc acc;
     acc.load(b, N, e);
+    park.put(acc);
   }
   SetPoint sp;
   if (EXTRAS) sp.load(c, N, e);
   bool was_reset = false;
-  const float wh = hover_rpm(c, th[0], th[4], th[5], th[6]);
-  const float ah = rpm_to_action(c, wh);
-  float aht[TILES];
   {
+    const float wh = hover_rpm(c, th[0], th[4], th[5], th[6]), ah = rpm_to_action(c, wh);
     const float v[4] = {ah, ah, ah, ah};
+    float aht[TILES];
     to_tiles<TILES>(v, lg, aht);
-  }
-  if (EXTRAS) {
-    float d[6];
-    disturbance(c, (uint32_t)e, (uint32_t)ep, d);
-    set_disturbance(B, d);
+    park[PK_HOVER] = wh;
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) park[PK_AH + t] = aht[t];
+    Body<float> B = make_body<float>(th);
+    if (EXTRAS) {
+      float d[6];
+      disturbance(c, (uint32_t)e, (uint32_t)ep, d);
+      set_disturbance(B, d);
+    }
+    park.put(B);
   }
   // next episode's start state drawn ahead (long launches only)
   const bool ahead = T >= 2 * RESERVE_PERIOD && (c.flags & F_AUTORESET) != 0;
-  // (kept in LDS, one column per lane: it is touched at resets only)
-  float* nxp = lds + T_TOTAL + threadIdx.x;
   const auto draw_next = [&]() {
     float nx[NRES];
-    draw_ahead<0>(c, (uint32_t)e, (uint32_t)(ep + 1), wh, nx);
+    draw_ahead<0>(c, (uint32_t)e, (uint32_t)(ep + 1), park[PK_HOVER], nx);
 #pragma unroll
-    for (int i = 0; i < NRES; ++i) nxp[i * T_MAX_THREADS] = nx[i];
+    for (int i = 0; i < NRES; ++i) park[PK_NEXT + i] = nx[i];
   };
   bool have = ahead;
   if (ahead) draw_next();
@@ -165,6 +198,7 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     for (int n = 0; n < 4; n += T_NN<TILES>) tile_history<TILES>(fp, H, n, a1);
   };
   history();
+  drain_loads();
   for (int t = 0; t < T; ++t) {
     // keeps the weight reads inside the step (hoisted out of the time loop
     // they would pin the registers)
@@ -196,16 +230,16 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     // other wave's vector instructions fill in
     __builtin_amdgcn_s_setprio(1);
     float z3[NA];
-    float* rt = nullptr;  // the step's record
     StepRec<TILES> sr;
     if constexpr (TAPE) {
-      rt = rec_on ? ra.base + rec_step(ra.step, N) : nullptr;
-      sr.base = rt;
+      sr.on = rec_on;
+      sr.buf = span_rsrc(ra.base, rec_on ? 4u * (uint32_t)rec_floats(ra.n, N) : 0u);
+      const uint32_t l = opaque((uint32_t)lane);  // (not formed ahead of the loop)
+      sr.z = 4u * (4 * (l >> 4) * RB + (l & 15));
 #pragma unroll
       for (int tl = 0; tl < TILES; ++tl) {
-        sr.on[tl] = env0 + 16 * tl + li < N;
-        sr.zoff[tl] = opaque((uint32_t)(rb_at(env0 + 16 * tl + li, REC_F) + 4 * lg * RB));
         sr.mask[tl] = 0u;
+        sr.s[tl] = 4u * (uint32_t)(rec_step(ra.step, N) + rb_at(env0 + 16 * tl, REC_F));
       }
       tile_actor<TILES>(lds, fp, a1, F, z3, sr);
     } else {
@@ -217,30 +251,29 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     for (int i = 0; i < NA; ++i) a[i] = tanh_act(z3[i]);
     to_tiles<TILES>(a, lg, at);
     if (TAPE && rec_on) {
-      const uint32_t koff = opaque((uint32_t)lg * RB);
-      float* act = ra.base + rec_act(ra.n, N);
+      const uint32_t l = opaque((uint32_t)lane), ko = 4u * ((l >> 4) * RB + (l & 15));  // row lg
 #pragma unroll
       for (int tl = 0; tl < TILES; ++tl) {
-        if (!sr.on[tl]) continue;
         // the state features, masks and actions; the history features are
         // earlier actions, kept on the segment's action tape (the
         // checkpoint's history first, then a_t)
-        const uint32_t ko = koff + (uint32_t)rb_at(env0 + 16 * tl + li, REC_F);
-        const uint32_t ao = koff + (uint32_t)rb_at(env0 + 16 * tl + li, (NH + ra.n) * NA);
+        const uint32_t act =
+            4u * (uint32_t)(rec_act(ra.n, N) + rb_at(env0 + 16 * tl, (NH + ra.n) * NA));
 #pragma unroll
         for (int q = 0; q < 5; ++q)
-          if (4 * q + lg < 18) rt[(size_t)(REC_O + 4 * q) * RB + ko] = F[tl][q];
-        rt[(size_t)REC_A * RB + ko] = at[tl];
-        rt[(size_t)REC_M * RB + ko] = __uint_as_float(sr.mask[tl]);
+          if (q < 4 || lg < 2) bst1(F[tl][q], sr.buf, ko, sr.s[tl] + 4u * (REC_O + 4 * q) * RB);
+        bst1(at[tl], sr.buf, ko, sr.s[tl] + 4u * REC_A * RB);
+        bst1(__uint_as_float(sr.mask[tl]), sr.buf, ko, sr.s[tl] + 4u * REC_M * RB);
         if (ra.step == 0) {
 #pragma unroll
-          for (int s = 0; s < NH; ++s) act[(size_t)(s * NA) * RB + ao] = H.get(tl, s);
+          for (int s = 0; s < NH; ++s) bst1(H.get(tl, s), sr.buf, ko, act + 4u * (s * NA) * RB);
         }
-        act[(size_t)((NH + ra.step) * NA) * RB + ao] = at[tl];
+        bst1(at[tl], sr.buf, ko, act + 4u * (uint32_t)((NH + ra.step) * NA) * RB);
       }
-      if (active)
-        store_rows<SUB, NS>(rt + REC_X * RB, RB,
-                            opaque(4u * (uint32_t)(rb_at(e, REC_F) + sub * RB)), sub, x);
+      // row sub of the own env, from the wave's first
+      const uint32_t xo = 4u * ((l >> 4) / TILES * RB + 16 * ((l >> 4) % TILES) + (l & 15));
+      store_rows<SUB, NS>(ra.base + rec_step(ra.step, N) + rb_at(env0, REC_F) + REC_X * RB, RB,
+                          xo, sub, x);
     }
     // the action goes to the history ring in memory as it is applied (the
     // last 32 of a launch; the older ones would be overwritten)
@@ -255,6 +288,8 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     for (int i = 0; i < NA; ++i) u[i] = action_to_rpm(c, a[i]);
     // ahead of each (two tiles) or every other (one tile) right-hand side the
     // history sums of one or two unit tiles for the next step
+    __asm__ volatile("" ::: "memory");  // the body is read here, not ahead of the actor
+    const Body<float> B = park.body<EXTRAS>();
     rk4_step<float, EXTRAS>(B, c.arm, c.km, c.g, c.dt, renorm, x, u, [&](int k) {
       __builtin_amdgcn_sched_barrier(0);
       if (k % T_NN<TILES> == 0) tile_history<TILES>(fp, H, k, a1);
@@ -264,21 +299,27 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     ++t_ep;
     const uint32_t d = episode_end(c, x, t_ep);
     const bool rst = d && (c.flags & F_AUTORESET);
+    EpAcc acc = park.acc();
     acc.add(r, rst, t_ep);
+    park.put(acc);
     const uint64_t any = __ballot(rst);
     if (any) {  // wave uniform
       bool on[TILES];
 #pragma unroll
       for (int tl = 0; tl < TILES; ++tl) on[tl] = (any >> (16 * tl + li)) & 1u;
+      float aht[TILES];
+#pragma unroll
+      for (int tl = 0; tl < TILES; ++tl) aht[tl] = park[PK_AH + tl];
       H.fill(on, aht);
       history();
       if (rst) {
         ++ep;
         t_ep = 0;
         was_reset = true;
+        const float wh = park[PK_HOVER];
         if (have) {
 #pragma unroll
-          for (int i = 0; i < NRES; ++i) x[i] = nxp[i * T_MAX_THREADS];
+          for (int i = 0; i < NRES; ++i) x[i] = park[PK_NEXT + i];
 #pragma unroll
           for (int i = NRES; i < NS; ++i) x[i] = wh;
           have = false;
@@ -288,7 +329,9 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
         if (EXTRAS) {
           float dd[6];
           disturbance(c, (uint32_t)e, (uint32_t)ep, dd);
-          set_disturbance(B, dd);
+          Body<float> Bn = B;
+          set_disturbance(Bn, dd);
+          park.put(Bn);
         }
       }
     }
@@ -313,6 +356,7 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
   if (was_reset)
 #pragma unroll 1
     for (int s = 0; s < NH - t_ep; ++s) {
+      const float ah = rpm_to_action(c, park[PK_HOVER]);
       const float v[NA] = {ah, ah, ah, ah};
       store_ring<SUB>(b.ring, N, (head1 + s) & (NH - 1), osub, sub, v);
     }
@@ -320,7 +364,7 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     b.head[ef] = head1;
     b.t_ep[ef] = t_ep;
     b.ep[ef] = ep;
-    acc.store(b, N, ef);
+    park.acc().store(b, N, ef);
   }
 }
 
