@@ -10,9 +10,9 @@
 //      through reward, quaternion renormalisation, the four RK4 stages, the
 //      action map, the actor (on MFMA) and the history shift; per-env
 //      parameter gradients accumulate in registers; the layer cotangents
-//      dz1, dz2, dz3 of every (step, env) go to scratch;
+//      dz1 and dz3 of every (step, env) go to scratch;
 //   3. weight gradients (k_bwd_dw): sum over (step, env) rows of dz (x) input
-//      on fp32 MFMA, one workgroup per (64-env chunk, step group)
+//      on bf16 MFMA with split operands, one workgroup per (64-env chunk, step group)
 //      accumulating into its own partial; biases come from a constant-one
 //      input column.
 // Finally k_bwd_reduce adds the workgroup partials in a fixed order, so the
@@ -21,6 +21,8 @@
 // Fused multiply-adds only where one expression of the source holds the product
 // and the sum, so kernels that promise equal results round alike.
 #pragma clang fp contract(on)
+#include <type_traits>
+
 #include "qs_actor.h"
 #include "qs_backward.h"
 #include "qs_forward.h"
@@ -249,7 +251,7 @@ k_bwd_reverse(DevCfg c, const float* __restrict__ theta, const float* __restrict
     for (int i = 0; i < NA; ++i) d3[i] = ga[i] * (1.0f - cur.a[i] * cur.a[i]);
     const float d3e = k == 0 ? d3[0] : k == 1 ? d3[1] : k == 2 ? d3[2] : d3[3];
     const float d3k = active ? d3e : 0.0f;
-    if (!SPLIT || w == 0) bst1(d3k, rdz, vz1, sz + 4u * (2 * NHID) * RB);
+    if (!SPLIT || w == 0) bst1(d3k, rdz, vz1, sz + 4u * DZ_3 * RB);
     // do = W1^T dz1 in observation order: tile p, register r of quarter k is
     // the cotangent of feature PHI(4p + r, k)
     float dob[40];
@@ -263,7 +265,6 @@ k_bwd_reverse(DevCfg c, const float* __restrict__ theta, const float* __restrict
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           dz2[q][r] = (zm >> (8 * q + 4 + r)) & 1u ? dz2[q][r] : 0.0f;
-          bst1(dz2[q][r], rdz, vz4, sz + 4u * (NHID + 16 * q + r) * RB);
         }
       }
       // dz1 = (W2^T dz2) * [z1 > 0]
@@ -299,7 +300,6 @@ k_bwd_reverse(DevCfg c, const float* __restrict__ theta, const float* __restrict
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         d2[r] = (zm >> (8 * w + 4 + r)) & 1u ? d2[r] : 0.0f;
-        bst1(d2[r], rdz, vz4, sz + 4u * (NHID + 16 * w + r) * RB);
       }
       put(xd2, d2);
       __syncthreads();
@@ -352,68 +352,54 @@ k_bwd_reverse(DevCfg c, const float* __restrict__ theta, const float* __restrict
 
 // Weight gradients of one segment: for every (step, env) row,
 //   dW1 += dz1 o^T, dW2 += dz2 relu(z1)^T, dW3 += dz3 relu(z2)^T, db += dz,
-// the rows being the contraction dimension.  Most of the work runs on fp32
-// MFMA (v_mfma_f32_16x16x4f32): A[i][k] (lane i + 16 k) = dz of neuron
-// 16 n + i at env e0 + k, B[k][j] = input column 16 t + j at the same env;
-// result register r of a tile holds neuron 16 n + 4 lg + r, column 16 t + li.
+// the rows being the contraction dimension.  The products run on bf16 matrix
+// cores with both operands split (qs_tile.h), 32 envs a product: A[i][k] (lane
+// i + 16 lg, 8 elements) = dz of neuron 16 n + i, B[k][j] = input column 16 t + j,
+// element e of both at env 32 s + 16 (e / 4) + 4 lg + e % 4 of slab pair s; result
+// register r of a tile holds neuron 16 n + 4 lg + r, column 16 t + li.
 //
 // One workgroup of 8 waves per (64-env block, step group).  The input
-// columns fall in column tiles of 16: layer 1's 146 columns make the full
-// tiles 0..8 and the 2 columns 144, 145; layer 2's 64 columns the tiles
-// 10..13.  Waves g and g + 4 run column group g on alternate steps (two
-// waves per SIMD, so one's loads overlap the other's matrix work) and add
-// their sums through LDS at the end, half 0 first.  A group owns three full
-// tiles with their 4 neuron tiles -- {g, g + 4} of layer 1 and 10 + g of
-// layer 2 -- and neuron tile g of the shared tile 8, so each group issues the
-// same 52 products per 16-env slab and no product multiplies padding.  The
-// rest is small: group 0 takes layer 1's last two columns and its bias
-// (16-block v_mfma_f32_4x4x1f32, block b = neurons 4 b .. 4 b + 3, one
-// product per env: D[i][j] in lane 4 b + j, register i, is neuron 4 b + i,
-// column 144 + j, with column 146 the constant one), group 2 layer 3 (the
-// same shape with block b = columns 4 b .. 4 b + 3: lane l, register o holds
-// output o, column l) and layer 3's bias, every group layer 2's bias of its
-// neuron tile (vector adds of the A operands it already holds).  The dz rows
-// (A operands, the same for the four groups of a half) are loaded once per
-// step by the half's four waves together, whole 256-byte rows per lane
-// group, and staged in LDS; each wave loads its own input columns (B
-// operands) from the record or the LDS copy of the action tape, one 16-env
-// slab ahead.  The history features of o_t are the actions of the 32
+// columns fall in column tiles of 16: layer 1's 146 columns and its constant one
+// (the bias) make the tiles 0..9, layer 2's 64 columns the tiles 10..13, layer
+// 3's the tiles 14..17.  Waves g and g + 4 run column group g on the two slab
+// pairs of each step (two waves per SIMD, so one's loads and splitting overlap
+// the other's matrix work) and add their sums through LDS at the end, half 0
+// first.  A group owns three tiles with their 4 neuron tiles -- {g, g + 4} of
+// layer 1 and 10 + g of layer 2 --, neuron tile g of the shared tiles 8 and 9, tile
+// 14 + g of layer 3 (A's rows are the 4 outputs, repeated) and layer 2's bias of
+// its neuron tile (a product with ones; group 2 layer 3's too), so the groups
+// issue the same products.  The dz rows (A operands, the same for the four groups)
+// are loaded once per step by the eight waves together, whole 256-byte rows
+// per lane group, split once and staged in LDS; each wave loads its own input
+// columns (B operands) from the record or the LDS copy of the action tape and
+// splits them.  The history features of o_t are the actions of the 32
 // previous steps, read from the segment's action tape (one contiguous span
 // per 64-env block).
-constexpr int DW_SPLIT = 8;  // the column tile shared by the four groups
-constexpr int DW_NB = 4;     // B operands of a slab: three full tiles, the shared one
-// accumulators (f4) of a wave: full tile i, neuron tile n at 4 i + n, then
-// the shared tile, layer 2's bias, the small products and layer 3's bias
-constexpr int DW_A_SHARED = 12, DW_A_B2 = 13, DW_A_SMALL = 14, DW_A_B3 = 15, DW_NACC = 16;
-constexpr int DW_COL_SMALL = 16 * (DW_SPLIT + 1);  // first layer-1 column of the small products
+//
+// A step of 65536 envs reads 58 MB (11 us at a copy's rate) and takes 6 us of
+// products and 8 us of vector instructions per SIMD, mostly splitting: 17 us, as
+// the two waves of a SIMD meet at a barrier every step.  It took 21 us with fp32
+// products (13 us of them) and dz2 read from memory (16384 envs: 5.6, now 4.7).
+constexpr int DW_GL = 3;  // B operands a group may read from the record: i of dw_tile
+// accumulators (f4) of a wave: tile i < 3, neuron tile n at 4 i + n, the shared
+// tiles 8 and 9, layer 3's tile, and the biases (layer 2's in columns 0..7,
+// layer 3's in columns 8..15 of group 2)
+constexpr int DW_A_T8 = 12, DW_A_T9 = 13, DW_A_L3 = 14, DW_A_BIAS = 15, DW_NACC = 16;
+constexpr int DW_T9 = 16 * 9;  // first column of tile 9: two columns, then the constant one
 
-// column tile of B slot i of group G
-__host__ __device__ constexpr int dw_tile(int G, int i) {
-  return i < 2 ? G + 4 * i : i == 2 ? 10 + G : DW_SPLIT;
-}
-static_assert(dw_tile(3, 1) == 7 && dw_tile(0, 2) == 10 && dw_tile(3, 2) == 13 &&
-                  DW_COL_SMALL + 2 == NO,
+// column tile of operand i < 3 of group G
+__host__ __device__ constexpr int dw_tile(int G, int i) { return i < 2 ? G + 4 * i : 10 + G; }
+static_assert(dw_tile(3, 1) == 7 && dw_tile(0, 2) == 10 && dw_tile(3, 2) == 13 && DW_T9 + 2 == NO,
               "column groups");
 
-// B operands of a slab; group 2's small products take z2 row l of the
-// lane for the slab's env quads 0..3 from the record
-struct DwOps {
-  f4 b[DW_NB];
-  f4 z[4];
-};
-// A operands of a slab and the small products' A (env quads 0..3 of the
-// slab), with group 0's small B (its tape columns), all read from LDS
-struct DwA {
-  f4 a1[4], a2[4];
-  f4 sa[4], sb[4];
-};
-
-// LDS staging of one step's dz rows for a half: DZ_F rows of 64 envs, pitch
-// DW_AP floats (the 4 extra floats put the 16 rows one ds_read_b128 touches
-// on distinct banks).  Wave g of the half loads rows DW_AW g .. DW_AW g +
-// DW_AW - 1, four rows per instruction.
-constexpr int DW_AP = RB + 4, DW_AW = (DZ_F + 3) / 4, DW_AL = (DW_AW + 3) / 4;
-constexpr int DW_ABUF = DZ_F * DW_AP;  // floats per half
+// LDS staging of one step's dz rows for a half: [part][row][64 envs] in bf16, a
+// row's eight 16-byte granules (4 s + lg: the operand of slab pair s, lane group
+// lg) permuted by its index, so that the 16 rows a read touches lie on distinct
+// banks.
+constexpr int DW_ROWS = 2 * NHID + NA;  // dz1, dz2, dz3
+constexpr int DW_PART = DW_ROWS * 128, DW_ABUF = T_P * DW_PART / 4;  // bytes; floats per half
+__device__ inline int dw_granule(int row, int gr) { return row * 128 + 16 * (gr ^ ((row >> 1) & 7)); }
+constexpr int DW_AP = RB + 4;  // pitch of the tape window: rows on distinct banks
 
 __device__ inline f4 const4(float v) { return f4{v, v, v, v}; }
 
@@ -428,92 +414,59 @@ __device__ inline f4 bld4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff
   return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
 }
 
-// Tiles 1..8 hold history columns: tile 1 mixes the last two state features
+// Tiles 1..9 hold history columns: tile 1 mixes the last two state features
 // with history and is read from the record with a per-lane offset (the
-// source step depends on the column); tiles 2..8 hold action-tape values
+// source step depends on the column); tiles 2..9 hold action-tape values
 // only and read an LDS copy of the block's tape window: the DW_CH steps [w0,
 // w0 + DW_CH) observe slots w0 .. w0 + DW_CH + NH - 2, which the workgroup
 // copies in (rows (slot - w0) * NA + a, pitch DW_AP) and refills every
 // DW_CH steps, so each tape value is read from memory once per window
 // instead of once for each of the 32 steps that observe it.
 constexpr int DW_CH = 16, DW_TW = (DW_CH + NH) * NA, DW_TBUF = DW_TW * DW_AP;
-static_assert(DW_CH % 2 == 0, "a window holds whole iterations (one step per half)");
-__host__ __device__ constexpr bool dw_tape(int t) { return t >= 2 && t <= DW_SPLIT; }
 
-// Addressing of one step, in bytes from the dz and record buffers: uniform
-// offsets of this step's block, the per-lane offset of tile 1 (group 1), and
-// in floats from the LDS tape window (w0 its first slot) those of the tape
-// tiles and of group 0's small B operands (tape rows of columns 144, 145).
-// Group 2's small B operands (relu(z2) row l of the lane) need no per-step
-// lane offset.
+// The record's B operands of a slab pair: tiles dw_tile(G, 0), dw_tile(G, 2) and
+// 14 + G, two slabs each.
+struct DwOps {
+  f4 v[DW_GL][2];
+};
+// Offsets of one step: of this step's block in the record (bytes, wave uniform),
+// the lane's of tile 1 (group 1), and the step's first row of the tape window.
 struct DwAddr {
-  uint32_t dzs, rs;
-  uint32_t h[DW_NB];
-  uint32_t hs;
+  uint32_t rs, h1;
+  int tape;
 };
 
 template <int G>
 __device__ inline void dw_addr(DwAddr& d, int tl, int n, int chunk, int N, int lane, int w0) {
   const int li = lane & 15, lg = lane >> 4;
   const uint32_t rbp = (uint32_t)rb_pad(N), rstep = (uint32_t)REC_F * rbp;
-  d.dzs = 4u * ((uint32_t)tl * (DZ_F * rbp) + (uint32_t)chunk * (DZ_F * RB));
-  d.rs = 4u * ((uint32_t)tl * rstep + (uint32_t)chunk * (REC_F * RB));
-  const uint32_t c4 = 4 * lg;
-  const uint32_t rbo = (uint32_t)tl * rstep + (uint32_t)chunk * (REC_F * RB) + c4;
-  // this block's action tape; history slot sl of step tl is tape slot tl + sl
-  const uint32_t tape = (uint32_t)n * rstep + (uint32_t)chunk * ((NH + n) * NA * RB) + c4;
-#pragma unroll
-  for (int i = 0; i < DW_NB; ++i) {
-    const int t = dw_tile(G, i), col = 16 * t + li;
-    if (dw_tape(t)) {
-      // window row of history column hc: (tl + hc / NA - w0) NA + hc % NA
-      d.h[i] = (uint32_t)(((tl - w0) * NA + col - 18) * DW_AP + 4 * lg);
-    } else if (t == 1) {
-      const int hc = col < 18 ? 0 : col - 18;
-      const uint32_t o_hist = tape + (uint32_t)((tl + (hc >> 2)) * NA + (hc & 3)) * RB;
-      d.h[i] = 4u * (col < 18 ? rbo + (REC_O + col) * RB : o_hist);
-    } else {
-      d.h[i] = 0;
-    }
-  }
-  // group 0: lane 4 b + j takes column 144 + j (j = 2, 3: constants, any
-  // valid row)
-  const int j = lane & 3;
-  d.hs = G == 0 ? (uint32_t)(((tl - w0) * NA + DW_COL_SMALL - 18 + (j < 2 ? j : 0)) * DW_AP) : 0u;
-}
-
-// Issues the record B loads of slab q of a step; dw_prepare finishes the
-// operands when they are used, so the loads stay in flight during the
-// previous slab's matrix work.  loff: the lane's byte offset 4 (li * RB +
-// 4 lg).
-template <int G>
-__device__ inline void dw_load_slab(DwOps& o, __amdgpu_buffer_rsrc_t rrec, const DwAddr& d,
-                                    uint32_t loff, int q) {
-  if (G == 2) {
-    // z2 row l, envs 16 q + 4 k .. + 3 (64 rows of 16 bytes per load)
-    const uint32_t lo = 4u * (uint32_t)((threadIdx.x & 63) * RB);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o.z[k] = bld4(rrec, lo + 64 * q + 16 * k, d.rs + 4 * (REC_Z2 * RB));
-  }
-#pragma unroll
-  for (int i = 0; i < DW_NB; ++i) {
-    const int t = dw_tile(G, i);
-    if (dw_tape(t)) continue;
-    if (t == 1) {
-      o.b[i] = bld4(rrec, d.h[i] + 64 * q, 0);
-    } else {
-      const int row = t == 0 ? REC_O : REC_Z1 + 16 * (t - 10);
-      o.b[i] = bld4(rrec, loff + 64 * q, d.rs + 4 * (row * RB));
-    }
+  const uint32_t blk = (uint32_t)tl * rstep + (uint32_t)chunk * (REC_F * RB);
+  d.rs = 4u * blk;
+  d.tape = (tl - w0) * NA;
+  d.h1 = 0;
+  if (G == 1) {
+    // history slot sl of step tl is tape slot tl + sl of the block
+    const uint32_t tape = (uint32_t)n * rstep + (uint32_t)chunk * ((NH + n) * NA * RB);
+    const int hc = li < 2 ? 0 : li - 2;
+    const uint32_t o_hist = tape + (uint32_t)((tl + (hc >> 2)) * NA + (hc & 3)) * RB;
+    d.h1 = 4u * (4 * lg + (li < 2 ? blk + (REC_O + 16 + li) * RB : o_hist));
   }
 }
 
-// The tape B operands of slab q from the LDS window.
+// Issues the record's B loads of slab pair s of a step; they are split when they
+// are used, so the loads stay in flight during the previous pair's matrix work.
+// loff: the lane's byte offset 4 (li * RB + 4 lg).
 template <int G>
-__device__ inline void dw_load_tape(DwOps& o, const float* tw, const DwAddr& d, int q) {
+__device__ inline void dw_load_pair(DwOps& o, __amdgpu_buffer_rsrc_t rrec, const DwAddr& d,
+                                    uint32_t loff, int s) {
 #pragma unroll
-  for (int i = 0; i < DW_NB; ++i)
-    if (dw_tape(dw_tile(G, i))) o.b[i] = *reinterpret_cast<const f4*>(&tw[d.h[i] + 16 * q]);
+  for (int q = 0; q < 2; ++q) {
+    const uint32_t b = 128 * s + 64 * q;
+    if (G == 0) o.v[0][q] = bld4(rrec, loff + b, d.rs + 4 * (REC_O * RB));
+    if (G == 1) o.v[0][q] = bld4(rrec, d.h1 + b, 0);
+    o.v[1][q] = bld4(rrec, loff + b, d.rs + 4 * ((REC_Z1 + 16 * G) * RB));
+    o.v[2][q] = bld4(rrec, loff + b, d.rs + 4 * ((REC_Z2 + 16 * G) * RB));
+  }
 }
 
 // Copies tape slots [w0, w0 + DW_CH + NH) of 64-env block `chunk` (those
@@ -542,126 +495,193 @@ __device__ inline void dw_stage_tape(float* tw, __amdgpu_buffer_rsrc_t rrec, int
   }
 }
 
-// This wave's share of step tl's dz rows (whole rows: lane l takes envs
-// 4 (l & 15) .. + 3 of row DW_AW g + 4 j + (l >> 4)); rows past the share
-// load a valid row and are not stored.
-__device__ inline void dw_a_load(f4 an[DW_AL], __amdgpu_buffer_rsrc_t rdz, int tl, int chunk,
-                                 int N, int g, int lane) {
+// A wave's share of a step's dz rows, wave g of half h: neurons 16 g + 8 h .. + 7
+// of layers 1 and 2 (lane l takes envs 4 (l & 15) .. + 3 of neuron 16 g + 8 h + 4 j
+// + (l >> 4), j < 2) and, of half 0, row g of layer 3.  dz2 is formed here, (W3^T
+// dz3) [z2 > 0] from dz3 and the record's mask words: it takes neither a store in
+// the sweep nor a load.
+struct DwRows {
+  f4 d1[2], d3[4], m[2];
+};
+__device__ inline void dw_a_load(DwRows& r, __amdgpu_buffer_rsrc_t rdz,
+                                 __amdgpu_buffer_rsrc_t rrec, int tl, int chunk, int N, int g,
+                                 int h, int lane) {
   const uint32_t rbp = (uint32_t)rb_pad(N);
   const uint32_t so = 4u * ((uint32_t)tl * (DZ_F * rbp) + (uint32_t)chunk * (DZ_F * RB));
+  const uint32_t ro = 4u * ((uint32_t)tl * (REC_F * rbp) + (uint32_t)chunk * (REC_F * RB));
+  const uint32_t v = 16u * (uint32_t)(lane & 15), vr = v + 4u * (uint32_t)((lane >> 4) * RB);
 #pragma unroll
-  for (int j = 0; j < DW_AL; ++j) {
-    int r = DW_AW * g + 4 * j + (lane >> 4);
-    r = r < DZ_F ? r : DZ_F - 1;
-    an[j] = bld4(rdz, 4u * (uint32_t)(r * RB + 4 * (lane & 15)), so);
+  for (int j = 0; j < 2; ++j) {
+    r.d1[j] = bld4(rdz, vr, so + 4u * (uint32_t)((16 * g + 8 * h + 4 * j) * RB));
+    r.m[j] = bld4(rrec, v, ro + 4u * (uint32_t)((REC_M + 2 * h + j) * RB));
   }
+#pragma unroll
+  for (int i = 0; i < NA; ++i) r.d3[i] = bld4(rdz, v, so + 4u * (uint32_t)((DZ_3 + i) * RB));
 }
-__device__ inline void dw_a_store(const f4 an[DW_AL], float* sA, int g, int lane) {
-#pragma unroll
-  for (int j = 0; j < DW_AL; ++j) {
-    const int jr = 4 * j + (lane >> 4), r = DW_AW * g + jr;
-    if (jr < DW_AW && r < DZ_F) *reinterpret_cast<f4*>(&sA[r * DW_AP + 4 * (lane & 15)]) = an[j];
-  }
+// Where a wave's rows go: envs 4 m .. 4 m + 3 of a row lie in granule 4 (m / 8) +
+// m % 4, its half (m / 4) % 2.  off: the byte offset of neuron 16 g + 8 h + (l >> 4)
+// of layer 1 (four neurons further: + 512, with the permutation's bit 1 turned).
+struct DwPlace {
+  int off, off3;
+};
+__device__ inline DwPlace dw_place(int g, int h, int lane) {
+  const int m = lane & 15, gr = 4 * (m >> 3) + (m & 3), half = 8 * ((m >> 2) & 1);
+  return {dw_granule(16 * g + 8 * h + (lane >> 4), gr) + half, dw_granule(2 * NHID + g, gr) + half};
 }
-// A operands of slab q from the staged rows, and the small products'
-// operands of envs 16 q + 4 k .. + 3 held in LDS: group 0 A = dz1 row l, B =
-// the tape rows of columns 144 + (l & 3) at window offset hs (lanes with
-// l & 3 >= 2 take constants, set by dw_prepare); group 2 A = dz3 row l & 3.
-template <int G>
-__device__ inline void dw_read_a(DwA& a, const float* sA, const float* tw, uint32_t hs, int q,
-                                 int lane) {
-  const int li = lane & 15, c = 16 * q + 4 * (lane >> 4);
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    a.a1[nt] = *reinterpret_cast<const f4*>(&sA[(16 * nt + li) * DW_AP + c]);
-    a.a2[nt] = *reinterpret_cast<const f4*>(&sA[(NHID + 16 * nt + li) * DW_AP + c]);
-  }
-  if (G == 0 || G == 2) {
-    const int row = G == 0 ? lane : 2 * NHID + (lane & 3);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      a.sa[k] = *reinterpret_cast<const f4*>(&sA[row * DW_AP + 16 * q + 4 * k]);
-      if (G == 0) a.sb[k] = *reinterpret_cast<const f4*>(&tw[hs + 16 * q + 4 * k]);
-    }
-  }
-}
-
-// ReLU of the pre-activation columns, the constant columns of group 0's
-// small products (one at the bias column 146, zero at 147) and the
-// forward's bf16 rounding of its inputs.  Envs >= N of the last block need
-// nothing: their dz slots are zero (cleared at allocation; the
-// one-env-per-lane sweep writes zeros there) and their record slots are
-// zero or finite copies of a batch env's values (the one-env-per-lane
-// forward writes those), so they add nothing.
-template <int G, bool BF16>
-__device__ inline void dw_prepare(DwOps& o, DwA& a, int lane) {
-#pragma unroll
-  for (int i = 0; i < DW_NB; ++i) {
-    const int t = dw_tile(G, i);
+// Splits and stages piece q of the share: neurons + 4 q of layer 1 (q < 2), + 4 (q -
+// 2) of layer 2 (q < 4), layer 3's row (q = 4).  w3[neuron]: layer 3's four weights
+// of it.
+template <int Q>
+__device__ inline void dw_stage(const DwRows& r, const f4* w3, char* sA, const DwPlace& at, int g,
+                                int h, int lane) {
+  constexpr int J = Q & 1;
+  f4 v;
+  if (Q < 2) {
+    v = r.d1[J];
+  } else if (Q < 4) {
+    const f4 w = w3[16 * g + 8 * h + 4 * J + (lane >> 4)];
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
-      float v = t < 10 ? o.b[i][m] : relu_bits(o.b[i][m]);
-      if (BF16) v = (float)(__bf16)v;
-      o.b[i][m] = v;
+      float d = w[0] * r.d3[0][m];
+#pragma unroll
+      for (int i = 1; i < NA; ++i) d = fmaf(w[i], r.d3[i][m], d);
+      // neuron 16 g + 4 k + i: bit 8 g + 4 + i of word k
+      v[m] = keep_if(d, __float_as_uint(r.m[J][m]) >> (lane >> 4), 8 * g + 4);
     }
+  } else {
+    v = r.d3[g];
   }
-  if (G == 0 || G == 2) {
-    const int j = lane & 3;
+  uint32_t p[T_P], q[T_P];
+  split_pair(v[0], v[1], p);
+  split_pair(v[2], v[3], q);
+  char* a = sA + (Q == 4 ? at.off3 : (at.off ^ (32 * J)) + 512 * J + (Q < 2 ? 0 : NHID * 128));
+  if (Q < 4 || (h == 0 && lane < 16))
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        float v = G == 2 ? relu_bits(o.z[k][m]) : a.sb[k][m];
-        if (BF16) v = (float)(__bf16)v;
-        if (G == 2)
-          o.z[k][m] = v;
-        else
-          a.sb[k][m] = j < 2 ? v : j == 2 ? 1.0f : 0.0f;
-      }
-  }
+    for (int s = 0; s < T_P; ++s) *reinterpret_cast<uint2*>(a + s * DW_PART) = uint2{p[s], q[s]};
 }
 
-// The products of one slab: m walks the four envs a lane group holds
-// (16x16x4: K = the four lane groups), k and m the 16 envs one at a time
-// (4x4x1: K = one env).
-template <int G>
-__device__ inline void dw_mfma(f4* acc, float* bs, const DwOps& o, const DwA& A) {
+// B operand of a slab pair from its two slabs: ReLU of the pre-activation columns
+// (RELU) and the forward's bf16 rounding of its inputs (BF16: one part).  Envs >=
+// N of the last block need nothing: their dz slots are zero (cleared at
+// allocation; the sweeps write zeros there) and their record slots are zero or
+// finite copies of a batch env's values, so they add nothing.
+template <bool RELU, bool BF16>
+__device__ inline void dw_operand(f4 lo, f4 hi, u4t (&x)[T_P]) {
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const int t = dw_tile(G, i);
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt)
-        acc[4 * i + nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-            t < 10 ? A.a1[nt][m] : A.a2[nt][m], o.b[i][m], acc[4 * i + nt], 0, 0, 0);
+    if (RELU) {
+      lo[m] = relu_bits(lo[m]);
+      hi[m] = relu_bits(hi[m]);
     }
-    acc[DW_A_SHARED] = __builtin_amdgcn_mfma_f32_16x16x4f32(A.a1[G][m], o.b[3][m],
-                                                            acc[DW_A_SHARED], 0, 0, 0);
   }
-  if (G == 0 || G == 2) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int m = 0; m < 4; ++m)
-        acc[DW_A_SMALL] = __builtin_amdgcn_mfma_f32_4x4x1f32(
-            A.sa[k][m], G == 2 ? o.z[k][m] : A.sb[k][m], acc[DW_A_SMALL], 0, 0, 0);
+  if (BF16) {
+    x[0] = u4t{pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3]), pack_bf16(hi[0], hi[1]),
+               pack_bf16(hi[2], hi[3])};
+  } else {
+    hidden_operand(lo, hi, x);
   }
-  // biases: layer 2's of neuron tile G (bs[0]), layer 3's (group 2, bs[1])
-  bs[0] += (A.a2[G][0] + A.a2[G][1]) + (A.a2[G][2] + A.a2[G][3]);
-  if (G == 2) {
+}
+// The products of A operand a with M B operands: the small terms first.
+template <int M, bool BF16>
+__device__ inline void dw_products(f4* acc, const u4t (&a)[T_P], const u4t (*x)[T_P]) {
+  constexpr int AP[6] = {2, 0, 1, 1, 0, 0}, XP[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
-    for (int k = 0; k < 4; ++k) bs[1] += (A.sa[k][0] + A.sa[k][1]) + (A.sa[k][2] + A.sa[k][3]);
+  for (int k = 0; k < 6; ++k) {
+    if (BF16 && XP[k] > 0) continue;
+#pragma unroll
+    for (int i = 0; i < M; ++i) acc[i] = mfma_bf(a[AP[k]], x[i][XP[k]], acc[i]);
   }
 }
 
-// This half's steps t_lo + half, t_lo + half + 2, ... of the group, the four
-// 16-env slabs of a step in turn, each slab's B loads issued one slab ahead
-// into the other of two operand buffers (a copy between them would wait for
-// the loads in flight), the next step's dz share loaded during this step and
-// staged after it.  Both halves run the same number of iterations (every
-// wave meets every barrier); a half without a step left reads a valid step
-// and skips the products.  sA: this half's staging buffer.
+// Slab pair s of a step.  sA: the step's staged rows; tw: the tape window; tape:
+// the step's first row in it.  stage(q), q < 5: the pieces of the next step's
+// staging, placed where matrix instructions can cover them.
+template <int G, bool BF16, typename Stage>
+__device__ inline void dw_pair(f4* acc, const DwOps& o, const char* sA, const float* tw, int tape,
+                               int s, int lane, Stage&& stage) {
+  const int li = lane & 15, lg = lane >> 4;
+  // the A operands of rows row0 + li, row0 a multiple of 16
+  const char* la = sA + dw_granule(li, 4 * s + lg);
+  const auto rows = [&](int row0, u4t (&a)[T_P]) {
+#pragma unroll
+    for (int p = 0; p < T_P; ++p)
+      a[p] = *reinterpret_cast<const u4t*>(la + row0 * 128 + p * DW_PART);
+  };
+  // tile t of the tape window: history columns 16 t - 18 ..
+  const auto tape_tile = [&](int t, u4t (&x)[T_P]) {
+    const int c = t == 9 && li >= 2 ? 0 : li;
+    const float* w = tw + (tape + 16 * t - 18 + c) * DW_AP + 32 * s + 4 * lg;
+    f4 lo = *reinterpret_cast<const f4*>(w), hi = *reinterpret_cast<const f4*>(w + 16);
+    if (t == 9) {
+      const float one = li == 2 ? 1.0f : 0.0f;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        lo[m] = li < 2 ? lo[m] : one;
+        hi[m] = li < 2 ? hi[m] : one;
+      }
+    }
+    dw_operand<false, BF16>(lo, hi, x);
+  };
+  // Neuron tiles in the outer loop: two operands of 12 registers a side at a time.
+  u4t a[2][T_P], x[2][T_P], y[2][T_P];
+  if (G < 2)
+    dw_operand<false, BF16>(o.v[0][0], o.v[0][1], x[0]);
+  else
+    tape_tile(G, x[0]);
+  tape_tile(G + 4, x[1]);
+  rows(0, a[0]);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    if (n < 3) rows(16 * (n + 1), a[(n + 1) & 1]);
+    f4 c[2] = {acc[n], acc[4 + n]};
+    dw_products<2, BF16>(c, a[n & 1], x);
+    acc[n] = c[0];
+    acc[4 + n] = c[1];
+    if (n == 0) tape_tile(8, y[0]);
+    if (n == 1) tape_tile(9, y[1]);
+    if (n == 2) stage(std::integral_constant<int, 0>());
+    if (n == 3) stage(std::integral_constant<int, 1>());
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  rows(16 * G, a[0]);
+  dw_products<2, BF16>(acc + DW_A_T8, a[0], y);
+  dw_operand<true, BF16>(o.v[1][0], o.v[1][1], x[0]);
+  stage(std::integral_constant<int, 4>());
+  rows(NHID, a[0]);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    if (n < 3) rows(NHID + 16 * (n + 1), a[(n + 1) & 1]);
+    dw_products<1, BF16>(acc + 8 + n, a[n & 1], x);
+    if (n == 0) stage(std::integral_constant<int, 2>());
+    if (n == 1) stage(std::integral_constant<int, 3>());
+    if (n == 2) dw_operand<true, BF16>(o.v[2][0], o.v[2][1], x[1]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // layer 3: rows 128 + li % 4
+  u4t a3[T_P], ag[T_P];
+#pragma unroll
+  for (int p = 0; p < T_P; ++p)
+    a3[p] = *reinterpret_cast<const u4t*>(sA + dw_granule(2 * NHID + (li & 3), 4 * s + lg) +
+                                          p * DW_PART);
+  rows(NHID + 16 * G, ag);
+  dw_products<1, BF16>(acc + DW_A_L3, a3, x + 1);
+  // biases
+  const uint32_t one = 0x3f803f80u, b2 = li < 8 ? one : 0u, b3 = li < 8 ? 0u : one;
+#pragma unroll
+  for (int p = T_P - 1; p >= 0; --p) {
+    acc[DW_A_BIAS] = mfma_bf(ag[p], u4t{b2, b2, b2, b2}, acc[DW_A_BIAS]);
+    if (G == 2) acc[DW_A_BIAS] = mfma_bf(a3[p], u4t{b3, b3, b3, b3}, acc[DW_A_BIAS]);
+  }
+}
+
+// Steps t_lo .. t_hi - 1 of the group, half h taking slab pair h of each.  A step's
+// B loads are issued one step ahead into the other of two operand buffers (a copy
+// between them would wait for the loads in flight); its dz share is loaded two
+// steps ahead and staged one ahead, beside the products, into the other of two
+// staging buffers: one barrier a step, and no phase that only stages.
+// sA: the staging buffers.
 // Barrier discipline: the four column groups run separate instantiations of
 // this loop, so their waves reach the workgroup barriers at different
 // program locations; the hardware barrier counts arriving waves, and every
@@ -671,86 +691,66 @@ __device__ inline void dw_mfma(f4* acc, float* bs, const DwOps& o, const DwA& A)
 // barriers in uniform code, but it keeps every group's operand slots live
 // across the switch and spills.
 template <int G, bool BF16>
-__device__ inline void dw_accumulate(f4* acc, float* bs, const float* __restrict__ rec,
+__device__ inline void dw_accumulate(f4* acc, const float* __restrict__ rec,
                                      const float* __restrict__ dz, int N, int chunk, int t_lo,
-                                     int t_hi, int n, int half, float* sA, float* tw) {
+                                     int t_hi, int n, int half, char* sA, float* tw,
+                                     const f4* w3) {
   const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
-  const int iters = (t_hi - t_lo + 1) / 2;  // half 0's steps, the same in every wave
+  const int iters = t_hi - t_lo;
   if (iters <= 0) return;
   const uint32_t rbp = (uint32_t)rb_pad(N);
   const __amdgpu_buffer_rsrc_t rrec =
       buf_rsrc(rec, 4u * ((uint32_t)n * REC_F * rbp + (uint32_t)(NH + n) * NA * rbp));
   const __amdgpu_buffer_rsrc_t rdz = buf_rsrc(dz, 4u * ((uint32_t)n * DZ_F * rbp));
   const uint32_t loff = 4u * (uint32_t)(li * RB + 4 * lg);
-  auto step = [&](int i) {
-    const int t = t_lo + half + 2 * i;
-    return t < t_hi ? t : t_hi - 1;
-  };
+  const DwPlace at = dw_place(G, half, lane);
+  const auto step = [&](int i) { return t_lo + (i < iters ? i : iters - 1); };
   int w0 = t_lo;  // first slot of the tape window
   dw_stage_tape(tw, rrec, chunk, n, N, w0);
-  f4 an[DW_AL];
-  dw_a_load(an, rdz, step(0), chunk, N, G, lane);
-  dw_a_store(an, sA, G, lane);
-  __syncthreads();
+  DwRows an;
+  dw_a_load(an, rdz, rrec, step(0), chunk, N, G, half, lane);
+  const auto stage_to = [&](char* a) {
+    return [&, a](auto q) { dw_stage<decltype(q)::value>(an, w3, a, at, G, half, lane); };
+  };
+  {
+    const auto st = stage_to(sA);
+    st(std::integral_constant<int, 0>());
+    st(std::integral_constant<int, 1>());
+    st(std::integral_constant<int, 2>());
+    st(std::integral_constant<int, 3>());
+    st(std::integral_constant<int, 4>());
+  }
   DwOps ob0, ob1;
-  DwA A;
   DwAddr d;
   dw_addr<G>(d, step(0), n, chunk, N, lane, w0);
-  dw_load_slab<G>(ob0, rrec, d, loff, 0);
-  dw_load_tape<G>(ob0, tw, d, 0);
-  // scheduling barriers keep each slab's loads ahead of the previous slab's
-  // matrix work (left alone, the scheduler interleaves a slab's products
-  // with its own loads and the waits then cover the loads just issued)
-  for (int i = 0; i < iters; ++i) {
-    const bool live = t_lo + half + 2 * i < t_hi;
-    const bool more = i + 1 < iters;
-    // unconditional (the last iteration reloads its own step): a load under
-    // a branch would leave the waits below counting it conservatively
-    dw_a_load(an, rdz, step(more ? i + 1 : i), chunk, N, G, lane);
-    dw_load_slab<G>(ob1, rrec, d, loff, 1);
-    dw_load_tape<G>(ob1, tw, d, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    dw_read_a<G>(A, sA, tw, d.hs, 0, lane);
-    dw_prepare<G, BF16>(ob0, A, lane);
-    if (live) dw_mfma<G>(acc, bs, ob0, A);
-    __builtin_amdgcn_sched_barrier(0);
-    dw_load_slab<G>(ob0, rrec, d, loff, 2);
-    dw_load_tape<G>(ob0, tw, d, 2);
-    __builtin_amdgcn_sched_barrier(0);
-    dw_read_a<G>(A, sA, tw, d.hs, 1, lane);
-    dw_prepare<G, BF16>(ob1, A, lane);
-    if (live) dw_mfma<G>(acc, bs, ob1, A);
-    __builtin_amdgcn_sched_barrier(0);
-    dw_load_slab<G>(ob1, rrec, d, loff, 3);
-    dw_load_tape<G>(ob1, tw, d, 3);
-    __builtin_amdgcn_sched_barrier(0);
-    dw_read_a<G>(A, sA, tw, d.hs, 2, lane);
-    dw_prepare<G, BF16>(ob0, A, lane);
-    if (live) dw_mfma<G>(acc, bs, ob0, A);
-    __builtin_amdgcn_sched_barrier(0);
-    // slab 3's small-product tape rows are this step's (d moves on below)
-    const uint32_t hs = d.hs;
+  dw_load_pair<G>(ob0, rrec, d, loff, half);
+  dw_a_load(an, rdz, rrec, step(1), chunk, N, G, half, lane);
+  __syncthreads();
+  // One step: operands cur, the next step's into nxt.  Loads past the last step
+  // read it again (a load under a branch would leave the waits counting it
+  // conservatively).
+  const auto body = [&](const DwOps& cur, DwOps& nxt, int i) {
+    const int tape = d.tape;
     // the next step's window (refilled below when the next step opens one)
-    const bool refill = more && (i + 1) % (DW_CH / 2) == 0;
+    const bool refill = i + 1 < iters && (i + 1) % DW_CH == 0;
     const int w0n = refill ? w0 + DW_CH : w0;
-    dw_addr<G>(d, step(more ? i + 1 : i), n, chunk, N, lane, w0n);
-    dw_load_slab<G>(ob0, rrec, d, loff, 0);
+    dw_addr<G>(d, step(i + 1), n, chunk, N, lane, w0n);
+    dw_load_pair<G>(nxt, rrec, d, loff, half);
     __builtin_amdgcn_sched_barrier(0);
-    dw_read_a<G>(A, sA, tw, hs, 3, lane);
-    dw_prepare<G, BF16>(ob1, A, lane);
-    if (live) dw_mfma<G>(acc, bs, ob1, A);
+    dw_pair<G, BF16>(acc, cur, sA + (i & 1) * (4 * DW_ABUF), tw, tape, half, lane,
+                     stage_to(sA + (~i & 1) * (4 * DW_ABUF)));
     __builtin_amdgcn_sched_barrier(0);
-    if (more) {
-      __syncthreads();  // every wave is done with this step's staged rows
-      dw_a_store(an, sA, G, lane);
-      if (refill) {
-        w0 = w0n;
-        dw_stage_tape(tw, rrec, chunk, n, N, w0);
-      }
-      __syncthreads();
+    dw_a_load(an, rdz, rrec, step(i + 2), chunk, N, G, half, lane);
+    if (refill) {
+      __syncthreads();  // every wave is done with the window
+      w0 = w0n;
+      dw_stage_tape(tw, rrec, chunk, n, N, w0);
     }
-    // after the barrier: the window holds the next step's slots
-    dw_load_tape<G>(ob0, tw, d, 0);
+    __syncthreads();
+  };
+  for (int i = 0; i < iters; i += 2) {
+    body(ob0, ob1, i);
+    if (i + 1 < iters) body(ob1, ob0, i + 1);
   }
 }
 
@@ -758,13 +758,13 @@ __device__ inline void dw_accumulate(f4* acc, float* bs, const float* __restrict
 // each chunk but the first lets every wave finish reading the previous
 // chunk's last staged step (its iteration ends without one).
 template <int G, bool BF16>
-__device__ inline void dw_chunks(f4* acc, float* bs, const float* __restrict__ rec,
+__device__ inline void dw_chunks(f4* acc, const float* __restrict__ rec,
                                  const float* __restrict__ dz, int N, int t_lo, int t_hi, int n,
-                                 int half, float* sA, float* tw) {
+                                 int half, char* sA, float* tw, const f4* w3) {
   const int n_chunks = (N + RB - 1) / RB;
   for (int chunk = blockIdx.x; chunk < n_chunks; chunk += gridDim.x) {
     if (chunk != (int)blockIdx.x) __syncthreads();
-    dw_accumulate<G, BF16>(acc, bs, rec, dz, N, chunk, t_lo, t_hi, n, half, sA, tw);
+    dw_accumulate<G, BF16>(acc, rec, dz, N, chunk, t_lo, t_hi, n, half, sA, tw, w3);
   }
 }
 
@@ -772,9 +772,6 @@ __device__ inline void dw_chunks(f4* acc, float* bs, const float* __restrict__ r
 // [group 4][accumulator DW_NACC][lane 64][register 4] floats, so a wave adds
 // its sums with whole-wave vector loads and stores; dw_slot maps a flat
 // gradient index to its place in a slot (k_bwd_reduce gathers with it).
-// The bias sums are reduced within the wave first: layer 2's bias of neuron
-// 16 g + i sits in lane i, register 0 of accumulator DW_A_B2 of group g,
-// layer 3's bias of output o in lane o, register 0 of DW_A_B3 of group 2.
 constexpr int DW_SLOT = 4 * DW_NACC * 64 * 4;
 
 __host__ __device__ constexpr int dw_pos(int g, int a, int lane, int r) {
@@ -788,15 +785,13 @@ __host__ __device__ constexpr int dw_tile_pos(int g, int a, int rr, int c) {
 // flat gradient index (torch Linear layout) -> place in a slot
 __device__ inline int dw_slot(int idx) {
   if (idx < OFF_B1) {
-    const int nrn = idx / NO, col = idx % NO;
-    if (col >= DW_COL_SMALL) return dw_pos(0, DW_A_SMALL, 4 * (nrn / 4) + col - DW_COL_SMALL, nrn % 4);
-    const int t = col / 16, c = col % 16;
-    if (t == DW_SPLIT) return dw_tile_pos(nrn / 16, DW_A_SHARED, nrn % 16, c);
+    const int nrn = idx / NO, col = idx % NO, t = col / 16, c = col % 16;
+    if (t >= 8) return dw_tile_pos(nrn / 16, t == 8 ? DW_A_T8 : DW_A_T9, nrn % 16, c);
     return dw_tile_pos(t % 4, 4 * (t / 4) + nrn / 16, nrn % 16, c);
   }
   if (idx < OFF_W2) {
     const int nrn = idx - OFF_B1;  // the constant column 146
-    return dw_pos(0, DW_A_SMALL, 4 * (nrn / 4) + NO - DW_COL_SMALL, nrn % 4);
+    return dw_tile_pos(nrn / 16, DW_A_T9, nrn % 16, NO - DW_T9);
   }
   if (idx < OFF_B2) {
     const int nrn = (idx - OFF_W2) / NHID, col = (idx - OFF_W2) % NHID;
@@ -804,13 +799,13 @@ __device__ inline int dw_slot(int idx) {
   }
   if (idx < OFF_W3) {
     const int nrn = idx - OFF_B2;
-    return dw_pos(nrn / 16, DW_A_B2, nrn % 16, 0);
+    return dw_tile_pos(nrn / 16, DW_A_BIAS, nrn % 16, 0);
   }
   if (idx < OFF_B3) {
     const int o = (idx - OFF_W3) / NHID, col = (idx - OFF_W3) % NHID;
-    return dw_pos(2, DW_A_SMALL, col, o);
+    return dw_tile_pos(col / 16, DW_A_L3, o, col % 16);
   }
-  return dw_pos(2, DW_A_B3, idx - OFF_B3, 0);
+  return dw_tile_pos(2, DW_A_BIAS, idx - OFF_B3, 8);
 }
 
 // grid (gx, S step groups), 512 threads; workgroup x takes the 64-env
@@ -819,11 +814,17 @@ __device__ inline int dw_slot(int idx) {
 // slot (x * S + sg) across segments.
 template <bool BF16>
 __global__ void __launch_bounds__(512)
-k_bwd_dw(int N, const float* __restrict__ rec, const float* __restrict__ dz, int n, int S,
+k_bwd_dw(int N, const float* __restrict__ W, const float* __restrict__ rec, const float* __restrict__ dz, int n, int S,
          float* __restrict__ gpart) {
-  // dz staging of the two halves during the loop, then the exchange of sums
-  __shared__ __attribute__((aligned(16))) float smem[2 * DW_ABUF + DW_TBUF];
+  // two staging buffers during the loop, then the exchange of sums
+  __shared__ __attribute__((aligned(16))) float smem[2 * DW_ABUF + DW_TBUF + NHID * NA];
   float* tw = smem + 2 * DW_ABUF;  // the action-tape window
+  f4* w3 = reinterpret_cast<f4*>(tw + DW_TBUF);  // layer 3's weights by neuron
+  if (threadIdx.x < NHID * NA) {
+    const float w = W[OFF_W3 + (threadIdx.x & 3) * NHID + (threadIdx.x >> 2)];
+    tw[DW_TBUF + threadIdx.x] = BF16 ? (float)(__bf16)w : w;
+  }
+  __syncthreads();
   static_assert(2 * DW_ABUF * 4 >= 4 * DW_NACC * 64 * 16, "exchange fits the staging space");
   f4(*xacc)[DW_NACC][64] = reinterpret_cast<f4(*)[DW_NACC][64]>(smem);
   const int sg = blockIdx.y;
@@ -833,24 +834,19 @@ k_bwd_dw(int N, const float* __restrict__ rec, const float* __restrict__ dz, int
   const int g = wv & 3, half = wv >> 2;
   const int per = (n + S - 1) / S;
   const int t_lo = sg * per, t_hi = (t_lo + per) < n ? (t_lo + per) : n;
-  // the bias sums accumulate in bs (layer 2's, layer 3's) and enter their
-  // slots DW_A_B2 and DW_A_B3 after the loop
   f4 acc[DW_NACC];
-  float bs[2] = {0.0f, 0.0f};
 #pragma unroll
   for (int i = 0; i < DW_NACC; ++i) acc[i] = const4(0.0f);
-  float* sA = smem + half * DW_ABUF;
+  char* sA = reinterpret_cast<char*>(smem);
   // one loop over the workgroup's chunks inside each group's instantiation
   // (a loop around the switch would keep every group's operand slots live
   // and spill)
   switch (g) {
-    case 0: dw_chunks<0, BF16>(acc, bs, rec, dz, N, t_lo, t_hi, n, half, sA, tw); break;
-    case 1: dw_chunks<1, BF16>(acc, bs, rec, dz, N, t_lo, t_hi, n, half, sA, tw); break;
-    case 2: dw_chunks<2, BF16>(acc, bs, rec, dz, N, t_lo, t_hi, n, half, sA, tw); break;
-    default: dw_chunks<3, BF16>(acc, bs, rec, dz, N, t_lo, t_hi, n, half, sA, tw); break;
+    case 0: dw_chunks<0, BF16>(acc, rec, dz, N, t_lo, t_hi, n, half, sA, tw, w3); break;
+    case 1: dw_chunks<1, BF16>(acc, rec, dz, N, t_lo, t_hi, n, half, sA, tw, w3); break;
+    case 2: dw_chunks<2, BF16>(acc, rec, dz, N, t_lo, t_hi, n, half, sA, tw, w3); break;
+    default: dw_chunks<3, BF16>(acc, rec, dz, N, t_lo, t_hi, n, half, sA, tw, w3); break;
   }
-  acc[DW_A_B2] = f4{bs[0], 0.0f, 0.0f, 0.0f};
-  acc[DW_A_B3] = f4{bs[1], 0.0f, 0.0f, 0.0f};
   __syncthreads();  // the staging space becomes the exchange buffer
   // half 1 hands its sums to half 0 (fixed order: half 0 + half 1)
   if (half == 1)
@@ -863,14 +859,6 @@ k_bwd_dw(int N, const float* __restrict__ rec, const float* __restrict__ dz, int
     const f4 o = xacc[g][i][lane];
 #pragma unroll
     for (int r = 0; r < 4; ++r) acc[i][r] += o[r];
-  }
-  // layer 2's bias sums over the four lane groups (lanes i, i ^ 32, then
-  // i ^ 16); every lane of layer 3's output o already holds the whole sum
-  {
-    float s = acc[DW_A_B2][0];
-    s += __shfl_xor(s, 32);
-    s += __shfl_xor(s, 16);
-    acc[DW_A_B2][0] = s;
   }
   // add into this group's part of the slot: all loads, then all stores
   f4* gp = reinterpret_cast<f4*>(gpart + ((size_t)blockIdx.x * S + sg) * DW_SLOT) + g * DW_NACC * 64;
@@ -1072,7 +1060,7 @@ static hipError_t backward_segments(const DevCfg& c, const SimBufs& b, const Bwd
       BWD_TRY(hipStreamWaitEvent(s_dw, bw.e_rev[buf], 0));
     }
     hipLaunchKernelGGL((c.flags & F_ACTOR_BF16) ? k_bwd_dw<true> : k_bwd_dw<false>,
-                       dim3(bw.dw_gx, bw.dw_groups), dim3(512), 0, s_dw, N, bw.seg[buf],
+                       dim3(bw.dw_gx, bw.dw_groups), dim3(512), 0, s_dw, N, W, bw.seg[buf],
                        bw.dz[buf], n, bw.dw_groups, bw.gpart);
     BWD_TRY(hipGetLastError());
     if (overlap) BWD_TRY(hipEventRecord(bw.e_dw[buf], s_dw));

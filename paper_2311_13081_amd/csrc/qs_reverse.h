@@ -6,8 +6,17 @@
 
 namespace qs {
 
-constexpr int DZ_F = NHID + NHID + NA;  // layer cotangents dz1 | dz2 | dz3 per (step, env)
+// Layer cotangents per (step, env): dz1, then dz3 at DZ_3.  dz2 follows from dz3,
+// the masks and layer 3 (k_bwd_dw); its rows between the two stay unused, which
+// keeps the size of the caller's scratch array.
+constexpr int DZ_3 = 2 * NHID, DZ_F = DZ_3 + NA;
 constexpr int LAM_F = NS + NH * NA;     // state and history adjoints carried between segments
+
+// v where bit b of the mask word m is set, +0 elsewhere (the sign-extended
+// one-bit field is all ones or zero)
+__device__ inline float keep_if(float v, uint32_t m, int b) {
+  return __uint_as_float(__float_as_uint(v) & (uint32_t)__builtin_amdgcn_sbfe((int)m, b, 1));
+}
 
 // The actor's transposed layers as fragments of 16 outputs (qs_tile.h's operand
 // layout, products and order of terms): dz1 = W2^T dz2, output tile mt, chunk m

@@ -67,12 +67,6 @@ __device__ inline void stage_reverse1(const float* __restrict__ W, float* lds, b
       [](int p, int i) { return 16 * p + i < NO ? 16 * p + i : -1; }, bf16);
 }
 
-// v where bit b of the mask word m is set, +0 elsewhere (the sign-extended
-// one-bit field is all ones or zero)
-__device__ inline float keep_if(float v, uint32_t m, int b) {
-  return __uint_as_float(__float_as_uint(v) & (uint32_t)__builtin_amdgcn_sbfe((int)m, b, 1));
-}
-
 // Inputs of one reverse step: the own env's recorded state and action and
 // cotangents, and the ReLU mask words of lane group lg for envs 16 bb + li.
 struct StepIn1 {
@@ -182,7 +176,7 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
       d3[i] = active ? ga[i] * (1.0f - cur.a[i] * cur.a[i]) : 0.0f;
-      bst1(d3[i], rdz, vlane, sz + 4u * (2 * NHID + i) * RB);
+      bst1(d3[i], rdz, vlane, sz + 4u * (DZ_3 + i) * RB);
     }
     // dz2 = (W3^T dz3) [z2 > 0]: one rank-1 update per action
     f16 d2[4];
@@ -202,7 +196,6 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
         for (int v = 0; v < 4; ++v) {
           const int r = 4 * bb + v;
           d2[n2][r] = keep_if(d2[n2][r], cur.m[bb], 8 * n2 + 4 + v);
-          bst1(d2[n2][r], rdz, vtile, sz + 4u * ((NHID + 16 * n2 + v) * RB + 16 * bb));
         }
     // dz1 = (W2^T dz2) [z1 > 0]
     const u4t* frag = reinterpret_cast<const u4t*>(lds + L_FRAG);
