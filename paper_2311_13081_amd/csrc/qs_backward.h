@@ -6,10 +6,16 @@ namespace qs {
 
 // Scratch owned by the handle for the backward pass (allocated at create).
 // Segments are pipelined over three streams (recompute, reverse sweep on the
-// caller's stream, weight gradients) with NBUF rotating segment buffers.
-constexpr int BWD_NBUF = 4;
+// caller's stream, weight gradients) with nbuf rotating segment buffers: one per
+// segment of the horizon up to BWD_NBUF (a segment without one is recomputed from
+// its checkpoint), those past the fourth only where no recompute overlaps the
+// sweep, all of them together stay below BWD_MORE_BYTES and memory is there.
+constexpr int BWD_NBUF = 8;
+constexpr int BWD_NBUF_MIN = 4;
+constexpr double BWD_MORE_BYTES = 8e9;
 struct BwdBufs {
   int N = 0, K = 0, H = 0;
+  int nbuf = 0;                       // segment buffers allocated
   int n_parts = 0;                    // partial slots of the weight gradients (dw_gx x groups)
   int dw_gx = 1;                      // weight-gradient workgroups along the 64-env chunks
   int dw_groups = 1;                  // step groups per 64-env chunk

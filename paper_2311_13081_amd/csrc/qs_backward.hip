@@ -930,20 +930,37 @@ hipError_t bwd_alloc(BwdBufs& bw, int N, int K, int H) {
   bw.dw_groups = S;
   bw.n_parts = bw.dw_gx * S;
   hipError_t e;
-  // a horizon of J segments uses min(J, BWD_NBUF) of the rotating buffers
-  const int nseg = (H + K - 1) / K < BWD_NBUF ? (H + K - 1) / K : BWD_NBUF;
+  // a horizon of J segments uses min(J, BWD_NBUF) of the rotating buffers, fewer
+  // where they are large or where a recompute runs beside the sweep (overlap):
+  // elsewhere every segment kept spares its recompute (16384 envs x 128 steps, K =
+  // 16: 2350 us with four, 1982 with eight)
+  const size_t seg_bytes = rec_floats(K, N) * 4, dz_bytes = (size_t)K * DZ_F * rb_pad(N) * 4;
+  const int most = chunks < n_cu ? BWD_NBUF_MIN : BWD_NBUF;
+  int nseg = (H + K - 1) / K < most ? (H + K - 1) / K : most;
+  while (nseg > BWD_NBUF_MIN && (double)nseg * (double)(seg_bytes + dz_bytes) > BWD_MORE_BYTES)
+    --nseg;
+  bw.nbuf = nseg;
   for (int i = 0; i < BWD_NBUF; ++i) {
     if ((e = hipEventCreateWithFlags(&bw.e_rec[i], hipEventDisableTiming)) != hipSuccess) return e;
     if ((e = hipEventCreateWithFlags(&bw.e_rev[i], hipEventDisableTiming)) != hipSuccess) return e;
     if ((e = hipEventCreateWithFlags(&bw.e_dw[i], hipEventDisableTiming)) != hipSuccess) return e;
-    if (i >= nseg) continue;
+    if (i >= bw.nbuf) continue;
+    e = hipMalloc(&bw.seg[i], seg_bytes);
+    if (e == hipSuccess) e = hipMalloc(&bw.dz[i], dz_bytes);
+    if (e != hipSuccess && i >= BWD_NBUF_MIN) {
+      // no memory for one more: do without
+      (void)hipGetLastError();
+      if (bw.seg[i]) (void)hipFree(bw.seg[i]);
+      bw.seg[i] = bw.dz[i] = nullptr;
+      bw.nbuf = i;
+      continue;
+    }
+    if (e != hipSuccess) return e;
     // zeroed once: whole wavefronts past the last env never write their slots
     // of the last 64-env block, which must read as finite (record) and zero
     // (cotangents) in the weight-gradient pass
-    if ((e = hipMalloc(&bw.seg[i], rec_floats(K, N) * 4)) != hipSuccess) return e;
-    if ((e = hipMemset(bw.seg[i], 0, rec_floats(K, N) * 4)) != hipSuccess) return e;
-    if ((e = hipMalloc(&bw.dz[i], (size_t)K * DZ_F * rb_pad(N) * 4)) != hipSuccess) return e;
-    if ((e = hipMemset(bw.dz[i], 0, (size_t)K * DZ_F * rb_pad(N) * 4)) != hipSuccess) return e;
+    if ((e = hipMemset(bw.seg[i], 0, seg_bytes)) != hipSuccess) return e;
+    if ((e = hipMemset(bw.dz[i], 0, dz_bytes)) != hipSuccess) return e;
   }
   int dev = 0;
   if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
@@ -991,7 +1008,7 @@ void bwd_free(BwdBufs& bw) {
     if (e_ != hipSuccess) return e_; \
   } while (0)
 
-// Segments run last to first.  Per segment j (buffer j mod 3):
+// Segments run last to first.  Per segment (buffers in turn):
 //   recompute stream: waits for the weight-gradient pass that last used the
 //     buffer, then records the segment;
 //   caller stream: waits for the record, runs the reverse sweep (the
@@ -1004,10 +1021,9 @@ void bwd_free(BwdBufs& bw) {
 // workgroups than CUs); for large batches the sweep (one wave per SIMD, most
 // registers) fills the chip and everything stays on the caller's stream in
 // order.
-// nbuf: segment buffers to rotate (BWD_NBUF, or 1 for the serial order of
-// the scratch-array variant, which also keeps every kernel on st).
-static hipError_t backward_segments(const DevCfg& c, const SimBufs& b, const BwdBufs& bw, int nbuf,
-                                    const float* W, const float* tape, int K, int T,
+// serial: every kernel on st (the scratch-array variant, one buffer).
+static hipError_t backward_segments(const DevCfg& c, const SimBufs& b, const BwdBufs& bw,
+                                    bool serial, const float* W, const float* tape, int K, int T,
                                     const float* d_rewards, const float* d_states,
                                     float* grad_actor, float* grad_params, int* held,
                                     hipStream_t st) {
@@ -1016,7 +1032,8 @@ static hipError_t backward_segments(const DevCfg& c, const SimBufs& b, const Bwd
   hipLaunchKernelGGL(k_fill, dim3(nb((int)np, 256)), dim3(256), 0, st, bw.gpart, np, 0.0f);
   hipLaunchKernelGGL(k_bwd_init, dim3(nb(N, 256)), dim3(256), 0, st, N,
                      d_states ? d_states + (size_t)T * NS * N : nullptr, bw.lam, bw.gth);
-  const bool overlap = nbuf == BWD_NBUF && (int)nb(N, 64) < bw.n_cu;
+  const int nbuf = bw.nbuf;
+  const bool overlap = !serial && (int)nb(N, 64) < bw.n_cu;
   hipStream_t s_rec = overlap ? bw.s_rec : st, s_dw = overlap ? bw.s_dw : st;
   if (overlap) {
     BWD_TRY(hipEventRecord(bw.e_init, st));
@@ -1036,7 +1053,7 @@ static hipError_t backward_segments(const DevCfg& c, const SimBufs& b, const Bwd
       // nothing to recompute
     } else {
       if (held) held[buf] = j;
-      if (overlap && idx >= BWD_NBUF) BWD_TRY(hipStreamWaitEvent(s_rec, bw.e_dw[buf], 0));
+      if (overlap && idx >= nbuf) BWD_TRY(hipStreamWaitEvent(s_rec, bw.e_dw[buf], 0));
       BWD_TRY(launch_recompute(c, b, W, n, tape + (size_t)j * CK_F * N, bw.seg[buf], s_rec));
       if (overlap) {
         BWD_TRY(hipEventRecord(bw.e_rec[buf], s_rec));
@@ -1080,7 +1097,7 @@ hipError_t run_backward(const DevCfg& c, const SimBufs& b, BwdBufs& bw, const fl
                         const float* tape, int K, int T, const float* d_rewards,
                         const float* d_states, float* grad_actor, float* grad_params,
                         int held[BWD_NBUF], hipStream_t st) {
-  return backward_segments(c, b, bw, BWD_NBUF, W, tape, K, T, d_rewards, d_states, grad_actor,
+  return backward_segments(c, b, bw, false, W, tape, K, T, d_rewards, d_states, grad_actor,
                            grad_params, held, st);
 }
 
@@ -1124,7 +1141,8 @@ hipError_t run_backward_in(const DevCfg& c, const SimBufs& b, const BwdBufs& bw,
   hipLaunchKernelGGL(k_fill, dim3(nb((int)f_rec, 256)), dim3(256), 0, st, sb.seg[0], f_rec, 0.0f);
   hipLaunchKernelGGL(k_fill, dim3(nb((int)f_dz, 256)), dim3(256), 0, st, sb.dz[0], f_dz, 0.0f);
   BWD_TRY(hipGetLastError());
-  return backward_segments(c, b, sb, 1, W, tape, K, T, d_rewards, d_states, grad_actor,
+  sb.nbuf = 1;
+  return backward_segments(c, b, sb, true, W, tape, K, T, d_rewards, d_states, grad_actor,
                            grad_params, nullptr, st);
 }
 
