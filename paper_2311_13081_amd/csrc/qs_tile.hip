@@ -311,7 +311,7 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
 #pragma unroll
       for (int tl = 0; tl < TILES; ++tl) aht[tl] = park[PK_AH + tl];
       H.fill(on, aht);
-      history();
+      reset_history<TILES>(lds, on, aht, a1);
       if (rst) {
         ++ep;
         t_ep = 0;
