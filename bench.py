@@ -40,7 +40,6 @@ FLOP_PER_ENV_STEP = 28_500
 # dynamics kernel reads parameters, state, action and counters (128 B) and
 # writes a ring slot, counters, state, reward and done (97 B).
 PLAIN_BYTES_PER_ENV_STEP = 1160 + 840 + 512 + 272 + 225
-PEAK_FP32_MFMA = 157.3e12      # MI355X dense fp32 matrix FLOP/s
 PEAK_BF16_MFMA = 2.5e15        # dense bf16 matrix FLOP/s
 PEAK_FP32_VALU = 78.6e12       # fp32 vector FLOP/s without packed instructions
 PEAK_FP64 = 78.6e12            # fp64 vector and matrix FLOP/s
@@ -57,11 +56,23 @@ DYN_FLOP_PER_ENV_STEP = 700
 # three GEMMs (3 x 27392) run on matrix cores; the rest is scalar fp32.
 FLOP_FWD_BWD_ENV_STEP = 28_500 + 2 * 27_392 + 2_400
 ACTOR_GEMM_FLOP_FWD_BWD = 3 * 27_392
+# The fp32 kernels form a product of two fp32 values from six bf16 products of
+# their parts (each value is the sum of three bf16 values).
+SPLIT_PRODUCTS = 6
+
+
+def split_roofline(achieved, flop, gemm):
+    """Roofline of `achieved` algorithmic FLOP/s of work with `gemm` of its
+    `flop` in split products on bf16 matrix cores and the rest on the vector
+    ALUs, the two one after the other."""
+    peak = flop / (SPLIT_PRODUCTS * gemm / PEAK_BF16_MFMA + (flop - gemm) / PEAK_FP32_VALU)
+    return {"bound": "bf16 mfma (6 products per fp32 product) + fp32 valu",
+            "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s",
+            "frac": achieved / peak}
 
 
 TRAFFIC_PROFILES = {
-    "k_fused<MFMA>": os.path.join(ROOT, "profiles", "k_fused_mfma_fwd65536_dr_hbm_traffic.md"),
-    "k_fused4<MFMA>": os.path.join(ROOT, "profiles", "k_fused4_mfma_fwd65536_dr_hbm_traffic.md"),
+    "k_tile<2>": os.path.join(ROOT, "profiles", "k_tile2_fwd65536_dr_hbm_traffic.md"),
 }
 
 
@@ -276,7 +287,7 @@ def fwd_bwd(torch, pkg, name, K, W, warmup=1, bf16=False):
     sim = pkg.QuadSim(cfg)
     torch.cuda.synchronize()
     handle_bytes = free0 - torch.cuda.mem_get_info()[0]
-    sim.set_variant(pkg.SIM_V_FUSED_MFMA4)   # the kernel taped rollouts use
+    sim.set_variant(pkg.SIM_V_FUSED_MFMA4)   # of the truth rollout; taped ones choose their own
     a = sim.actor_tensor(W)
     snap = {k: v.clone() for k, v in sim.get_state().items()}
     if name.startswith("sysid"):
@@ -330,9 +341,8 @@ def fwd_bwd(torch, pkg, name, K, W, warmup=1, bf16=False):
         roof = {"bound": "bf16 mfma + fp32 valu", "roof_env_steps_per_s": 1.0 / t_roof,
                 "frac": rate * t_roof}
     else:
-        ach = rate * FLOP_FWD_BWD_ENV_STEP / 1e12
-        roof = {"bound": "mfma", "achieved": ach, "peak": PEAK_FP32_MFMA / 1e12,
-                "unit": "TFLOP/s", "frac": ach * 1e12 / PEAK_FP32_MFMA}
+        roof = split_roofline(rate * FLOP_FWD_BWD_ENV_STEP, FLOP_FWD_BWD_ENV_STEP,
+                              ACTOR_GEMM_FLOP_FWD_BWD)
     roof["flop_per_env_step"] = FLOP_FWD_BWD_ENV_STEP
     K = cfg["ckpt_every"]
     # checkpoints of (state, history, counters): 147 floats per env; the
@@ -468,8 +478,8 @@ def main():
     flop_per_launch = FLOP_PER_ENV_STEP * N * (T / launches)
     achieved = flop_per_launch / (kernel_ms * 1e-3)
     vname = {1: "plain", 2: "fused_valu", 3: "fused_mfma", 4: "fused_mfma4", 5: "fused_split"}[v]
-    kname = {1: "plain (5 kernels)", 2: "k_fused<VALU>", 3: "k_fused<MFMA>",
-             4: "k_fused4<MFMA>", 5: "k_split<MFMA>"}[v]
+    kname = {1: "plain (5 kernels)", 2: "k_fused<VALU>", 3: "k_tile<2>", 4: "k_tile<1>",
+             5: "k_split"}[v]
     res = {
         "metric": METRIC,
         "value": value,
@@ -490,8 +500,7 @@ def main():
                    "launch": ("hipGraph replay of %d launches" % launches if graph and launches > 1
                               else "%d launch(es) from the host" % launches),
                    "launches_per_step": launches},
-        "roofline": {"bound": "mfma", "achieved": achieved / 1e12, "peak": PEAK_FP32_MFMA / 1e12,
-                     "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_MFMA,
+        "roofline": {**split_roofline(achieved, FLOP_PER_ENV_STEP, ACTOR_GEMM_FLOP),
                      "traffic": measured_traffic(kname, N, T // launches),
                      "kernel": kname,
                      "kernel_ms": kernel_ms, "flop_per_env_step": FLOP_PER_ENV_STEP},

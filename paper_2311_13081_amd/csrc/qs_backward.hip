@@ -48,8 +48,7 @@ __global__ void k_bwd_init(int N, const float* __restrict__ dS_T, float* __restr
 }
 
 // Reverse sweep in the quarter-lane layout (16 envs per wave, lane L = j +
-// 16 k: env j, quarter k), the adjoint of the forward step (the quarter-lane
-// or the split-actor kernel, which compute the same values).  Per lane:
+// 16 k: env j, quarter k), the adjoint of the forward step.  Per lane:
 // the state adjoint (17) and the dynamics VJP, replicated over the 4 quarters
 // of an env; the history adjoint of action component k (32 slots).  The actor
 // VJP runs on matrix cores:

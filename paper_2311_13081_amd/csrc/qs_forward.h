@@ -69,7 +69,8 @@ constexpr int CK_TEP = NS + NH * NA, CK_EP = CK_TEP + 1, CK_F = CK_EP + 1;
 // rows per env.  The rows of a block are 256 B apart and a block's record of
 // a step is one contiguous span, so the readers, which take a few envs of
 // many rows at a time, stay within a few DRAM pages.  A step holds rb_pad(N)
-// env slots; the slots of envs >= N in the last block are never written.
+// env slots; those of envs >= N in the last block hold zeros (cleared at
+// allocation) or finite copies of a batch env's values.
 constexpr int RB = 64;
 __host__ __device__ inline size_t rb_pad(int N) { return (size_t)((N + RB - 1) / RB) * RB; }
 __host__ __device__ inline size_t rb_at(int e, int F) {
@@ -116,9 +117,9 @@ inline bool rec_span_ok(const RecSpan& rs) {
 }
 hipError_t launch_recompute(const DevCfg& c, const SimBufs& b, const float* W, int T,
                             const float* ck_in, float* rec, hipStream_t st);
-// Tile kernel (qs_tile.hip): 16 tiles envs per wave (tiles = 1 or 2), actor on
-// bf16 matrix cores with split fp32 operands; the kernel of policy rollouts and of taped rollouts (tape: CK_F-row checkpoints
-// every ckpt_every steps).  With ck_in != NULL it starts from that checkpoint
+// Tile kernel (qs_tile.hip): tiles (1 or 2) of 16 envs per wave, actor on bf16
+// matrix cores with split fp32 operands; the kernel of policy rollouts and of taped
+// rollouts (tape: CK_F-row checkpoints every ckpt_every steps).  With ck_in != NULL it starts from that checkpoint
 // and leaves the env state alone (the backward's recompute).  With rs.buf[0] !=
 // NULL it writes the backward's record of the span rs (the recompute: its
 // one segment; a taped rollout: its last segments).

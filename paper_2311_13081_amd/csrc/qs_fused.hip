@@ -1,6 +1,7 @@
 // Fused multi-step kernel of the batched quadrotor step with one env per
 // lane: observation, actor (vector ALUs; the bf16 option on bf16 matrix
-// cores; or given actions), action map, RK4, reward, history push, termination and reset for T steps in one launch.
+// cores; or given actions), action map, RK4, reward, history push, termination
+// and reset for T steps in one launch.
 //
 // Layout: struct-of-arrays in HBM ([K][N]) so every global access of a wave is
 // a contiguous 256-byte segment; actor weights are staged in LDS once per
@@ -17,8 +18,8 @@ namespace qs {
 
 // T steps of the whole step (observation, actor, action map, RK4, reward,
 // history push, termination, truncation, reset, episode accumulators) with
-// state and history kept in registers.  Outputs indexed by t_base + t.  ext_act ([T][4][N]) replaces
-// the actor when non-NULL.  Inactive lanes of the last wave shadow the wave's
+// state and history kept in registers.  Outputs indexed by t_base + t.
+// ext_act ([T][4][N]) replaces the actor when non-NULL.  Inactive lanes of the last wave shadow the wave's
 // first env (read only) so every MFMA operand is finite.  EXTRAS (the
 // training extras or a set point are on): the episode disturbance enters the
 // dynamics and the actor sees its observation with noise and the set-point
