@@ -350,9 +350,10 @@ __device__ inline void noise_uniforms(const DevCfg& c, uint32_t e, uint32_t ep, 
 // The noise costs more than the rest of the step's vector work, so a lane
 // evaluates only the normals of the features it hands out: one of a pair for
 // one tile, a pair for two.
-template <int TILES, bool EXTRAS>
-__device__ inline void tile_features(const DevCfg& c, const SetPoint& sp, uint32_t e, uint32_t ep,
-                                     int t_ep, const float x[NS], int lg, float (&F)[TILES][5]) {
+// noise(zc, zs): the five pairs of normals of the lane's half.
+template <int TILES, bool EXTRAS, typename Noise>
+__device__ inline void tile_features(const DevCfg& c, const SetPoint& sp, const float x[NS], int lg,
+                                     float (&F)[TILES][5], Noise&& noise) {
   float f[20];
   rotmat(x + 3, f + 3);
 #pragma unroll
@@ -365,12 +366,11 @@ __device__ inline void tile_features(const DevCfg& c, const SetPoint& sp, uint32
   if (EXTRAS) {
     sp.apply(c, f);
     if (c.flags & F_OBS_NOISE) {
-      float u0[5], u1[5];
-      noise_uniforms<TILES>(c, e, ep, t_ep, lg, u0, u1);
+      float zcs[5], zss[5];
+      noise(zcs, zss);
 #pragma unroll
       for (int q = 0; q < 5; ++q) {
-        float zc, zs;
-        box_muller(u0[q], u1[q], zc, zs);
+        const float zc = zcs[q], zs = zss[q];
         // the pair 4 q + 2 h, 4 q + 2 h + 1 of this lane's half h
         const bool lo = lg < 2;
         f[4 * q] = fmaf(pick(lo, noise_std(c, 4 * q), 0.0f), zc, f[4 * q]);
@@ -387,6 +387,25 @@ __device__ inline void tile_features(const DevCfg& c, const SetPoint& sp, uint32
 #pragma unroll
     for (int t = 0; t < TILES; ++t) F[t][q] = o[t];
   }
+}
+
+// The normals drawn by the lane itself.
+template <int TILES>
+__device__ inline void draw_normals(const DevCfg& c, uint32_t e, uint32_t ep, int t_ep, int lg,
+                                    float zc[5], float zs[5]) {
+  float u0[5], u1[5];
+  noise_uniforms<TILES>(c, e, ep, t_ep, lg, u0, u1);
+#pragma unroll
+  for (int q = 0; q < 5; ++q) box_muller(u0[q], u1[q], zc[q], zs[q]);
+}
+// One of its pairs: block q of the step, the half of lane group lg.
+__device__ inline float2 draw_normal_pair(const DevCfg& c, uint32_t e, uint32_t ep, int t_ep,
+                                          int lg, int q) {
+  float u[4];
+  float2 z;
+  uniforms4(c.seed_lo, c.seed_hi, e, ep, (uint32_t)t_ep * 5u + (uint32_t)q, STREAM_NOISE, u);
+  box_muller(pick(lg < 2, u[0], u[2]), pick(lg < 2, u[1], u[3]), z.x, z.y);
+  return z;
 }
 
 // Layer 3 (fp32 16-block 4x4x1, one product per layer-2 result register: block

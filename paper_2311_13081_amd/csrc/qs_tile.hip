@@ -225,7 +225,9 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
       }
     }
     float F[TILES][5];
-    tile_features<TILES, EXTRAS>(c, sp, (uint32_t)e, (uint32_t)ep, t_ep, x, lg, F);
+    tile_features<TILES, EXTRAS>(c, sp, x, lg, F, [&](float* zc, float* zs) {
+      draw_normals<TILES>(c, (uint32_t)e, (uint32_t)ep, t_ep, lg, zc, zs);
+    });
     // the wave in its actor goes first: its products are the serial part, the
     // other wave's vector instructions fill in
     __builtin_amdgcn_s_setprio(1);
