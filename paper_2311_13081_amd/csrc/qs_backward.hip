@@ -436,7 +436,7 @@ struct DwAddr {
 };
 
 template <int G>
-__device__ inline void dw_addr(DwAddr& d, int tl, int n, int chunk, int N, int lane, int w0) {
+__device__ inline void dw_addr(DwAddr& d, int tl, int K, int chunk, int N, int lane, int w0) {
   const int li = lane & 15, lg = lane >> 4;
   const uint32_t rbp = (uint32_t)rb_pad(N), rstep = (uint32_t)REC_F * rbp;
   const uint32_t blk = (uint32_t)tl * rstep + (uint32_t)chunk * (REC_F * RB);
@@ -445,7 +445,7 @@ __device__ inline void dw_addr(DwAddr& d, int tl, int n, int chunk, int N, int l
   d.h1 = 0;
   if (G == 1) {
     // history slot sl of step tl is tape slot tl + sl of the block
-    const uint32_t tape = (uint32_t)n * rstep + (uint32_t)chunk * ((NH + n) * NA * RB);
+    const uint32_t tape = (uint32_t)K * rstep + (uint32_t)chunk * ((NH + K) * NA * RB);
     const int hc = li < 2 ? 0 : li - 2;
     const uint32_t o_hist = tape + (uint32_t)((tl + (hc >> 2)) * NA + (hc & 3)) * RB;
     d.h1 = 4u * (4 * lg + (li < 2 ? blk + (REC_O + 16 + li) * RB : o_hist));
@@ -469,17 +469,17 @@ __device__ inline void dw_load_pair(DwOps& o, __amdgpu_buffer_rsrc_t rrec, const
 }
 
 // Copies tape slots [w0, w0 + DW_CH + NH) of 64-env block `chunk` (those
-// below NH + n) into the window tw, every thread of the 512 issuing its six
+// below NH + K) into the window tw, every thread of the 512 issuing its six
 // 16-byte loads before its first store.
 constexpr int DW_TLD = DW_TW * (RB / 4) / 512;
 static_assert(DW_TW * (RB / 4) % 512 == 0, "the window splits evenly over the workgroup");
-__device__ inline void dw_stage_tape(float* tw, __amdgpu_buffer_rsrc_t rrec, int chunk, int n,
+__device__ inline void dw_stage_tape(float* tw, __amdgpu_buffer_rsrc_t rrec, int chunk, int K,
                                      int N, int w0) {
   const uint32_t rbp = (uint32_t)rb_pad(N);
   // the block's tape, in bytes from the record's start
   const uint32_t base =
-      4u * ((uint32_t)n * REC_F * rbp + (uint32_t)chunk * (uint32_t)((NH + n) * NA * RB));
-  const int rows = min(DW_TW, (NH + n - w0) * NA);
+      4u * ((uint32_t)K * REC_F * rbp + (uint32_t)chunk * (uint32_t)((NH + K) * NA * RB));
+  const int rows = min(DW_TW, (NH + K - w0) * NA);
   f4 v[DW_TLD];
 #pragma unroll
   for (int j = 0; j < DW_TLD; ++j) {
@@ -692,20 +692,20 @@ __device__ inline void dw_pair(f4* acc, const DwOps& o, const char* sA, const fl
 template <int G, bool BF16>
 __device__ inline void dw_accumulate(f4* acc, const float* __restrict__ rec,
                                      const float* __restrict__ dz, int N, int chunk, int t_lo,
-                                     int t_hi, int n, int half, char* sA, float* tw,
+                                     int t_hi, int K, int half, char* sA, float* tw,
                                      const f4* w3) {
   const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
   const int iters = t_hi - t_lo;
   if (iters <= 0) return;
   const uint32_t rbp = (uint32_t)rb_pad(N);
   const __amdgpu_buffer_rsrc_t rrec =
-      buf_rsrc(rec, 4u * ((uint32_t)n * REC_F * rbp + (uint32_t)(NH + n) * NA * rbp));
-  const __amdgpu_buffer_rsrc_t rdz = buf_rsrc(dz, 4u * ((uint32_t)n * DZ_F * rbp));
+      buf_rsrc(rec, 4u * ((uint32_t)K * REC_F * rbp + (uint32_t)(NH + K) * NA * rbp));
+  const __amdgpu_buffer_rsrc_t rdz = buf_rsrc(dz, 4u * ((uint32_t)K * DZ_F * rbp));
   const uint32_t loff = 4u * (uint32_t)(li * RB + 4 * lg);
   const DwPlace at = dw_place(G, half, lane);
   const auto step = [&](int i) { return t_lo + (i < iters ? i : iters - 1); };
   int w0 = t_lo;  // first slot of the tape window
-  dw_stage_tape(tw, rrec, chunk, n, N, w0);
+  dw_stage_tape(tw, rrec, chunk, K, N, w0);
   DwRows an;
   dw_a_load(an, rdz, rrec, step(0), chunk, N, G, half, lane);
   const auto stage_to = [&](char* a) {
@@ -721,7 +721,7 @@ __device__ inline void dw_accumulate(f4* acc, const float* __restrict__ rec,
   }
   DwOps ob0, ob1;
   DwAddr d;
-  dw_addr<G>(d, step(0), n, chunk, N, lane, w0);
+  dw_addr<G>(d, step(0), K, chunk, N, lane, w0);
   dw_load_pair<G>(ob0, rrec, d, loff, half);
   dw_a_load(an, rdz, rrec, step(1), chunk, N, G, half, lane);
   __syncthreads();
@@ -733,7 +733,7 @@ __device__ inline void dw_accumulate(f4* acc, const float* __restrict__ rec,
     // the next step's window (refilled below when the next step opens one)
     const bool refill = i + 1 < iters && (i + 1) % DW_CH == 0;
     const int w0n = refill ? w0 + DW_CH : w0;
-    dw_addr<G>(d, step(i + 1), n, chunk, N, lane, w0n);
+    dw_addr<G>(d, step(i + 1), K, chunk, N, lane, w0n);
     dw_load_pair<G>(nxt, rrec, d, loff, half);
     __builtin_amdgcn_sched_barrier(0);
     dw_pair<G, BF16>(acc, cur, sA + (i & 1) * (4 * DW_ABUF), tw, tape, half, lane,
@@ -743,7 +743,7 @@ __device__ inline void dw_accumulate(f4* acc, const float* __restrict__ rec,
     if (refill) {
       __syncthreads();  // every wave is done with the window
       w0 = w0n;
-      dw_stage_tape(tw, rrec, chunk, n, N, w0);
+      dw_stage_tape(tw, rrec, chunk, K, N, w0);
     }
     __syncthreads();
   };
@@ -758,12 +758,12 @@ __device__ inline void dw_accumulate(f4* acc, const float* __restrict__ rec,
 // chunk's last staged step (its iteration ends without one).
 template <int G, bool BF16>
 __device__ inline void dw_chunks(f4* acc, const float* __restrict__ rec,
-                                 const float* __restrict__ dz, int N, int t_lo, int t_hi, int n,
+                                 const float* __restrict__ dz, int N, int t_lo, int t_hi, int K,
                                  int half, char* sA, float* tw, const f4* w3) {
   const int n_chunks = (N + RB - 1) / RB;
   for (int chunk = blockIdx.x; chunk < n_chunks; chunk += gridDim.x) {
     if (chunk != (int)blockIdx.x) __syncthreads();
-    dw_accumulate<G, BF16>(acc, rec, dz, N, chunk, t_lo, t_hi, n, half, sA, tw, w3);
+    dw_accumulate<G, BF16>(acc, rec, dz, N, chunk, t_lo, t_hi, K, half, sA, tw, w3);
   }
 }
 
@@ -810,11 +810,12 @@ __device__ inline int dw_slot(int idx) {
 // grid (gx, S step groups), 512 threads; workgroup x takes the 64-env
 // chunks x, x + gx, ... in turn, step group sg the steps [sg * per, min(n,
 // (sg + 1) * per)), per = ceil(n / S); it accumulates into its own partial
-// slot (x * S + sg) across segments.
+// slot (x * S + sg) across segments.  n: the segment's steps, K: the capacity of
+// its buffers.
 template <bool BF16>
 __global__ void __launch_bounds__(512)
-k_bwd_dw(int N, const float* __restrict__ W, const float* __restrict__ rec, const float* __restrict__ dz, int n, int S,
-         float* __restrict__ gpart) {
+k_bwd_dw(int N, const float* __restrict__ W, const float* __restrict__ rec,
+         const float* __restrict__ dz, int n, int K, int S, float* __restrict__ gpart) {
   // two staging buffers during the loop, then the exchange of sums
   __shared__ __attribute__((aligned(16))) float smem[2 * DW_ABUF + DW_TBUF + NHID * NA];
   float* tw = smem + 2 * DW_ABUF;  // the action-tape window
@@ -841,10 +842,10 @@ k_bwd_dw(int N, const float* __restrict__ W, const float* __restrict__ rec, cons
   // (a loop around the switch would keep every group's operand slots live
   // and spill)
   switch (g) {
-    case 0: dw_chunks<0, BF16>(acc, rec, dz, N, t_lo, t_hi, n, half, sA, tw, w3); break;
-    case 1: dw_chunks<1, BF16>(acc, rec, dz, N, t_lo, t_hi, n, half, sA, tw, w3); break;
-    case 2: dw_chunks<2, BF16>(acc, rec, dz, N, t_lo, t_hi, n, half, sA, tw, w3); break;
-    default: dw_chunks<3, BF16>(acc, rec, dz, N, t_lo, t_hi, n, half, sA, tw, w3); break;
+    case 0: dw_chunks<0, BF16>(acc, rec, dz, N, t_lo, t_hi, K, half, sA, tw, w3); break;
+    case 1: dw_chunks<1, BF16>(acc, rec, dz, N, t_lo, t_hi, K, half, sA, tw, w3); break;
+    case 2: dw_chunks<2, BF16>(acc, rec, dz, N, t_lo, t_hi, K, half, sA, tw, w3); break;
+    default: dw_chunks<3, BF16>(acc, rec, dz, N, t_lo, t_hi, K, half, sA, tw, w3); break;
   }
   __syncthreads();  // the staging space becomes the exchange buffer
   // half 1 hands its sums to half 0 (fixed order: half 0 + half 1)
@@ -1053,7 +1054,7 @@ static hipError_t backward_segments(const DevCfg& c, const SimBufs& b, const Bwd
     } else {
       if (held) held[buf] = j;
       if (overlap && idx >= nbuf) BWD_TRY(hipStreamWaitEvent(s_rec, bw.e_dw[buf], 0));
-      BWD_TRY(launch_recompute(c, b, W, n, tape + (size_t)j * CK_F * N, bw.seg[buf], s_rec));
+      BWD_TRY(launch_recompute(c, b, W, n, K, tape + (size_t)j * CK_F * N, bw.seg[buf], s_rec));
       if (overlap) {
         BWD_TRY(hipEventRecord(bw.e_rec[buf], s_rec));
         BWD_TRY(hipStreamWaitEvent(st, bw.e_rec[buf], 0));
@@ -1077,7 +1078,7 @@ static hipError_t backward_segments(const DevCfg& c, const SimBufs& b, const Bwd
     }
     hipLaunchKernelGGL((c.flags & F_ACTOR_BF16) ? k_bwd_dw<true> : k_bwd_dw<false>,
                        dim3(bw.dw_gx, bw.dw_groups), dim3(512), 0, s_dw, N, W, bw.seg[buf],
-                       bw.dz[buf], n, bw.dw_groups, bw.gpart);
+                       bw.dz[buf], n, K, bw.dw_groups, bw.gpart);
     BWD_TRY(hipGetLastError());
     if (overlap) BWD_TRY(hipEventRecord(bw.e_dw[buf], s_dw));
     last = buf;

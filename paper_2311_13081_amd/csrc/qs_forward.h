@@ -50,11 +50,15 @@ hipError_t launch_dyn_rollout(const DevCfg& c, const SimBufs& b, const float* ac
 // layout, in row REC_M + k of the env's column: bit 8 n + r for layer-1 unit 16
 // n + 4 k + r, bit 8 n + 4 + r for layer 2 (tile_mask).
 // The 128 history features of o_t are not stored per step: they are the
-// actions of the 32 previous steps.  After the n step records of a segment
-// comes its action tape: per 64-env block, (NH + n) slots of NA rows, slot s
-// < NH the checkpoint's history slot s (oldest first), slot NH + t the
-// action of step t; the history slot sl of step t is tape slot t + sl.  One
-// block's tape is one contiguous span (48 KB for n = 16).
+// actions of the 32 previous steps.  After the K step records of a segment
+// buffer comes the segment's action tape: per 64-env block, (NH + K) slots of
+// NA rows, slot s < NH the checkpoint's history slot s (oldest first), slot NH
+// + t the action of step t; the history slot sl of step t is tape slot t + sl.
+// One block's tape is one contiguous span (48 KB for K = 16).  K is the
+// buffer's capacity, also where a segment is shorter: every row then has one
+// place for the life of the buffer.  (Placed by the segment's own length, the
+// tape of a short segment took the place of a longer one's steps, and its
+// slots of envs >= N kept their mask words, which can be NaN as floats.)
 constexpr int REC_X = 0, REC_A = REC_X + NS, REC_Z1 = REC_A + NA, REC_Z2 = REC_Z1 + NHID,
               REC_O = REC_Z2 + NHID, REC_M = REC_O + 18, REC_F = REC_M + 4;
 
@@ -76,9 +80,9 @@ __host__ __device__ inline size_t rb_pad(int N) { return (size_t)((N + RB - 1) /
 __host__ __device__ inline size_t rb_at(int e, int F) {
   return (size_t)(e / RB) * F * RB + (size_t)(e % RB);
 }
-// Step t of a record buffer, and the action tape of a segment of n steps.
+// Step t of a record buffer, and the action tape of one of capacity K.
 __host__ __device__ inline size_t rec_step(int t, int N) { return (size_t)t * REC_F * rb_pad(N); }
-__host__ __device__ inline size_t rec_act(int n, int N) { return (size_t)n * REC_F * rb_pad(N); }
+__host__ __device__ inline size_t rec_act(int K, int N) { return (size_t)K * REC_F * rb_pad(N); }
 // floats of a record buffer for segments of up to K steps
 __host__ __device__ inline size_t rec_floats(int K, int N) {
   return ((size_t)K * REC_F + (size_t)(NH + K) * NA) * rb_pad(N);
@@ -87,27 +91,25 @@ __host__ __device__ inline size_t rec_floats(int K, int N) {
 // Where a launch writes the backward's record: the steps [from, from +
 // total) cut into segments of len steps (the last one may be shorter), the
 // last segment into buf[0], the one before it into buf[1], ... (at most
-// REC_SEGS segments, each in its own record buffer).
+// REC_SEGS segments, each in its own record buffer of capacity len).
 constexpr int REC_SEGS = 8;
 struct RecSpan {
   float* buf[REC_SEGS];
   int from, len, total;
 };
-// Where global step gt is recorded: the segment's buffer, the step within
-// the segment and the segment's length (false: gt is not recorded).
+// Where global step gt is recorded: the segment's buffer and the step within
+// the segment (false: gt is not recorded).
 struct RecAt {
   float* base;
-  int step, n;
+  int step;
 };
 __device__ inline bool rec_at(const RecSpan& rs, int gt, RecAt& r) {
   const int rt = gt - rs.from;
   r.base = rs.buf[0];
   r.step = 0;
-  r.n = 1;
   if (!rs.buf[0] || rt < 0 || rt >= rs.total) return false;
   const int segs = (rs.total + rs.len - 1) / rs.len, k = rt / rs.len;
   r.step = rt - k * rs.len;
-  r.n = k == segs - 1 ? rs.total - k * rs.len : rs.len;
   r.base = rs.buf[segs - 1 - k];
   return true;
 }
@@ -115,7 +117,8 @@ __device__ inline bool rec_at(const RecSpan& rs, int gt, RecAt& r) {
 inline bool rec_span_ok(const RecSpan& rs) {
   return !rs.buf[0] || (rs.len >= 1 && rs.total >= 1 && (rs.total + rs.len - 1) / rs.len <= REC_SEGS);
 }
-hipError_t launch_recompute(const DevCfg& c, const SimBufs& b, const float* W, int T,
+// rec: a record buffer of capacity K >= T
+hipError_t launch_recompute(const DevCfg& c, const SimBufs& b, const float* W, int T, int K,
                             const float* ck_in, float* rec, hipStream_t st);
 // Tile kernel (qs_tile.hip): tiles (1 or 2) of 16 envs per wave, actor on bf16
 // matrix cores with split fp32 operands; the kernel of policy rollouts and of taped

@@ -274,8 +274,8 @@ k_fused4(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
       for (int cc = 0; cc < 5; ++cc)
         if (q_phi(cc, k) >= 0) rt[(size_t)(REC_O + 4 * cc) * RB + koff] = F[cc];
       // action tape of the segment: the checkpoint history once, then a_t
-      float* act = ra.base + rec_act(ra.n, N);
-      const uint32_t aoff = opaque((uint32_t)(rb_at(e, (NH + ra.n) * NA) + k * RB));
+      float* act = ra.base + rec_act(rs.len, N);
+      const uint32_t aoff = opaque((uint32_t)(rb_at(e, (NH + rs.len) * NA) + k * RB));
       if (rt_step == 0) {
 #pragma unroll
         for (int s = 0; s < NH; ++s) act[(size_t)(s * NA) * RB + aoff] = F[5 + s];
