@@ -652,6 +652,12 @@ __device__ __forceinline__ uint32_t opaque(uint32_t v) {
   return v;
 }
 
+// The same for a wave-uniform value, kept in a scalar register.
+__device__ __forceinline__ int opaque_uniform(int v) {
+  __asm__ volatile("" : "+s"(v));
+  return v;
+}
+
 // Waits for every vector load issued so far.  Ahead of a time loop: at its head the
 // compiler otherwise takes the loads before the loop, the youngest on the way in,
 // as the count to wait down to, which on the way back drains the step's stores.

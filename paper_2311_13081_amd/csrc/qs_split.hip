@@ -276,8 +276,9 @@ k_split(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
 #pragma unroll
       for (int q = 0; q < 5; ++q)
         if (4 * q + k < 18) rt[(size_t)(REC_O + 4 * q) * RB + moff] = F[0][q];
-      float* act = ra.base + rec_act(rs.len, N);
-      const uint32_t aoff = opaque((uint32_t)(rb_at(e, (NH + rs.len) * NA) + k * RB));
+      const int cap = opaque_uniform(rs.len);  // (not formed ahead of the loop)
+      float* act = ra.base + rec_act(cap, N);
+      const uint32_t aoff = opaque((uint32_t)(rb_at(e, (NH + cap) * NA) + k * RB));
       if (ra.step == 0) {
 #pragma unroll
         for (int s = 0; s < NH; ++s) act[(size_t)(s * NA) * RB + aoff] = H.get(0, s);

@@ -235,7 +235,7 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     StepRec<TILES> sr;
     if constexpr (TAPE) {
       sr.on = rec_on;
-      sr.buf = span_rsrc(ra.base, rec_on ? 4u * (uint32_t)rec_floats(rs.len, N) : 0u);
+      sr.buf = span_rsrc(ra.base, rec_on ? 4u * (uint32_t)rec_floats(opaque_uniform(rs.len), N) : 0u);
       const uint32_t l = opaque((uint32_t)lane);  // (not formed ahead of the loop)
       sr.z = 4u * (4 * (l >> 4) * RB + (l & 15));
 #pragma unroll
@@ -254,13 +254,14 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     to_tiles<TILES>(a, lg, at);
     if (TAPE && rec_on) {
       const uint32_t l = opaque((uint32_t)lane), ko = 4u * ((l >> 4) * RB + (l & 15));  // row lg
+      const int cap = opaque_uniform(rs.len);  // (not formed ahead of the loop)
 #pragma unroll
       for (int tl = 0; tl < TILES; ++tl) {
         // the state features, masks and actions; the history features are
         // earlier actions, kept on the segment's action tape (the
         // checkpoint's history first, then a_t)
         const uint32_t act =
-            4u * (uint32_t)(rec_act(rs.len, N) + rb_at(env0 + 16 * tl, (NH + rs.len) * NA));
+            4u * (uint32_t)(rec_act(cap, N) + rb_at(env0 + 16 * tl, (NH + cap) * NA));
 #pragma unroll
         for (int q = 0; q < 5; ++q)
           if (q < 4 || lg < 2) bst1(F[tl][q], sr.buf, ko, sr.s[tl] + 4u * (REC_O + 4 * q) * RB);
