@@ -113,9 +113,11 @@ enum {
   SIM_V_PLAIN = 1,       /* five kernels per step, intermediates through HBM      */
   SIM_V_FUSED_VALU = 2,  /* one fused kernel, actor on the vector ALUs            */
   SIM_V_FUSED_MFMA = 3,  /* one fused kernel, actor on matrix cores, 32 envs per wave:
-                            fp32 weights and inputs as exact sums of three bf16
-                            values, six bf16 products per fp32 product, fp32
-                            accumulation (closer to FP64 than an fp32 chain)     */
+                            fp32 weights and inputs as sums of three bf16 values, six
+                            bf16 products per fp32 product, fp32 accumulation
+                            (closer to FP64 than an fp32 chain); a NaN among an
+                            env's inputs, or a weight that is not finite, gives NaN
+                            actions, an infinite input some finite ones           */
   SIM_V_FUSED_MFMA4 = 4, /* the same with 16 envs per wave, four lanes per env (twice
                             the waves; equal results)                            */
   SIM_V_FUSED_SPLIT = 5  /* the same products, the actor split by neuron tile over the 4

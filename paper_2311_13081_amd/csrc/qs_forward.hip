@@ -165,6 +165,7 @@ __global__ void __launch_bounds__(256) k_plain_l1(int N, const float* __restrict
                                                   const float* __restrict__ in,
                                                   float* __restrict__ out) {
   __shared__ u4t sW[T_G2 * T_P * 64];
+  __shared__ uint32_t flags[4];
   const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
   const int first = blockIdx.x * P_ENVS + 32 * (threadIdx.x >> 6);
   // every input load in flight before the weights are staged
@@ -181,7 +182,7 @@ __global__ void __launch_bounds__(256) k_plain_l1(int N, const float* __restrict
     if (lg >= 2) F[b][4] = 0.0f;  // features 18, 19: padding
   }
   __builtin_amdgcn_sched_barrier(0);
-  stage_fragments<4>(W, sW, T_G2, tile_src);
+  set_flag(!stage_fragments<4>(W, sW, T_G2, tile_src), flags);
   __syncthreads();
   if (first >= N) return;
   u4t x[4][2][T_P], xs[1][2][T_P];
@@ -208,9 +209,16 @@ __global__ void __launch_bounds__(256) k_plain_l1(int N, const float* __restrict
 #pragma unroll
     for (int b = 0; b < 2; ++b) a1[n][b] = h[0][b] + as[0][b];
   }
+  const bool bad_actor = any_flag(flags);
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
     const int oe = first + 16 * b + li;
+    const uint64_t nan = nan_slots(a1[0][b], [&](int s) {
+      return in[(size_t)(18 + NA * s + lg) * N + min(oe, N - 1)];
+    });
+#pragma unroll
+    for (int r = 0; r < 4; ++r) a1[0][b][r] = relu_bits(a1[0][b][r]);
+    carry_nan(a1[0][b], (bad_actor ? ~0ull : nan) | nan_lanes(F[b]));
     if (oe < N)
 #pragma unroll
       for (int n = 0; n < 4; ++n)
@@ -225,6 +233,7 @@ __global__ void __launch_bounds__(256) k_plain_l2(int N, const float* __restrict
                                                   const float* __restrict__ in,
                                                   float* __restrict__ out) {
   __shared__ u4t sW[(T_G - T_G2) * T_P * 64];
+  __shared__ uint32_t flags[4];
   const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
   const int first = blockIdx.x * P_ENVS + 32 * (threadIdx.x >> 6);
   f4t h1[4][2];
@@ -237,8 +246,9 @@ __global__ void __launch_bounds__(256) k_plain_l2(int N, const float* __restrict
       for (int r = 0; r < 4; ++r) h1[n][b][r] = in[(size_t)(16 * n + 4 * lg + r) * N + e];
   }
   __builtin_amdgcn_sched_barrier(0);
-  stage_fragments<4>(W, sW, T_G - T_G2,
-                     [](int g, int l, int e) { return tile_src(T_G2 + g, l, e); });
+  set_flag(!stage_fragments<4>(W, sW, T_G - T_G2,
+                               [](int g, int l, int e) { return tile_src(T_G2 + g, l, e); }),
+           flags);
   __syncthreads();
   if (first >= N) return;
   u4t x[2][2][T_P];
@@ -257,9 +267,13 @@ __global__ void __launch_bounds__(256) k_plain_l2(int N, const float* __restrict
 #pragma unroll
     for (int b = 0; b < 2; ++b) a2[n][b] = acc[0][b] + b2;
   }
+  const bool bad_actor = any_flag(flags);
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
     const int oe = first + 16 * b + li;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) a2[0][b][r] = relu_bits(a2[0][b][r]);
+    carry_nan(a2[0][b], (bad_actor ? ~0ull : 0ull) | __ballot(h1[0][b][0] != h1[0][b][0]));
     if (oe < N)
 #pragma unroll
       for (int n = 0; n < 4; ++n)

@@ -44,13 +44,19 @@ struct SplitActor {
   Frags<1> hist[4], state, l2[2];
   f4t b2, b3, w3[4];
 
-  __device__ inline void load(const float* __restrict__ W, int w, int lane) {
+  // false where a weight of the lane's share has no split
+  __device__ inline bool load(const float* __restrict__ W, int w, int lane) {
     const int lg = lane >> 4;
+    uint32_t third = 0;
+    const auto get = [&](int g, u4t (&a)[T_P]) {
+      load_fragment(W, g, lane, a);
+      third |= (a[2][0] | a[2][1]) | (a[2][2] | a[2][3]);
+    };
 #pragma unroll
-    for (int c = 0; c < 4; ++c) load_fragment(W, 4 * w + c, lane, hist[c].a[0]);
-    load_fragment(W, T_GS + w, lane, state.a[0]);
+    for (int c = 0; c < 4; ++c) get(4 * w + c, hist[c].a[0]);
+    get(T_GS + w, state.a[0]);
 #pragma unroll
-    for (int m = 0; m < 2; ++m) load_fragment(W, T_G2 + 2 * w + m, lane, l2[m].a[0]);
+    for (int m = 0; m < 2; ++m) get(T_G2 + 2 * w + m, l2[m].a[0]);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       b2[r] = W[OFF_B2 + 16 * w + 4 * lg + r];
@@ -58,6 +64,15 @@ struct SplitActor {
 #pragma unroll
       for (int n = 0; n < 4; ++n) w3[n][r] = W[OFF_W3 + (lane & 3) * NHID + 16 * n + 4 * lg + r];
     }
+    bool ok = true;
+    if (__builtin_expect(__ballot(maybe_unsplit(third)) != 0, 0)) {
+      const u4t t[7] = {hist[0].a[0][2], hist[1].a[0][2], hist[2].a[0][2], hist[3].a[0][2],
+                        state.a[0][2],   l2[0].a[0][2],   l2[1].a[0][2]};
+#pragma unroll
+      for (int i = 0; i < 7; ++i)
+        ok = ok && !(unsplit(t[i][0]) || unsplit(t[i][1]) || unsplit(t[i][2]) || unsplit(t[i][3]));
+    }
+    return ok;
   }
   // layer 1's history sums of the wave's unit tile
   __device__ inline void history(const TileHist<1>& H, f4t (&a1)[1][1]) const {
@@ -75,10 +90,12 @@ struct SplitActor {
 // in every lane of every wave.  When rec != NULL (the step's record), writes
 // this wave's tile of the layer pre-activations (rows 16 w + 4 lg + r; zoff
 // addresses row 4 lg of this lane's env) and its byte of the ReLU mask word
-// (tile_mask; moff addresses the word), for lanes with on set.
+// (tile_mask; moff addresses the word), for lanes with on set.  lost: lanes that
+// carry_nan whatever their features are, in the wave's tile.
 __device__ inline void actor_split(const SplitActor& A, SplitXch& xc, f4t (&a1)[1][1],
-                                   const float F[5], float z3[NA], float* __restrict__ rec,
-                                   bool on, uint32_t zoff, uint32_t moff, int w) {
+                                   const float (&F)[5], uint64_t lost, float z3[NA],
+                                   float* __restrict__ rec, bool on, uint32_t zoff, uint32_t moff,
+                                   int w) {
   const int lane = threadIdx.x & 63;
   {
     u4t x[1][1][T_P];
@@ -105,6 +122,7 @@ __device__ inline void actor_split(const SplitActor& A, SplitXch& xc, f4t (&a1)[
       *(reinterpret_cast<uint2*>(&xc.x1[s][w >> 1][lane]) + (w & 1)) = uint2{p[s], q[s]};
   }
   __syncthreads();
+  uint64_t nan;
   f4t a2[1][1];
   {
     u4t x[2][1][T_P];
@@ -112,6 +130,10 @@ __device__ inline void actor_split(const SplitActor& A, SplitXch& xc, f4t (&a1)[
     for (int m = 0; m < 2; ++m)
 #pragma unroll
       for (int s = 0; s < T_P; ++s) x[m][0][s] = xc.x1[s][m][lane];
+    // (while the reads are on their way)
+    __builtin_amdgcn_sched_barrier(0);
+    nan = lost | nan_lanes(F);
+    __builtin_amdgcn_sched_barrier(0);
     split_sum<2, 1, 1>([&](int m) { return A.l2[m]; }, x, a2);
     a2[0][0] += A.b2;
   }
@@ -124,6 +146,7 @@ __device__ inline void actor_split(const SplitActor& A, SplitXch& xc, f4t (&a1)[
     if (on) reinterpret_cast<uint8_t*>(rec + (size_t)REC_M * RB + moff)[w] = (uint8_t)mask;
   }
   relu_tiles(a2);
+  carry_nan(a2[0][0], nan);
   xc.x2[w][lane] = a2[0][0];
   __syncthreads();
   f4t h2[4][1];
@@ -155,7 +178,8 @@ k_split(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
   const int lane = threadIdx.x & 63, j = lane & 15, k = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   SplitActor A;
-  A.load(W, w, lane);
+  // (of the wave's share; its layer-2 tile tells the other waves)
+  const bool bad_actor = __ballot(!A.load(W, w, lane)) != 0;
   const bool writer = w == 0;
   const int env = env0 + j;
   const bool active = env < N;
@@ -237,6 +261,12 @@ k_split(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
 
   f4t a1[1][1];  // layer 1's history sums of the coming step
   A.history(H, a1);
+  // lanes that carry_nan in the first step
+  uint64_t lost = nan_slots(a1[0][0], [&](int s) {
+    if (REC) return ck_in[(size_t)(NS + s * NA + k) * N + e];
+    return b.ring[(size_t)(((head0 + s) & (NH - 1)) * NA + k) * N + e];
+  });
+  if (bad_actor) lost = ~0ull;
   drain_loads();
   for (int t = 0; t < T; ++t) {
     const uint32_t so = opaque(ok);
@@ -267,7 +297,8 @@ k_split(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     const uint32_t zoff = TAPE ? opaque((uint32_t)(rb_at(env0 + j, REC_F) + 4 * k * RB)) : 0u;
     const uint32_t moff = TAPE ? opaque((uint32_t)(rb_at(env0 + j, REC_F) + k * RB)) : 0u;
     float z3[NA];
-    actor_split(A, xc, a1, F[0], z3, TAPE ? rt : nullptr, active, zoff, moff, w);
+    actor_split(A, xc, a1, F[0], lost, z3, TAPE ? rt : nullptr, active, zoff, moff, w);
+    lost = bad_actor ? ~0ull : 0ull;
     float a[NA], ak[1];
 #pragma unroll
     for (int i = 0; i < NA; ++i) a[i] = tanh_act(z3[i]);

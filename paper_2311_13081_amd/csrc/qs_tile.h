@@ -14,9 +14,11 @@
 //       4, the order in which the layer-1 result registers arrive (register r
 //       of result tile n: unit 16 n + 4 lg + r of env 16 b + li).
 //
-// fp32 products by splitting.  An fp32 value is the sum of three bf16 values
-// (its bf16 rounding, the rounding of what is left, and the rest: 24 bits in
-// all, exact), and a product of two such sums keeps the six terms down to
+// fp32 products by splitting.  An fp32 value from about 2^-110 up to bf16's
+// largest is the sum of three bf16 values (its bf16 rounding, the rounding of what
+// is left, and the rest: 24 bits in all, exact; smaller ones lose bits below
+// 2^-133, and infinities, NaN and magnitudes that round past bf16's largest have no
+// split: "No split" below), and a product of two such sums keeps the six terms down to
 // 2^-16 of the leading one; the three left out are below 2^-25.  The six
 // products run at 16 times the rate of the fp32 shapes, 2.7 times per fp32
 // product, and overlap with vector instructions, which the fp32 shapes do
@@ -29,6 +31,8 @@
 // into an offset).  The order of the terms is the same in every kernel, so they
 // agree bit for bit.
 #pragma once
+#include <type_traits>
+
 #include "qs_device.h"
 
 namespace qs {
@@ -72,6 +76,35 @@ __device__ inline uint32_t pack_bf16(float a, float b) {
 __device__ inline float bf_lo(uint32_t p) { return __uint_as_float(p << 16); }
 __device__ inline float bf_hi(uint32_t p) { return __uint_as_float(p & 0xffff0000u); }
 
+// No split.  The second and third part of an infinity or NaN are NaN, so every sum of
+// its env's column is NaN, of the sign that the ReLU (a maximum of the bit patterns)
+// takes as zero; the columns of other envs are as without it.  For an infinite input
+// that leaves finite actions, as mixed infinities do in an fp32 chain.  But a NaN input or
+// weight has to give NaN actions: an env that has lost its state, or a policy that
+// has diverged, would otherwise look sound.  So NaN is carried past the products: a
+// lane that has one among its features (or its history at the start of a launch; a
+// NaN action shows in the next step's state) makes one of its layer-2 units NaN
+// (carry_nan), and with a weight that has no split every lane does, in every step.
+// Four instructions a tile and step.
+// (As masks of the wave's lanes, which take no vector register.)
+__device__ __forceinline__ uint64_t nan_lanes(const float (&F)[5]) {
+  return __ballot(__builtin_isunordered(F[0], F[1])) | __ballot(__builtin_isunordered(F[2], F[3])) |
+         __ballot(F[4] != F[4]);
+}
+__device__ __forceinline__ void carry_nan(f4t& h2, uint64_t nan) {
+  h2[0] = pick(__builtin_amdgcn_inverse_ballot_w64(nan), __uint_as_float(0x7fc00000u), h2[0]);
+}
+// Whether v holds in a thread of the workgroup: set_flag, a barrier, any_flag.  flags: a
+// word per wave.
+__device__ inline void set_flag(bool v, uint32_t* flags) {
+  const uint64_t m = __ballot(v);
+  if ((threadIdx.x & 63) == 0) flags[threadIdx.x >> 6] = m != 0;
+}
+__device__ inline bool any_flag(const uint32_t* flags) {
+  const int last = (int)(blockDim.x >> 6) - 1;
+  return __ballot(flags[min((int)(threadIdx.x & 63), last)] != 0) != 0;
+}
+
 // The parts of a pair of values, packed: p[0] + p[1] + p[2] is the value.
 __device__ inline void split_pair(float a, float b, uint32_t p[T_P]) {
   p[0] = pack_bf16(a, b);
@@ -80,6 +113,13 @@ __device__ inline void split_pair(float a, float b, uint32_t p[T_P]) {
   p[1] = pack_bf16(a, b);
   p[2] = pack_bf16(a - bf_lo(p[1]), b - bf_hi(p[1]));
 }
+
+// Weights are looked at by their third parts, words w: bit 14 of a half is set where it
+// is 2 or more, infinite or NaN (the weight 2^18 or more, or without a split), so the
+// bits of a thread's share or-ed together (an instruction for three words: this is
+// in every launch) mostly settle it.
+__device__ inline bool maybe_unsplit(uint32_t bits) { return (bits & 0x40004000u) != 0; }
+__device__ inline bool unsplit(uint32_t w) { return __builtin_isunordered(bf_lo(w), bf_hi(w)); }
 
 // The fragment of group g of lane l, straight from the actor.
 __device__ inline void load_fragment(const float* __restrict__ W, int g, int l, u4t (&a)[T_P]) {
@@ -102,11 +142,13 @@ __device__ inline void load_fragment(const float* __restrict__ W, int g, int l, 
 // Stages n groups of fragments at dst, src(g, l, e) the source index of element e
 // of lane l in group g (-1 for padding), every thread of the workgroup taking
 // (group, lane) pairs, the loads of MAXT pairs in flight at a time.  bf16: the
-// weights rounded to bf16 first.
+// weights rounded to bf16 first.  False where a weight of the thread's share has no
+// split.
 template <int MAXT, typename Src>
-__device__ inline void stage_fragments(const float* __restrict__ W, u4t* dst, int groups, Src src,
+__device__ inline bool stage_fragments(const float* __restrict__ W, u4t* dst, int groups, Src src,
                                        bool bf16 = false) {
   const int nt = blockDim.x, n = groups * 64;
+  uint32_t third = 0;
   for (int base = threadIdx.x; base < n; base += MAXT * nt) {
     float v[MAXT][8];
 #pragma unroll
@@ -134,13 +176,21 @@ __device__ inline void stage_fragments(const float* __restrict__ W, u4t* dst, in
       }
 #pragma unroll
       for (int s = 0; s < T_P; ++s) dst[((t >> 6) * T_P + s) * 64 + (t & 63)] = o[s];
+      third |= (o[2][0] | o[2][1]) | (o[2][2] | o[2][3]);
     }
   }
+  bool ok = true;
+  if (maybe_unsplit(third))
+    for (int t = threadIdx.x; t < n; t += nt) {
+      const u4t w = dst[((t >> 6) * T_P + 2) * 64 + (t & 63)];  // the thread's own
+      ok = ok && !(unsplit(w[0]) || unsplit(w[1]) || unsplit(w[2]) || unsplit(w[3]));
+    }
+  return ok;
 }
 
-// The whole actor into LDS.
-__device__ inline void stage_tile(const float* __restrict__ W, float* lds) {
-  stage_fragments<4>(W, reinterpret_cast<u4t*>(lds), T_G, tile_src);
+// The whole actor into LDS; false where a weight of the thread's share has no split.
+__device__ inline bool stage_tile(const float* __restrict__ W, float* lds) {
+  const bool ok = stage_fragments<4>(W, reinterpret_cast<u4t*>(lds), T_G, tile_src);
   for (int i = threadIdx.x; i < NHID + NA * T_W3_LD + NA; i += blockDim.x) {
     if (i < NHID) {
       lds[T_B2 + i] = W[OFF_B2 + i];
@@ -152,6 +202,7 @@ __device__ inline void stage_tile(const float* __restrict__ W, float* lds) {
       lds[T_B3 + o] = W[OFF_B3 + o];
     }
   }
+  return ok;
 }
 
 __device__ inline f4t mfma_bf(u4t a, u4t b, f4t c) {
@@ -510,7 +561,7 @@ struct TileHist {
           h[b][s][q >> 2][q & 3] = on[b] ? p[s] : h[b][s][q >> 2][q & 3];
     }
   }
-  // the value of slot sl (the sum of its parts, exact)
+  // the value of slot sl (the sum of its parts, exact; an infinity is its first part)
   __device__ inline float get(int b, int sl) const {
     const int q = sl >> 1;
     float p[3];
@@ -519,9 +570,24 @@ struct TileHist {
       const uint32_t w = h[b][s][q >> 2][q & 3];
       p[s] = sl & 1 ? bf_hi(w) : bf_lo(w);
     }
-    return p[0] + (p[1] + p[2]);
+    return pick(fabsf(p[0]) < __uint_as_float(0x7f800000u), p[0] + (p[1] + p[2]), p[0]);
   }
 };
+
+// The lanes with a NaN among their 32 history values slot(s) of a tile, of which a1 are
+// layer 1's sums: these are NaN in every unit then, so most launches look no further.
+template <typename Slot>
+__device__ inline uint64_t nan_slots(const f4t& a1, Slot&& slot) {
+  uint64_t m = 0;
+  if (__builtin_expect(__ballot(a1[0] != a1[0]) != 0, 0)) {
+#pragma unroll 1
+    for (int s = 0; s < NH; ++s) {
+      const float v = slot(s);
+      m |= __ballot(v != v);
+    }
+  }
+  return m;
+}
 
 // Layer 1's history sums of unit tiles n0 .. n0 + NN - 1.  They need the actions
 // only, so a step's share is evaluated while the step before integrates its
@@ -604,12 +670,21 @@ __device__ inline void reset_history(const float* lds, const bool (&on)[TILES],
 // The rest of the actor for the wave's tiles: z3 (pre-tanh) of the lane's own
 // env in every lane.  a1: layer 1's history sums (consumed); F: the state
 // features 4 e + lg of each tile's env.  rec takes the layer results before the
-// ReLU (the record of taped rollouts).
+// ReLU (the record of taped rollouts).  lost: lanes that carry_nan whatever their
+// features are.
 template <int TILES, typename Rec>
 __device__ inline void tile_actor(const float* lds, FragPipe<TILES>& fp, f4t (&a1)[4][TILES],
-                                  const float (&F)[TILES][5], float z3[NA], Rec&& rec) {
+                                  const float (&F)[TILES][5], const uint64_t (&lost)[TILES],
+                                  float z3[NA], Rec&& rec) {
   constexpr int NN = T_NN<TILES>;
   const int lg = (int)opaque((threadIdx.x & 63) >> 4);
+  // (with a record the features are kept anyway, and are looked at where the mask is
+  // used)
+  constexpr bool LATE = std::remove_reference_t<Rec>::KEEPS_FEATURES;
+  uint64_t nan[TILES];
+#pragma unroll
+  for (int b = 0; b < TILES; ++b)
+    if (!LATE) nan[b] = lost[b] | nan_lanes(F[b]);
   {
     u4t x[1][TILES][T_P];
 #pragma unroll
@@ -647,6 +722,11 @@ __device__ inline void tile_actor(const float* lds, FragPipe<TILES>& fp, f4t (&a
   }
   rec.layer2(a2);
   relu_tiles(a2);
+#pragma unroll
+  for (int b = 0; b < TILES; ++b) {
+    if (LATE) nan[b] = lost[b] | nan_lanes(F[b]);
+    carry_nan(a2[0][b], nan[b]);
+  }
   Layer3 l3;
   l3.load(lds + T_W3, lds + T_B3);
   tile_layer3<TILES>(l3.w, l3.b, a2, z3);
@@ -654,6 +734,7 @@ __device__ inline void tile_actor(const float* lds, FragPipe<TILES>& fp, f4t (&a
 
 // No record.
 struct NoRec {
+  static constexpr bool KEEPS_FEATURES = false;
   template <typename A>
   __device__ inline void layer1(const A&) {}
   template <typename A>

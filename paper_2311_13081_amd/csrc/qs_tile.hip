@@ -24,6 +24,7 @@ namespace qs {
 // last block.
 template <int TILES>
 struct StepRec {
+  static constexpr bool KEEPS_FEATURES = true;
   __amdgpu_buffer_rsrc_t buf;
   bool on;  // wave uniform
   uint32_t s[TILES], z, mask[TILES];
@@ -98,11 +99,13 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
        float* __restrict__ tape, int ckpt_every, const float* __restrict__ ck_in, RecSpan rs) {
   constexpr int SUB = 4 / TILES;  // lanes per env
   __shared__ __attribute__((aligned(16))) float lds[T_TOTAL + PK_F * T_MAX_THREADS];
-  static_assert((T_TOTAL + PK_F * T_MAX_THREADS) * 4 <= 160 * 1024, "weights and columns fit in LDS");
+  static_assert((T_TOTAL + PK_F * T_MAX_THREADS + T_MAX_THREADS / 64) * 4 <= 160 * 1024,
+                "weights and columns fit in LDS");
+  __shared__ uint32_t flags[T_MAX_THREADS / 64];
   const int N = c.n_envs;
-  stage_tile(W, lds);
-  __syncthreads();
   const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+  set_flag(!stage_tile(W, lds), flags);
+  __syncthreads();
   const int wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const int env0 = __builtin_amdgcn_readfirstlane(wave * 16 * TILES);
   if (env0 >= N) return;
@@ -198,6 +201,16 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
     for (int n = 0; n < 4; n += T_NN<TILES>) tile_history<TILES>(fp, H, n, a1);
   };
   history();
+  const bool bad_actor = any_flag(flags);
+  uint64_t lost[TILES];  // lanes that carry_nan in the first step
+#pragma unroll
+  for (int t = 0; t < TILES; ++t) {
+    const uint64_t m = nan_slots(a1[0][t], [&](int s) {
+      if (REC) return ck_in[(size_t)(NS + s * NA + lg) * N + et[t]];
+      return b.ring[(size_t)(((b.head[et[t]] + s) & (NH - 1)) * NA + lg) * N + et[t]];
+    });
+    lost[t] = bad_actor ? ~0ull : m;
+  }
   drain_loads();
   for (int t = 0; t < T; ++t) {
     // keeps the weight reads inside the step (hoisted out of the time loop
@@ -243,10 +256,12 @@ k_tile(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
         sr.mask[tl] = 0u;
         sr.s[tl] = 4u * (uint32_t)(rec_step(ra.step, N) + rb_at(env0 + 16 * tl, REC_F));
       }
-      tile_actor<TILES>(lds, fp, a1, F, z3, sr);
+      tile_actor<TILES>(lds, fp, a1, F, lost, z3, sr);
     } else {
-      tile_actor<TILES>(lds, fp, a1, F, z3, NoRec{});
+      tile_actor<TILES>(lds, fp, a1, F, lost, z3, NoRec{});
     }
+#pragma unroll
+    for (int tl = 0; tl < TILES; ++tl) lost[tl] = bad_actor ? ~0ull : 0ull;
     __builtin_amdgcn_s_setprio(0);
     float a[NA], at[TILES];
 #pragma unroll
