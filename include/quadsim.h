@@ -186,8 +186,8 @@ int sim_step(sim_handle* h, const float* actor, const float* actions, float* rew
  * per wave from 32769 envs, else 16 envs per wave; the quarter-lane kernel
  * for the bf16 actor), whatever variant is set or tuned, and also writes the
  * backward's records of its last segments (the last one on the split-actor
- * kernel, else up to eight, four where the batch leaves compute units idle),
- * whose recomputes the next sim_backward skips. */
+ * kernel, else up to eight, four where the batch leaves compute units idle or
+ * memory is short), whose recomputes the next sim_backward skips. */
 int sim_rollout(sim_handle* h, const float* actor, int32_t T, float* rewards, uint8_t* dones,
                 float* states, int32_t record_tape, void* stream);
 

@@ -9,10 +9,12 @@ namespace qs {
 // caller's stream, weight gradients) with nbuf rotating segment buffers: one per
 // segment of the horizon up to BWD_NBUF (a segment without one is recomputed from
 // its checkpoint), those past the fourth only where no recompute overlaps the
-// sweep, all of them together stay below BWD_MORE_BYTES and memory is there.
+// sweep, all of them together stay below BWD_MORE_BYTES and each is at most one part
+// in BWD_MORE_SHARE of the memory that is free after everything else.
 constexpr int BWD_NBUF = 8;
 constexpr int BWD_NBUF_MIN = 4;
 constexpr double BWD_MORE_BYTES = 8e9;
+constexpr size_t BWD_MORE_SHARE = 16;
 struct BwdBufs {
   int N = 0, K = 0, H = 0;
   int nbuf = 0;                       // segment buffers allocated

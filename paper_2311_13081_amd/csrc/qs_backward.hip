@@ -939,29 +939,25 @@ hipError_t bwd_alloc(BwdBufs& bw, int N, int K, int H) {
   int nseg = (H + K - 1) / K < most ? (H + K - 1) / K : most;
   while (nseg > BWD_NBUF_MIN && (double)nseg * (double)(seg_bytes + dz_bytes) > BWD_MORE_BYTES)
     --nseg;
-  bw.nbuf = nseg;
+  const auto add_buffer = [&]() -> hipError_t {
+    const int i = bw.nbuf;
+    hipError_t e = hipMalloc(&bw.seg[i], seg_bytes);
+    if (e == hipSuccess) e = hipMalloc(&bw.dz[i], dz_bytes);
+    // zeroed once: whole wavefronts past the last env never write their slots
+    // of the last 64-env block, which must read as finite (record) and zero
+    // (cotangents) in the weight-gradient pass
+    if (e == hipSuccess) e = hipMemset(bw.seg[i], 0, seg_bytes);
+    if (e == hipSuccess) e = hipMemset(bw.dz[i], 0, dz_bytes);
+    if (e == hipSuccess) ++bw.nbuf;
+    return e;
+  };
   for (int i = 0; i < BWD_NBUF; ++i) {
     if ((e = hipEventCreateWithFlags(&bw.e_rec[i], hipEventDisableTiming)) != hipSuccess) return e;
     if ((e = hipEventCreateWithFlags(&bw.e_rev[i], hipEventDisableTiming)) != hipSuccess) return e;
     if ((e = hipEventCreateWithFlags(&bw.e_dw[i], hipEventDisableTiming)) != hipSuccess) return e;
-    if (i >= bw.nbuf) continue;
-    e = hipMalloc(&bw.seg[i], seg_bytes);
-    if (e == hipSuccess) e = hipMalloc(&bw.dz[i], dz_bytes);
-    if (e != hipSuccess && i >= BWD_NBUF_MIN) {
-      // no memory for one more: do without
-      (void)hipGetLastError();
-      if (bw.seg[i]) (void)hipFree(bw.seg[i]);
-      bw.seg[i] = bw.dz[i] = nullptr;
-      bw.nbuf = i;
-      continue;
-    }
-    if (e != hipSuccess) return e;
-    // zeroed once: whole wavefronts past the last env never write their slots
-    // of the last 64-env block, which must read as finite (record) and zero
-    // (cotangents) in the weight-gradient pass
-    if ((e = hipMemset(bw.seg[i], 0, seg_bytes)) != hipSuccess) return e;
-    if ((e = hipMemset(bw.dz[i], 0, dz_bytes)) != hipSuccess) return e;
   }
+  while (bw.nbuf < nseg && bw.nbuf < BWD_NBUF_MIN)
+    if ((e = add_buffer()) != hipSuccess) return e;
   int dev = 0;
   if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
   if ((e = hipDeviceGetAttribute(&bw.n_cu, hipDeviceAttributeMultiprocessorCount, dev)) !=
@@ -982,7 +978,22 @@ hipError_t bwd_alloc(BwdBufs& bw, int N, int K, int H) {
                                hipFuncAttributeMaxDynamicSharedMemorySize, (R_TOTAL + R_XCH) * 4)) !=
       hipSuccess)
     return e;
-  return reverse1_prepare();
+  if ((e = reverse1_prepare()) != hipSuccess) return e;
+  // The buffers past the fourth only save time: last, so that they take nothing the
+  // handle needs, and each only where it is a small part of the free memory, most of
+  // which is left to the caller.
+  size_t free_bytes = 0, all_bytes = 0;
+  while (bw.nbuf < nseg && hipMemGetInfo(&free_bytes, &all_bytes) == hipSuccess &&
+         seg_bytes + dz_bytes <= free_bytes / BWD_MORE_SHARE) {
+    if (add_buffer() == hipSuccess) continue;
+    const int i = bw.nbuf;
+    if (bw.seg[i]) (void)hipFree(bw.seg[i]);
+    if (bw.dz[i]) (void)hipFree(bw.dz[i]);
+    bw.seg[i] = bw.dz[i] = nullptr;
+    break;
+  }
+  (void)hipGetLastError();  // of the calls for optional memory
+  return hipSuccess;
 }
 
 void bwd_free(BwdBufs& bw) {
