@@ -12,6 +12,13 @@ from . import _lib
 from ._lib import check
 
 
+# Names the kernels behind the variant numbers in autotune's cache: raised whenever what
+# a number runs, or which is the fastest, changes, so that an older file's choices are
+# not taken over.  (1, not written in the key: one env per lane under number 3, an fp32
+# quarter-lane kernel under 4.)
+VARIANT_KERNELS = 2
+
+
 def _ptr(t: torch.Tensor | None):
     if t is None:
         return None
@@ -295,12 +302,13 @@ class QuadSim:
     def autotune(self, actor: torch.Tensor, T: int, cache: str | None = None):
         """Times the variants on a T-step rollout and keeps the fastest.  With
         `cache` (a JSON file path), a result stored for the same (N, flags, T,
-        device architecture) is reused instead of timing again, and new
-        results are added to the file."""
+        device architecture) and the same kernels (VARIANT_KERNELS) is reused instead
+        of timing again, and new results are added to the file."""
         key = None
         if cache is not None:
             arch = torch.cuda.get_device_properties(self.device).gcnArchName.split(":")[0]
-            key = f"N={self.N} flags={int(self.cfg['flags'])} T={int(T)} arch={arch}"
+            key = (f"N={self.N} flags={int(self.cfg['flags'])} T={int(T)} arch={arch} "
+                   f"kernels={VARIANT_KERNELS}")
             table = {}
             if os.path.exists(cache):
                 with open(cache) as f:
