@@ -467,8 +467,11 @@ __device__ inline void rk4_step(const Body<R>& B, R arm, R km, R g, R h, bool re
 // position, whose increment is h v + h^2/6 (k1 + k2 + k3); inertias are folded
 // into the torque arms and the gyroscopic factors.  The rotor speeds are stored
 // to 1e-3 RPM, and open-loop flights integrate that rounding twice: their
-// arithmetic is rk4_step's to the bit.  Every product that meets a sum is an
-// explicit fused multiply-add, so the kernels round alike.
+// arithmetic is rk4_step's to the bit.  Most products that meet a sum are explicit
+// fused multiply-adds; of the others (the rotor lag, the velocity rows, the reward)
+// the compiler decides in each instantiation, so held actions and an action set per
+// step may differ in the last place.  Single steps and held actions run one
+// instantiation and agree.
 // ---------------------------------------------------------------------------
 struct Quad {
   float inv_m, c0, c1, c2;

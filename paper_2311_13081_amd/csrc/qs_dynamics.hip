@@ -99,14 +99,23 @@ k_dyn_rollout(DevCfg c, SimBufs b, const float* __restrict__ act, int a_tstride,
   // are written.
   const int head1 = (b.head[e] + T) & (NH - 1);
   const int n_new = T - 1 - last_reset;  // actions pushed since the last reset (or all T)
+  const auto slot_of = [&](int age) {    // 0 = newest
+    return b.ring + (size_t)(((head1 - 1 - age) & (NH - 1)) * NA) * N + e;
+  };
+  if (last_reset >= 0)
+#pragma unroll 8
+    for (int age = 0; age < NH; ++age) {
+      if (age < n_new) continue;
+      float* p = slot_of(age);
+#pragma unroll
+      for (int i = 0; i < NA; ++i) p[(size_t)i * N] = ah;
+    }
 #pragma unroll 1
-  for (int s = 0; s < NH; ++s) {
-    const int age = NH - 1 - s;  // 0 = newest
-    if (age >= n_new && last_reset < 0) continue;
-    const size_t slot = (size_t)((head1 + s) & (NH - 1)) * NA;
+  for (int age = 0; age < NH && age < n_new; ++age) {
+    float* p = slot_of(age);
+#pragma unroll
     for (int i = 0; i < NA; ++i)
-      b.ring[(slot + i) * N + e] =
-          age < n_new ? act[((size_t)(T - 1 - age) * a_tstride + i) * N + e] : ah;
+      p[(size_t)i * N] = act[((size_t)(T - 1 - age) * a_tstride + i) * N + e];
   }
   b.head[e] = head1;
   b.t_ep[e] = t_ep;

@@ -38,8 +38,8 @@ hipError_t launch_reward_batch(const DevCfg& c, const float* s, const float* a, 
 // either may be NULL.
 hipError_t launch_observe(const DevCfg& c, const SimBufs& b, float* actor_obs, float* critic_obs,
                           hipStream_t st);
-// Dynamics-only rollout with given actions ([4][N] constant if a_tstride == 0,
-// [T][4][N] if a_tstride == 4).
+// Rollouts and single steps under given actions ([4][N] constant if a_tstride
+// == 0, [T][4][N] if a_tstride == 4).
 hipError_t launch_dyn_rollout(const DevCfg& c, const SimBufs& b, const float* act, int a_tstride,
                               int T, float* rewards, uint8_t* dones, float* states,
                               hipStream_t st);
@@ -158,9 +158,8 @@ inline TapedKernel taped_kernel(const DevCfg& c) {
   return c.n_envs <= TILE1_MAX_ENVS ? TAPED_TILE1 : TAPED_TILE2;
 }
 // One-env-per-lane fused kernel (qs_fused.hip): the actor on the vector ALUs,
-// or the bf16 actor under its flag, or given actions (ext_act, [T][4][N]).
-hipError_t launch_fused(const DevCfg& c, const SimBufs& b, const float* W, const float* ext_act,
-                        int T, int t_base, float* rewards, uint8_t* dones, float* states,
-                        hipStream_t st);
+// or the bf16 actor under its flag.
+hipError_t launch_fused(const DevCfg& c, const SimBufs& b, const float* W, int T, int t_base,
+                        float* rewards, uint8_t* dones, float* states, hipStream_t st);
 
 }  // namespace qs

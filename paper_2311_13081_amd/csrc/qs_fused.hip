@@ -1,13 +1,11 @@
 // Fused multi-step kernel of the batched quadrotor step with one env per
 // lane: observation, actor (vector ALUs; the bf16 option on bf16 matrix
-// cores; or given actions), action map, RK4, reward, history push, termination
-// and reset for T steps in one launch.
+// cores), action map, RK4, reward, history push, termination and reset for T
+// steps in one launch.
 //
 // Layout: struct-of-arrays in HBM ([K][N]) so every global access of a wave is
 // a contiguous 256-byte segment; actor weights are staged in LDS once per
 // workgroup.
-#include <type_traits>
-
 #include "qs_actor.h"
 #include "qs_forward.h"
 
@@ -19,33 +17,25 @@ namespace qs {
 // T steps of the whole step (observation, actor, action map, RK4, reward,
 // history push, termination, truncation, reset, episode accumulators) with
 // state and history kept in registers.  Outputs indexed by t_base + t.
-// ext_act ([T][4][N]) replaces the actor when non-NULL.  Inactive lanes of the last wave shadow the wave's
-// first env (read only) so every MFMA operand is finite.  EXTRAS (the
-// training extras or a set point are on): the episode disturbance enters the
-// dynamics and the actor sees its observation with noise and the set-point
-// shift; without them the kernel carries none of that code.
-//
-// ACT_GIVEN: the actions come from ext_act and the kernel holds no actor; without
-// them the loop issues no vector-memory load at all.  (Vector loads and stores
-// share one completion counter: a wait for a load issued in the loop would
-// also wait for every record and output store issued before it -- with the
-// external-action loads only on a runtime branch, the waits at the branch's
-// join would drain the step's stores on every step.)
-enum FusedActor { ACT_VALU, ACT_BF16, ACT_GIVEN };
+// Inactive lanes of the last wave shadow the wave's first env (read only) so
+// every MFMA operand is finite.  EXTRAS (the training extras or a set point are
+// on): the episode disturbance enters the dynamics and the actor sees its
+// observation with noise and the set-point shift; without them the kernel
+// carries none of that code.  The loop issues no vector-memory load: loads and
+// stores share one completion counter, so a wait for a load issued in the loop
+// would also wait for every output store issued before it.
+enum FusedActor { ACT_VALU, ACT_BF16 };
 
 template <bool EXTRAS, FusedActor ACT>
 __global__ void __launch_bounds__(256)
-k_fused(DevCfg c, SimBufs b, const float* __restrict__ W, const float* __restrict__ ext_act,
-        int T, int t_base, float* __restrict__ rewards, uint8_t* __restrict__ dones,
-        float* __restrict__ states) {
-  __shared__ __attribute__((aligned(16))) float lds[ACT == ACT_VALU   ? V_TOTAL
-                                                            : ACT == ACT_BF16 ? MB_TOTAL
-                                                                              : 4];
+k_fused(DevCfg c, SimBufs b, const float* __restrict__ W, int T, int t_base,
+        float* __restrict__ rewards, uint8_t* __restrict__ dones, float* __restrict__ states) {
+  __shared__ __attribute__((aligned(16))) float lds[ACT == ACT_VALU ? V_TOTAL : MB_TOTAL];
   const int N = c.n_envs;
-  constexpr int DRAW = ACT == ACT_BF16 ? 1 : ACT == ACT_VALU ? 0 : -1;
+  constexpr int DRAW = ACT == ACT_BF16 ? 1 : 0;
   if constexpr (ACT == ACT_VALU) stage_actor(W, lds);
   if constexpr (ACT == ACT_BF16) stage_actor_bf16(W, lds);
-  if constexpr (ACT != ACT_GIVEN) __syncthreads();
+  __syncthreads();
   const int env = blockIdx.x * blockDim.x + threadIdx.x;
   const int first = env - (threadIdx.x & 63);
   if (first >= N) return;  // whole wave past the end
@@ -55,12 +45,7 @@ k_fused(DevCfg c, SimBufs b, const float* __restrict__ W, const float* __restric
   float th[NP];
 #pragma unroll
   for (int i = 0; i < NP; ++i) th[i] = b.theta[i * N + e];
-  // given actions take the dynamics-only rollout's form of the step
-  std::conditional_t<ACT == ACT_GIVEN, Quad, Body<float>> B;
-  if constexpr (ACT == ACT_GIVEN)
-    B = make_quad(c, th);
-  else
-    B = make_body<float>(th);
+  Body<float> B = make_body<float>(th);
   const bool renorm = (c.flags & F_RENORM_Q) != 0;
 
   float x[NS];
@@ -104,10 +89,7 @@ k_fused(DevCfg c, SimBufs b, const float* __restrict__ W, const float* __restric
     const uint32_t eo = opaque((uint32_t)e);
     const int gt = t_base + t;
     float a[NA];
-    if constexpr (ACT == ACT_GIVEN) {
-#pragma unroll
-      for (int i = 0; i < NA; ++i) a[i] = ext_act[((size_t)t * NA + i) * N + eo];
-    } else {
+    {
       float Rm[9];
       rotmat(x + 3, Rm);
       float z3[NA];
@@ -139,14 +121,10 @@ k_fused(DevCfg c, SimBufs b, const float* __restrict__ W, const float* __restric
 #pragma unroll
       for (int i = 0; i < NA; ++i) a[i] = tanh_act(z3[i]);
     }
-    if constexpr (ACT == ACT_GIVEN) {
-      quad_step<EXTRAS>(B, c, renorm, x, a);
-    } else {
-      float u[NA];
+    float u[NA];
 #pragma unroll
-      for (int i = 0; i < NA; ++i) u[i] = action_to_rpm(c, a[i]);
-      rk4_step<float, EXTRAS>(B, c.arm, c.km, c.g, c.dt, renorm, x, u);
-    }
+    for (int i = 0; i < NA; ++i) u[i] = action_to_rpm(c, a[i]);
+    rk4_step<float, EXTRAS>(B, c.arm, c.km, c.g, c.dt, renorm, x, u);
     const float r = reward(c, x, a);
     ++t_ep;
     const uint32_t d = episode_end(c, x, t_ep);
@@ -203,16 +181,14 @@ k_fused(DevCfg c, SimBufs b, const float* __restrict__ W, const float* __restric
 
 static inline unsigned nblk(int n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
-hipError_t launch_fused(const DevCfg& c, const SimBufs& b, const float* W, const float* ext_act,
-                        int T, int t_base, float* rewards, uint8_t* dones, float* states,
-                        hipStream_t st) {
+hipError_t launch_fused(const DevCfg& c, const SimBufs& b, const float* W, int T, int t_base,
+                        float* rewards, uint8_t* dones, float* states, hipStream_t st) {
   const dim3 g(nblk(c.n_envs, 256)), blk(256);
   const bool ex = (c.flags & (F_DISTURB | F_OBS_NOISE)) != 0 || c.target != nullptr;
   const bool bf = (c.flags & F_ACTOR_BF16) != 0;
-  auto k = ext_act ? (ex ? k_fused<true, ACT_GIVEN> : k_fused<false, ACT_GIVEN>)
-           : bf    ? (ex ? k_fused<true, ACT_BF16> : k_fused<false, ACT_BF16>)
-                   : (ex ? k_fused<true, ACT_VALU> : k_fused<false, ACT_VALU>);
-  hipLaunchKernelGGL(k, g, blk, 0, st, c, b, W, ext_act, T, t_base, rewards, dones, states);
+  auto k = bf ? (ex ? k_fused<true, ACT_BF16> : k_fused<false, ACT_BF16>)
+              : (ex ? k_fused<true, ACT_VALU> : k_fused<false, ACT_VALU>);
+  hipLaunchKernelGGL(k, g, blk, 0, st, c, b, W, T, t_base, rewards, dones, states);
   return hipGetLastError();
 }
 
