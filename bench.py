@@ -71,18 +71,28 @@ def split_roofline(achieved, flop, gemm):
             "frac": achieved / peak}
 
 
+# counter summaries by kernel, one for each launch shape the autotuner may pick
 TRAFFIC_PROFILES = {
-    "k_tile<2>": os.path.join(ROOT, "profiles", "k_tile2_fwd65536_dr_hbm_traffic.md"),
+    "k_tile<2>": [os.path.join(ROOT, "profiles", f) for f in
+                  ("k_tile2_fwd65536_dr_hbm_traffic.md",
+                   "k_tile2_fwd65536_dr_100_steps_hbm_traffic.md")],
 }
 
 
 def measured_traffic(kernel, n_envs, steps_per_launch):
-    """HBM bytes per launch from the committed counter summary of `kernel`,
-    or None when there is none, the kernel sources changed since the counters
-    were taken, or the launch shape differs."""
+    """HBM bytes per launch from the committed counter summaries of `kernel`,
+    or None when there is none of this launch shape, or the kernel sources
+    changed since the counters were taken."""
+    for path in TRAFFIC_PROFILES.get(kernel, ()):
+        t = traffic_of(path, n_envs, steps_per_launch)
+        if t is not None:
+            return t
+    return None
+
+
+def traffic_of(path, n_envs, steps_per_launch):
     import hashlib
-    path = TRAFFIC_PROFILES.get(kernel)
-    if path is None or not os.path.exists(path):
+    if not os.path.exists(path):
         return None
     fields = {}
     for line in open(path).read().splitlines():
@@ -126,6 +136,8 @@ def parse():
     ap.add_argument("--variant", default="auto", choices=["auto", "mfma4", "mfma", "valu", "split"],
                     help="auto = run the autotuner; otherwise a fixed fused kernel, one launch "
                          "per rollout (used for profiling so only timed launches appear)")
+    ap.add_argument("--steps-per-launch", type=int, default=0,
+                    help="with a fixed --variant: env steps per launch (0: the whole rollout)")
     return ap.parse_args()
 
 
@@ -468,7 +480,7 @@ def main():
     else:
         sim.set_variant({"mfma4": pkg.SIM_V_FUSED_MFMA4, "mfma": pkg.SIM_V_FUSED_MFMA,
                          "valu": pkg.SIM_V_FUSED_VALU, "split": pkg.SIM_V_FUSED_SPLIT}[args.variant],
-                        0, True)
+                        args.steps_per_launch, args.steps_per_launch == 0)
     v, spl, graph = sim.get_variant()
     wall, dev_ms, launches = time_rollouts(torch, sim, actor, T, args.steps, args.warmup)
     env_steps = N * T * args.steps

@@ -288,9 +288,12 @@ void drop_graph(sim_handle* h) {
 // Segments of a taped T-step rollout whose backward records the rollout
 // writes itself: the last ones, one per segment buffer.  Small batches (the
 // split-actor kernel) record only the last: their backward runs the other
-// recomputes beside the sweeps on a stream of their own, so recording more
-// in the forward, which nothing overlaps, measured slower (1024 x 64: 0.86
-// against 0.84 ms).
+// recomputes beside the sweeps on a stream of their own, and recording more
+// in the forward, which nothing overlaps, is slower while they fit there (forward
+// and backward of 64 steps, one segment against all four: 256 envs 594 and 609 us,
+// 1024 611 and 621).  From 2048 envs the recompute's workgroups and the sweep's
+// compete for the CUs and recording all would be faster (678 and 634; 4096: 936 and
+// 709).
 static_assert(REC_SEGS == BWD_NBUF, "one record segment per segment buffer");
 static int recorded_segments(const sim_handle* h, int T) {
   const int J = (T + h->cfg.ckpt_every - 1) / h->cfg.ckpt_every;

@@ -23,7 +23,9 @@ struct BwdBufs {
   int dw_groups = 1;                  // step groups per 64-env chunk
   int n_cu = 0;                       // compute units of the device
   float* seg[BWD_NBUF] = {};          // [K] steps of REC_F blocked rows (rb_at) per env: record
-  float* dz[BWD_NBUF] = {};           // [K] steps of 132 blocked rows per env: layer cotangents
+  // [K] steps of 132 blocked rows per env: layer cotangents dz1 (rows 0-63) and dz3
+  // (128-131); the rows between are not used (DZ_3)
+  float* dz[BWD_NBUF] = {};
   hipStream_t s_rec = nullptr, s_dw = nullptr;
   hipEvent_t e_init = nullptr, e_rec[BWD_NBUF] = {}, e_rev[BWD_NBUF] = {},
              e_dw[BWD_NBUF] = {};

@@ -142,10 +142,16 @@ __device__ __forceinline__ void reverse_observation(const float dob[40], const f
 // [10][64] (f4).
 constexpr int R_XCH = (2 * T_P + 2 * T_P + 10) * 64 * 4;
 // Batches up to this size run the split sweep (four times the waves; the
-// quarter-lane sweep leaves most SIMDs idle there).
+// quarter-lane sweep leaves most SIMDs idle there; a workgroup of either takes a CU,
+// so beyond 4096 envs the split one needs a second round: forward and backward of
+// 4097 envs x 64 steps 790 us on the quarter-lane sweep, 1065 on the split one).
 constexpr int REVERSE_SPLIT_MAX_ENVS = 4096;
-// From this size (fp32 actor) the one-env-per-lane sweep (qs_reverse1.hip):
-// one wave of 64 envs per SIMD and no repeated dynamics adjoint.
+// From this size (fp32 actor) the one-env-per-lane sweep (qs_reverse1.hip): one
+// round of 64-env waves, one per SIMD, up to 65536 envs, and no repeated dynamics
+// adjoint; the quarter-lane sweep takes a round per 16384 envs.  Forward and backward
+// of 64 steps, quarter-lane against one-lane: 32768 envs 1825 and 1957 us, 32769
+// 2490 and 2306, 49152 2660 and 2455, 65535 3550 and 3080.  The present kernels
+// cross at 32769 envs; the line is still where their fp32-product forms did.
 constexpr int REVERSE_LANE_MIN_ENVS = 65536;
 
 // Reverse sweep of one segment.  SPLIT = false: 16 envs per wave in the
@@ -684,8 +690,9 @@ __device__ inline void dw_pair(f4* acc, const DwOps& o, const char* sA, const fl
 // Barrier discipline: the four column groups run separate instantiations of
 // this loop, so their waves reach the workgroup barriers at different
 // program locations; the hardware barrier counts arriving waves, and every
-// wave executes the same sequence of barriers (one before the loop, two per
-// iteration but the last, iters uniform over the workgroup), so they pair up.
+// wave executes the same sequence of barriers (one before the loop, one at the end
+// of every iteration, another where the tape window is refilled; iters and the refills
+// are uniform over the workgroup), so they pair up.
 // A loop in the kernel body with the group switched per step would keep the
 // barriers in uniform code, but it keeps every group's operand slots live
 // across the switch and spills.
@@ -753,18 +760,16 @@ __device__ inline void dw_accumulate(f4* acc, const float* __restrict__ rec,
   }
 }
 
-// The workgroup's 64-env chunks x, x + gx, ... in turn; the barrier before
-// each chunk but the first lets every wave finish reading the previous
-// chunk's last staged step (its iteration ends without one).
+// The workgroup's 64-env chunks x, x + gx, ... in turn.  (A chunk's last iteration
+// ends with a barrier, so no wave still reads its staged step or its window when
+// the next one is staged.)
 template <int G, bool BF16>
 __device__ inline void dw_chunks(f4* acc, const float* __restrict__ rec,
                                  const float* __restrict__ dz, int N, int t_lo, int t_hi, int K,
                                  int half, char* sA, float* tw, const f4* w3) {
   const int n_chunks = (N + RB - 1) / RB;
-  for (int chunk = blockIdx.x; chunk < n_chunks; chunk += gridDim.x) {
-    if (chunk != (int)blockIdx.x) __syncthreads();
+  for (int chunk = blockIdx.x; chunk < n_chunks; chunk += gridDim.x)
     dw_accumulate<G, BF16>(acc, rec, dz, N, chunk, t_lo, t_hi, K, half, sA, tw, w3);
-  }
 }
 
 // A partial slot holds the sums in the accumulators' own register layout:
@@ -916,6 +921,10 @@ hipError_t bwd_alloc(BwdBufs& bw, int N, int K, int H) {
   // chunks, each split into step groups to fill the CUs; beyond n_cu chunks,
   // n_cu workgroups that each take every n_cu-th chunk in turn (one partial
   // slot per workgroup, whose sums stay in registers across its chunks).
+  // A group takes at least two steps: its start (the tape window, a first step
+  // staged beside nothing) costs more than the second step (forward and backward
+  // of 1024 envs x 64 steps 612 us; with groups of one step, on twice the CUs, 640;
+  // no difference at 64 and 256 envs).
   const int chunks = (int)nb(N, 64);
   int n_cu = 256;
   {
@@ -924,7 +933,7 @@ hipError_t bwd_alloc(BwdBufs& bw, int N, int K, int H) {
       (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
   }
   int S = n_cu / chunks;
-  if (S > K / 2) S = K / 2;  // at least two steps per group: one per half
+  if (S > K / 2) S = K / 2;
   if (S < 1) S = 1;
   bw.dw_gx = chunks < n_cu ? chunks : n_cu;
   bw.dw_groups = S;
@@ -933,7 +942,11 @@ hipError_t bwd_alloc(BwdBufs& bw, int N, int K, int H) {
   // a horizon of J segments uses min(J, BWD_NBUF) of the rotating buffers, fewer
   // where they are large or where a recompute runs beside the sweep (overlap):
   // elsewhere every segment kept spares its recompute (16384 envs x 128 steps, K =
-  // 16: 2350 us with four, 1982 with eight)
+  // 16: 2350 us with four, 1982 with eight).  Forward and backward of 128 steps, K =
+  // 8 (64 steps, K = 16), four buffers with the overlap against eight without: 6000
+  // envs 1575 (797) against 2255 (866) us, 12288 2180 (920) against 2470 (978), 16320
+  // 2695 (1033) against 2544 (1009), so the line by compute units lies within a few
+  // percent of the crossing.
   const size_t seg_bytes = rec_floats(K, N) * 4, dz_bytes = (size_t)K * DZ_F * rb_pad(N) * 4;
   const int most = chunks < n_cu ? BWD_NBUF_MIN : BWD_NBUF;
   int nseg = (H + K - 1) / K < most ? (H + K - 1) / K : most;
@@ -1028,10 +1041,10 @@ void bwd_free(BwdBufs& bw) {
 // So the recompute of the next segments and the weight gradients of the
 // previous ones overlap the sweep.  The caller's stream finally waits for
 // the last weight-gradient pass before the fixed-order partial sum.
-// Overlap only pays while the sweep leaves compute units idle (fewer
-// workgroups than CUs); for large batches the sweep (one wave per SIMD, most
-// registers) fills the chip and everything stays on the caller's stream in
-// order.
+// Overlap only pays while the sweep leaves compute units idle (a workgroup of
+// the recompute takes a whole one); for large batches the sweep (one wave per
+// SIMD, most registers) fills the chip and everything stays on the caller's
+// stream in order.  Both sides measured: bwd_alloc.
 // serial: every kernel on st (the scratch-array variant, one buffer).
 static hipError_t backward_segments(const DevCfg& c, const SimBufs& b, const BwdBufs& bw,
                                     bool serial, const float* W, const float* tape, int K, int T,

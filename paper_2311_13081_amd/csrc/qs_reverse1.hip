@@ -27,10 +27,11 @@
 // of its env, where the observation's share joins the state and history
 // adjoints.  One wave per SIMD, so matrix and vector work add up rather than
 // overlap: per 64-env step 688 bf16 products of 16 cycles and about 2600 vector
-// instructions; with fp32 products (640 of 32 cycles) 16 steps of 65536 envs
-// took 402 us, now 286.  The per-step inputs and outputs use the blocked layouts of the
-// record and the cotangent buffer (row f of env e at (e / 64) F 64 + 64 f +
-// e % 64), so a lane's own-env rows are whole 256-byte rows of the wave.
+// instructions; with fp32 products (640 of 32 cycles) and dz2 stored 16 steps of
+// 65536 envs took 402 us, now 262.  The per-step inputs and outputs use the
+// blocked layouts of the record and the cotangent buffer (row f of env e at (e /
+// 64) F 64 + 64 f + e % 64), so a lane's own-env rows are whole 256-byte rows of
+// the wave.
 //
 // Fused multiply-adds only where one expression of the source holds the product
 // and the sum, so kernels that promise equal results round alike.
@@ -53,7 +54,8 @@ constexpr int L_W3T = 0, L_FRAG = L_W3T + NHID * NA, L_TOTAL = L_FRAG + 4 * RT_F
 // and a write of LDS per value, in registers an accumulator-register move or
 // two.  HR = 12 is the smallest at which the kernel spills no register (a spill
 // read back behind a step's stores waits for all of them): 16 steps of 65536
-// envs in 279 us, against 320 for 8 (14 spilled) and 284 for 16.
+// envs took 279 us (262 since dz2 is no longer stored), against 320 for 8 (14
+// spilled) and 284 for 16.
 constexpr int HR = 12;
 constexpr int L_RING = HR * NA * 64;
 constexpr int L_BYTES = (L_TOTAL + 4 * L_RING) * 4;

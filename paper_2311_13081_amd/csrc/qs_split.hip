@@ -6,9 +6,10 @@
 // tile layout (qs_tile.h), so every env sits on 16 lanes.  Wave w evaluates
 // unit tile w (16 units) of layers 1 and 2, a quarter of the matrix work, from
 // weight fragments that it keeps in registers (84 of them: no staging of
-// the actor in LDS and no weight reads in the loop); the layer-1 results are split into their bf16 parts by the wave that
-// owns them and exchanged through LDS as layer-2 operands, the layer-2 results
-// as fp32 tiles, with one barrier per layer.  Every wave then evaluates layer
+// the actor in LDS and no weight reads in the loop); the layer-1 results are
+// split into their bf16 parts by the wave that owns them and exchanged through LDS
+// as layer-2 operands, the layer-2 results
+// as fp32 tiles, with one barrier per layer (and one for the noise).  Every wave then evaluates layer
 // 3 and the dynamics of the 16 envs: the same arithmetic on identical inputs,
 // so the copies agree bit for bit, and the products are the tile kernel's in
 // its order, so its results are the same too.  Wave 0 writes the outputs.
@@ -16,9 +17,9 @@
 // What bounds it is the serial chain of a step: features, 6 dependent matrix
 // products, exchange, 12 products, exchange, layer 3, tanh, four right-hand
 // sides.  The history products of layer 1 (24 of its 30) are off the chain:
-// they run beside the right-hand sides of the step before.  4096 envs: 2.35 us
+// they run beside the right-hand sides of the step before.  4096 envs: 2.37 us
 // per step (3.15 us with fp32 products, the actor in LDS and every product on
-// the chain).  One wave per SIMD with up to 512 registers; two waves of 256
+// the chain; with noise 3.21).  One wave per SIMD with up to 512 registers; two waves of 256
 // spill and take 2.67 us there, 3.96 us at 8192 envs against 3.38 us for the
 // tile kernel.
 // Fused multiply-adds only where one expression of the source holds the
@@ -158,7 +159,8 @@ __device__ inline void actor_split(const SplitActor& A, SplitXch& xc, f4t (&a1)[
 // T steps of the whole env step for 16 envs per workgroup (blockDim 256).
 // A barrier separates each layer's writes of the exchange buffers from the
 // reads, and the next step's writes of a buffer come after the barrier that
-// follows every wave's reads of it, so two barriers per step suffice.
+// follows every wave's reads of it, so two barriers per step suffice; with
+// observation noise a third stands between its draws and their use.
 // TAPE: as the tile kernel: with tape != NULL, checkpoints every ckpt_every
 // steps; with ck_in != NULL the launch starts from that checkpoint (no
 // write-back of the env state); with rs.buf[0] != NULL the record of the span

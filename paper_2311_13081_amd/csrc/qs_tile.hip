@@ -52,7 +52,11 @@ constexpr int T_MAX_THREADS = 512;
 // hover speed and each tile's hover action, and the next start state.  Left to
 // the compiler they are spilled to memory, and reading a spill back waits for
 // every store issued before it: recorded steps of 65536 envs took 19.1 us with 85
-// spills (and 1.1 GB written for 0.64 GB of record per 16 steps), now 12.
+// spills (and 1.1 GB written for 0.64 GB of record per 16 steps), now 12.  Spills
+// that are left, by the compiler's count: 9 (two tiles), 20 (with the record), 32 and
+// 48 (one, two tiles with the extras), 30 and 59 (with both); without the extras
+// those in the loop lie around draws and resets, with them a step stores 16 to 27
+// and reads as many back around the noise.
 enum { PK_NEXT = 0, PK_ACC = NRES, PK_HOVER = PK_ACC + 3, PK_AH = PK_HOVER + 1, PK_BODY = PK_AH + 2 };
 constexpr int PK_F = PK_BODY + sizeof(Body<float>) / 4;
 struct Park {
