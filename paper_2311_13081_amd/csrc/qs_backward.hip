@@ -105,13 +105,13 @@ __device__ __forceinline__ void load_step(StepIn& in, __amdgpu_buffer_rsrc_t rre
 // of quarter k = the cotangent of feature PHI(4p + r, k)): shifts the
 // history adjoint (H_t[s] feeds H_{t+1}[s-1]), gathers the 18 state features
 // from the quarters, adds them (through R(q)) to gx and forms the state
-// adjoint before the step, ls = gx + dS.
+// adjoint before the step, ls = gx + dS.  sgn: do's sign (dz_sign).
 __device__ __forceinline__ void reverse_observation(const float dob[40], const float x[NS],
-                                                    const float dS[NS], int j, float gx[NS],
-                                                    float lH[NH], float ls[NS]) {
+                                                    const float dS[NS], float sgn, int j,
+                                                    float gx[NS], float lH[NH], float ls[NS]) {
   // descending s reads the older adjoint before it is overwritten
 #pragma unroll
-  for (int s = NH - 1; s >= 0; --s) lH[s] = (s >= 1 ? lH[s - 1] : 0.0f) + dob[5 + s];
+  for (int s = NH - 1; s >= 0; --s) lH[s] = fmaf(sgn, dob[5 + s], s >= 1 ? lH[s - 1] : 0.0f);
   // state features 4cc + q live in quarter q: gather them into every lane
   float gf[20];
 #pragma unroll
@@ -122,16 +122,16 @@ __device__ __forceinline__ void reverse_observation(const float dob[40], const f
           __builtin_amdgcn_ds_bpermute((j + 16 * q) << 2, __float_as_int(dob[cc])));
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-    gx[i] += gf[i];
-    gx[7 + i] += gf[12 + i];
-    gx[10 + i] += gf[15 + i];
+    gx[i] = fmaf(sgn, gf[i], gx[i]);
+    gx[7 + i] = fmaf(sgn, gf[12 + i], gx[7 + i]);
+    gx[10 + i] = fmaf(sgn, gf[15 + i], gx[10 + i]);
   }
   {
     float gq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     const float q[4] = {x[3], x[4], x[5], x[6]};
     rotmat_vjp(q, gf + 3, gq);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) gx[3 + i] += gq[i];
+    for (int i = 0; i < 4; ++i) gx[3 + i] = fmaf(sgn, gq[i], gx[3 + i]);
   }
 #pragma unroll
   for (int i = 0; i < NS; ++i) ls[i] = gx[i] + dS[i];
@@ -210,6 +210,7 @@ k_bwd_reverse(DevCfg c, const float* __restrict__ theta, const float* __restrict
   const Quad B = make_rev_quad(c, th, dist);
   const RevStep rs = make_rev_step(c);
   const bool renorm = (c.flags & F_RENORM_Q) != 0;
+  const float sgn = wave_const(dz_sign(env0));  // of all 16 envs
 
   float ls[NS], lH[NH], gth[NP];
 #pragma unroll
@@ -255,7 +256,7 @@ k_bwd_reverse(DevCfg c, const float* __restrict__ theta, const float* __restrict
 #pragma unroll
     for (int i = 0; i < NA; ++i) d3[i] = ga[i] * (1.0f - cur.a[i] * cur.a[i]);
     const float d3e = k == 0 ? d3[0] : k == 1 ? d3[1] : k == 2 ? d3[2] : d3[3];
-    const float d3k = active ? d3e : 0.0f;
+    const float d3k = active ? sgn * d3e : 0.0f;
     if (!SPLIT || w == 0) bst1(d3k, rdz, vz1, sz + 4u * DZ_3 * RB);
     // do = W1^T dz1 in observation order: tile p, register r of quarter k is
     // the cotangent of feature PHI(4p + r, k)
@@ -339,7 +340,7 @@ k_bwd_reverse(DevCfg c, const float* __restrict__ theta, const float* __restrict
         for (int r = 0; r < 4; ++r) dob[4 * p + r] = v[r];
       }
     }
-    reverse_observation(dob, cur.x, cur.dS, j, gx, lH, ls);
+    reverse_observation(dob, cur.x, cur.dS, sgn, j, gx, lH, ls);
     cur = nxt;
   }
   if (!active || w != 0) return;
@@ -368,8 +369,8 @@ k_bwd_reverse(DevCfg c, const float* __restrict__ theta, const float* __restrict
 // (the bias) make the tiles 0..9, layer 2's 64 columns the tiles 10..13, layer
 // 3's the tiles 14..17.  Waves g and g + 4 run column group g on the two slab
 // pairs of each step (two waves per SIMD, so one's loads and splitting overlap
-// the other's matrix work) and add their sums through LDS at the end, half 0
-// first.  A group owns three tiles with their 4 neuron tiles -- {g, g + 4} of
+// the other's matrix work); at the end the second's sums, of the opposite sign
+// (dz_sign), are taken from the first's through LDS.  A group owns three tiles with their 4 neuron tiles -- {g, g + 4} of
 // layer 1 and 10 + g of layer 2 --, neuron tile g of the shared tiles 8 and 9, tile
 // 14 + g of layer 3 (A's rows are the 4 outputs, repeated) and layer 2's bias of
 // its neuron tile (a product with ones; group 2 layer 3's too), so the groups
@@ -853,7 +854,7 @@ k_bwd_dw(int N, const float* __restrict__ W, const float* __restrict__ rec,
     default: dw_chunks<3, BF16>(acc, rec, dz, N, t_lo, t_hi, K, half, sA, tw, w3); break;
   }
   __syncthreads();  // the staging space becomes the exchange buffer
-  // half 1 hands its sums to half 0 (fixed order: half 0 + half 1)
+  // half 1 hands its sums, of the opposite sign, to half 0
   if (half == 1)
 #pragma unroll
     for (int i = 0; i < DW_NACC; ++i) xacc[g][i][lane] = acc[i];
@@ -863,7 +864,7 @@ k_bwd_dw(int N, const float* __restrict__ W, const float* __restrict__ rec,
   for (int i = 0; i < DW_NACC; ++i) {
     const f4 o = xacc[g][i][lane];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) acc[i][r] += o[r];
+    for (int r = 0; r < 4; ++r) acc[i][r] -= o[r];
   }
   // add into this group's part of the slot: all loads, then all stores
   f4* gp = reinterpret_cast<f4*>(gpart + ((size_t)blockIdx.x * S + sg) * DW_SLOT) + g * DW_NACC * 64;

@@ -135,6 +135,7 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
   const Quad B = make_rev_quad(c, th, dist);
   const RevStep rs = make_rev_step(c);
   const bool renorm = (c.flags & F_RENORM_Q) != 0;
+  const float sgn = dz_sign(lane);
 
   // history adjoint: slot s < HR at ring row (s + base) mod HR, slot s >= HR
   // in lR[s - HR]
@@ -177,7 +178,7 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
     float d3[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-      d3[i] = active ? ga[i] * (1.0f - cur.a[i] * cur.a[i]) : 0.0f;
+      d3[i] = active ? sgn * (ga[i] * (1.0f - cur.a[i] * cur.a[i])) : 0.0f;
       bst1(d3[i], rdz, vlane, sz + 4u * (DZ_3 + i) * RB);
     }
     // dz2 = (W3^T dz3) [z2 > 0]: one rank-1 update per action
@@ -285,9 +286,9 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
             gf[f] = val[x];
           } else if (f < 18 + HR * NA) {
             const int row = (sl + base) % HR;
-            ring[(row * NA + a) * 64] += val[x];
+            ring[(row * NA + a) * 64] = fmaf(sgn, val[x], ring[(row * NA + a) * 64]);
           } else if (f < NO) {
-            lR[sl - HR][a] += val[x];
+            lR[sl - HR][a] = fmaf(sgn, val[x], lR[sl - HR][a]);
           }
         }
       }
@@ -295,16 +296,16 @@ k_bwd_reverse1(DevCfg c, const float* __restrict__ theta, const float* __restric
     // the state features' share: p, v, w directly, R(q) through its VJP
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-      gx[i] += gf[i];
-      gx[7 + i] += gf[12 + i];
-      gx[10 + i] += gf[15 + i];
+      gx[i] = fmaf(sgn, gf[i], gx[i]);
+      gx[7 + i] = fmaf(sgn, gf[12 + i], gx[7 + i]);
+      gx[10 + i] = fmaf(sgn, gf[15 + i], gx[10 + i]);
     }
     {
       float gq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
       const float q[4] = {cur.x[3], cur.x[4], cur.x[5], cur.x[6]};
       rotmat_vjp(q, gf + 3, gq);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) gx[3 + i] += gq[i];
+      for (int i = 0; i < 4; ++i) gx[3 + i] = fmaf(sgn, gq[i], gx[3 + i]);
     }
 #pragma unroll
     for (int i = 0; i < NS; ++i) ls[i] = gx[i] + cur.dS[i];
