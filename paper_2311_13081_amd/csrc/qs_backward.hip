@@ -882,16 +882,19 @@ k_bwd_dw(int N, const float* __restrict__ W, const float* __restrict__ rec,
 // grad[i] = sum over the G partial slots of slot g's entry for i, in a fixed
 // order:
 // DR_SPLIT threads per output each add a contiguous range of slots in
-// ascending order, then the range sums are added in ascending range order.
+// ascending order, then the range sums are added in ascending range order, in
+// double (the kernel waits for memory, 11 us either way): in single precision these
+// sums alone add a tenth to the error of the actor gradients (16384 envs x 32 steps
+// 1.06e-7, with this 9.4e-8).
 constexpr int DR_OUT = 32, DR_SPLIT = 8;
 __global__ void __launch_bounds__(DR_OUT * DR_SPLIT)
 k_bwd_reduce(const float* __restrict__ gpart, int G, float* __restrict__ out) {
-  __shared__ float part[DR_SPLIT][DR_OUT];
+  __shared__ double part[DR_SPLIT][DR_OUT];
   const int tx = threadIdx.x % DR_OUT, ty = threadIdx.x / DR_OUT;
   const int i = blockIdx.x * DR_OUT + tx;
   const int per = (G + DR_SPLIT - 1) / DR_SPLIT;
   const int g0 = ty * per, g1 = (g0 + per) < G ? (g0 + per) : G;
-  float s = 0.0f;
+  double s = 0.0;
   if (i < NW) {
     const int pl = dw_slot(i);
 #pragma unroll 8
@@ -900,10 +903,10 @@ k_bwd_reduce(const float* __restrict__ gpart, int G, float* __restrict__ out) {
   part[ty][tx] = s;
   __syncthreads();
   if (ty != 0 || i >= NW) return;
-  float t = part[0][tx];
+  double t = part[0][tx];
 #pragma unroll
   for (int r = 1; r < DR_SPLIT; ++r) t += part[r][tx];
-  out[i] = t;
+  out[i] = (float)t;
 }
 
 __global__ void k_copy(const float* __restrict__ src, float* __restrict__ dst, size_t n) {
