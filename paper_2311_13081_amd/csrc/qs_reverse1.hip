@@ -28,7 +28,7 @@
 // adjoints.  One wave per SIMD, so matrix and vector work add up rather than
 // overlap: per 64-env step 688 bf16 products of 16 cycles and about 2600 vector
 // instructions; with fp32 products (640 of 32 cycles) and dz2 stored 16 steps of
-// 65536 envs took 402 us, now 262.  The per-step inputs and outputs use the
+// 65536 envs took 402 us, now 257.  The per-step inputs and outputs use the
 // blocked layouts of the record and the cotangent buffer (row f of env e at (e /
 // 64) F 64 + 64 f + e % 64), so a lane's own-env rows are whole 256-byte rows of
 // the wave.
@@ -54,7 +54,7 @@ constexpr int L_W3T = 0, L_FRAG = L_W3T + NHID * NA, L_TOTAL = L_FRAG + 4 * RT_F
 // and a write of LDS per value, in registers an accumulator-register move or
 // two.  HR = 12 is the smallest at which the kernel spills no register (a spill
 // read back behind a step's stores waits for all of them): 16 steps of 65536
-// envs took 279 us (262 since dz2 is no longer stored), against 320 for 8 (14
+// envs took 279 us (257 since dz2 is no longer stored), against 320 for 8 (14
 // spilled) and 284 for 16.
 constexpr int HR = 12;
 constexpr int L_RING = HR * NA * 64;

@@ -17,9 +17,9 @@
 // What bounds it is the serial chain of a step: features, 6 dependent matrix
 // products, exchange, 12 products, exchange, layer 3, tanh, four right-hand
 // sides.  The history products of layer 1 (24 of its 30) are off the chain:
-// they run beside the right-hand sides of the step before.  4096 envs: 2.37 us
+// they run beside the right-hand sides of the step before.  4096 envs: 2.25 us
 // per step (3.15 us with fp32 products, the actor in LDS and every product on
-// the chain; with noise 3.21).  One wave per SIMD with up to 512 registers; two waves of 256
+// the chain; with noise 3.0).  One wave per SIMD with up to 512 registers; two waves of 256
 // spill and take 2.67 us there, 3.96 us at 8192 envs against 3.38 us for the
 // tile kernel.
 // Fused multiply-adds only where one expression of the source holds the
